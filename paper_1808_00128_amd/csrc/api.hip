@@ -92,6 +92,8 @@ struct Instance {
   double l1 = 1.0;
   bool at_zero = true;  // every term is |0^n> and the store holds nothing yet
   bool amp_ready = false;  // the amplitude prologue output matches the terms
+  bool mfma_ready = false;  // the matrix-core prologue output matches the terms
+  bool mfma_off = false;    // its buffers did not fit: the table kernel serves this instance
   EvolveShape shape;    // evolution mapping (0 = default for n)
   bool autotune = false;  // time every shape at the next from-|0^n> evolution
   float tuned_ms[kTuneShapes] = {};     // per tuned shape, kTuneLanes order (0 = not timed)
@@ -108,6 +110,8 @@ struct Instance {
   // amplitude prologue output
   DevBuf<uint64_t> acrow;
   DevBuf<AmpTerm> acst;
+  DevBuf<uint8_t> mrec;    // matrix-core tile records and condition words
+  DevBuf<uint64_t> mcond;
   // shared-prefix evolution: knob, cached plan of the last gate list
   int prefix_mode = 1;  // 0 off, 1 auto, 2 always when it saves any work
   bool plan_valid = false;
@@ -187,7 +191,7 @@ struct Instance {
     F.release(); G.release(); M.release(); v.release(); s.release();
     gamma.release(); omega.release(); branch.release(); b.release();
     slots.release();
-    acrow.release(); acst.release();
+    acrow.release(); acst.release(); mrec.release(); mcond.release();
     plan_slot.release(); plan_width.release(); plan_count.release();
     mstate0.release(); mpmask.release(); mx.release(); mtrace.release();
     mpend.release(); mj.release(); mamp.release(); mpartial.release(); mu.release(); macc.release();
@@ -218,6 +222,14 @@ struct chsim_ctx {
   DevBuf<uint64_t> amp_prefix;
   DevBuf<uint32_t> amp_counter;
   std::vector<AmpInst> amp_key;
+  // Matrix-core amplitudes: device copy of the last plan (requests, string
+  // prefix, work items in one buffer), its host key and shape key.
+  DevBuf<uint64_t> mplan;
+  std::vector<AmpMfmaInst> mplan_key;
+  std::vector<uint64_t> mshape_key;
+  std::vector<AmpItem> mitems_h;
+  std::vector<uint32_t> mtpr, mrows;
+  uint32_t m_split = 0;
   uint32_t amp_n_items = 0;
   hipStream_t cap_stream = nullptr;  // stream the Metropolis graphs are recorded on
   // The last gate list as given (instance, raw gates) and as converted; a call
@@ -383,7 +395,7 @@ chsim_status ensure_materialised(Instance& I, hipStream_t st) {
   if (!I.at_zero) return CHSIM_OK;
   HIP_TRY(launch_set_zero(I.view(), st));
   I.at_zero = false;
-  I.amp_ready = false;
+  I.amp_ready = I.mfma_ready = false;
   return CHSIM_OK;
 }
 
@@ -494,7 +506,7 @@ chsim_status chsim_terms_reset(chsim_ctx* ctx, uint32_t inst, uint64_t seed, voi
   const double scale = I.l1 / (double)I.chi;
   HIP_TRY(launch_choose(I.view(), I.slots.p, I.mode, I.seed, scale, as_stream(stream)));
   I.at_zero = true;
-  I.amp_ready = false;
+  I.amp_ready = I.mfma_ready = false;
   I.drop_chains();
   return CHSIM_OK;
 }
@@ -996,7 +1008,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
     if (st) return st;
   }
   I.at_zero = false;
-  I.amp_ready = false;
+  I.amp_ready = I.mfma_ready = false;
   return check_err_flag(ctx, s, "apply_clifford");
 }
 
@@ -1021,8 +1033,127 @@ chsim_status ensure_amp_prep(Instance& I, hipStream_t s) {
   return CHSIM_OK;
 }
 
-// Plan, upload the plan if it differs from the last one, and launch.
+// The matrix-core prologue, if the terms changed since.  An instance whose
+// records do not fit beside its term store stays with the table kernel, whose
+// prologue output is smaller.
+chsim_status ensure_mfma_prep(Instance& I, hipStream_t s) {
+  if (I.mfma_ready || I.mfma_off) return CHSIM_OK;
+  const size_t tiles = (I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile;
+  hipError_t e = I.mrec.ensure(tiles * amp_mfma_tile_bytes(I.n));
+  if (e == hipSuccess) e = I.mcond.ensure(tiles * I.n * kAmpMfmaTile);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    I.mrec.release();
+    I.mcond.release();
+    I.mfma_off = true;
+    return CHSIM_OK;
+  }
+  HIP_TRY(e);
+  HIP_TRY(launch_amp_mfma_prep(I.view(), I.mrec.p, I.mcond.p, s));
+  I.mfma_ready = true;
+  return CHSIM_OK;
+}
+
+// Plan, upload the plan if it differs from the last one, and launch the
+// matrix-core kernel (every request's instance has its prologue output).
+chsim_status run_amplitudes_mfma(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, hipStream_t s) {
+  const size_t R = reqs.size();
+  std::vector<uint64_t> shape_key;
+  shape_key.reserve(3 * R);
+  for (const auto& r : reqs) {
+    const Instance& I = ctx->inst[r.inst];
+    shape_key.push_back(I.n);
+    shape_key.push_back(r.n_x);
+    shape_key.push_back(I.chi);
+  }
+  if (shape_key != ctx->mshape_key) {
+    std::vector<AmpRequestPlan> plan;
+    for (const auto& r : reqs) plan.push_back(AmpRequestPlan{ctx->inst[r.inst].n, r.n_x, ctx->inst[r.inst].chi});
+    ctx->mshape_key.clear();  // invalid until the plan is whole
+    ctx->mplan_key.clear();
+    amp_mfma_plan(plan, ctx->mitems_h, &ctx->m_split, ctx->mtpr, ctx->mrows);
+    ctx->mshape_key = shape_key;
+  }
+  size_t part = 0;
+  uint64_t total_x = 0;
+  uint32_t max_steps = 0;
+  for (size_t q = 0; q < R; ++q) {
+    part += (size_t)ctx->mrows[q] * reqs[q].n_x;
+    total_x += reqs[q].n_x;
+    max_steps = std::max(max_steps, amp_mfma_steps(ctx->inst[reqs[q].inst].n));
+  }
+  HIP_TRY(ctx->partial.ensure(part));
+  std::vector<AmpMfmaInst> insts(R);
+  size_t off = 0;
+  for (size_t q = 0; q < R; ++q) {
+    Instance& I = ctx->inst[reqs[q].inst];
+    AmpMfmaInst a;
+    std::memset(&a, 0, sizeof a);
+    a.rec = I.mrec.p;
+    a.cond = I.mcond.p;
+    a.x = reqs[q].x;
+    a.partial = ctx->partial.p + off;
+    a.out = reqs[q].out;
+    a.n = I.n;
+    a.steps = amp_mfma_steps(I.n);
+    a.tiles = (uint32_t)((I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile);
+    a.n_x = reqs[q].n_x;
+    a.tiles_per_range = ctx->mtpr[q];
+    a.rows = ctx->mrows[q];
+    insts[q] = a;
+    off += (size_t)ctx->mrows[q] * reqs[q].n_x;
+  }
+  // One device buffer: the requests, the string prefix, the items.
+  const size_t w_inst = R * sizeof(AmpMfmaInst) / 8, w_items = ctx->mitems_h.size() * sizeof(AmpItem) / 8;
+  const bool same = ctx->mplan_key.size() == R &&
+                    std::memcmp(insts.data(), ctx->mplan_key.data(), R * sizeof(AmpMfmaInst)) == 0;
+  if (!same) {
+    std::vector<uint64_t> words(w_inst + R + 1 + w_items + 1, 0);
+    std::memcpy(words.data(), insts.data(), R * sizeof(AmpMfmaInst));
+    for (size_t q = 0; q < R; ++q) words[w_inst + q + 1] = words[w_inst + q] + reqs[q].n_x;
+    const size_t at = (w_inst + R + 2) & ~(size_t)1;  // items are 16 bytes
+    std::memcpy(words.data() + at, ctx->mitems_h.data(), w_items * 8);
+    ctx->mplan_key.clear();
+    HIP_TRY(ctx->mplan.ensure(words.size()));
+    HIP_TRY(hipMemcpyAsync(ctx->mplan.p, words.data(), words.size() * 8, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));  // the host vector dies with this call
+    ctx->mplan_key = insts;
+  }
+  const uint64_t* base = ctx->mplan.p;
+  HIP_TRY(launch_amp_mfma(reinterpret_cast<const AmpMfmaInst*>(base),
+                          reinterpret_cast<const AmpItem*>(base + ((w_inst + R + 2) & ~(size_t)1)),
+                          (uint32_t)ctx->mitems_h.size(), ctx->m_split, max_steps, fp32c, base + w_inst, (uint32_t)R,
+                          total_x, s));
+  return CHSIM_OK;
+}
+
+chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, uint32_t xpl,
+                                  hipStream_t s);
+
+// The matrix cores take every request with n <= 60 (the bits of a string, the
+// constant and three spare features fit one 64-feature condition operand); the
+// table kernel the others.
 chsim_status run_amplitudes_xpl(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, uint32_t xpl,
+                                hipStream_t s) {
+  std::vector<AmpReq> mf, tb;
+  for (const auto& r : reqs) {
+    Instance& I = ctx->inst[r.inst];
+    const bool fits = I.n <= kAmpMfmaMaxN && (I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile <= 0x7FFFFFFFull;
+    if (fits) {
+      chsim_status st = ensure_mfma_prep(I, s);
+      if (st) return st;
+    }
+    (fits && !I.mfma_off ? mf : tb).push_back(r);
+  }
+  if (!mf.empty()) {
+    chsim_status st = run_amplitudes_mfma(ctx, mf, fp32c, s);
+    if (st) return st;
+  }
+  return tb.empty() ? CHSIM_OK : run_amplitudes_table(ctx, tb, fp32c, xpl, s);
+}
+
+// The table kernel's plan, uploaded if it differs from the last one, and launch.
+chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, uint32_t xpl,
                                 hipStream_t s) {
   for (const auto& r : reqs) {
     chsim_status st = ensure_amp_prep(ctx->inst[r.inst], s);
@@ -1689,7 +1820,7 @@ chsim_status chsim_set_terms(chsim_ctx* ctx, uint32_t inst, uint64_t first, uint
   HIP_TRY(hipMemcpy(I.s.p + first, s, count * 8, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(I.omega.p + first, omega, count, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(I.b.p + first, b, count * 16, hipMemcpyHostToDevice));
-  I.amp_ready = false;
+  I.amp_ready = I.mfma_ready = false;
   return CHSIM_OK;
 }
 
@@ -1932,7 +2063,7 @@ chsim_status run_projection(chsim_ctx* ctx, uint32_t inst, const ProjGates& P, v
   I.drop_chains();
   HIP_TRY(hipMemsetAsync(ctx->err.p, 0, sizeof(uint32_t), s));
   HIP_TRY(launch_project(I.view(), P, ctx->err.p, s));
-  I.amp_ready = false;
+  I.amp_ready = I.mfma_ready = false;
   return check_err_flag(ctx, s, "projection");
 }
 
@@ -2014,7 +2145,7 @@ chsim_status chsim_terms_copy(chsim_ctx* ctx, uint32_t src_inst, uint32_t dst_in
   if (A.n_slot == D.n_slot && A.n_slot)
     HIP_TRY(hipMemcpyAsync(d.branch, a.branch, (size_t)A.n_slot * A.chi, hipMemcpyDeviceToDevice, s));
   D.at_zero = false;
-  D.amp_ready = false;
+  D.amp_ready = D.mfma_ready = false;
   return CHSIM_OK;
 }
 
@@ -2091,6 +2222,7 @@ chsim_status chsim_destroy(chsim_ctx* ctx) {
   ctx->amp_items.release();
   ctx->amp_prefix.release();
   ctx->amp_counter.release();
+  ctx->mplan.release();
   ctx->slotseq.release();
   ctx->pf_table.release();
   ctx->pf_ids.release();

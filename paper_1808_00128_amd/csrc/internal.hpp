@@ -247,6 +247,33 @@ hipError_t launch_amp_items(const AmpInst* insts_d, const AmpItem* items_d, uint
                             uint32_t* counter, bool fp32c, uint32_t xpl, const uint64_t* prefix_d,
                             uint32_t n_inst, uint64_t total_x, hipStream_t st);
 
+// Amplitudes on the matrix cores (n <= kAmpMfmaMaxN, amplitude_mfma.hip).  Per
+// tile of kAmpMfmaTile terms a record of amp_mfma_tile_bytes(n) (weights,
+// values, the first condition words) and n x kAmpMfmaTile further condition
+// words, computed once per term set; steps = amp_mfma_steps(n).
+constexpr uint32_t kAmpMfmaTile = 32, kAmpMfmaMaxN = 60;
+struct AmpMfmaInst {
+  const uint8_t* rec;    // [tiles][amp_mfma_tile_bytes]
+  const uint64_t* cond;  // [tiles][n][32]
+  const uint64_t* x;
+  double2* partial;  // [rows][n_x]
+  double2* out;      // [n_x]
+  uint32_t n, steps, tiles, n_x;
+  uint32_t tiles_per_range;
+  uint32_t rows;  // partial sums per string
+};
+uint32_t amp_mfma_steps(uint32_t n);
+uint32_t amp_mfma_tile_bytes(uint32_t n);
+hipError_t launch_amp_mfma_prep(const TermsView& T, uint8_t* rec, uint64_t* cond, hipStream_t st);
+// Work items in launch order (item i is workgroup i; the last n_split items
+// are those whose waves split the tiles), tiles per range and partial sums per
+// string of each request.
+void amp_mfma_plan(const std::vector<AmpRequestPlan>& reqs, std::vector<AmpItem>& items, uint32_t* n_split,
+                   std::vector<uint32_t>& tiles_per_range, std::vector<uint32_t>& rows);
+hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items, uint32_t n_split,
+                           uint32_t max_steps, bool fp32c, const uint64_t* prefix_d, uint32_t n_inst,
+                           uint64_t total_x, hipStream_t st);
+
 // Inner products with equatorial states: L states in batches of 64 (Lp =
 // L rounded up), partial sums per term group, and a device workspace of
 // work_words 8-byte words (per-term records and A rearranged by state).
