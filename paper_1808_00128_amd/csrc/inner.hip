@@ -497,17 +497,36 @@ __global__ __launch_bounds__(64, NMAX <= 40 ? 3 : 2) void k_inner_pairs(TermsVie
   if (l < L) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
 }
 
+// overlap_l = the sum of the groups' partials in FP64, in a fixed order: a
+// 256-thread block takes 8 states and 32 slices of the groups, and the slice
+// sums are added in slice order (one thread per state walking 512 groups took
+// 122 us for 100 states, a serial chain of loads; this takes 5 us).
+constexpr uint32_t kRedX = 8, kRedSlices = 32;
 __global__ __launch_bounds__(256) void k_inner_reduce(const double2* __restrict__ partial,
                                                       uint32_t n_blocks, uint32_t L, uint32_t n,
                                                       double2* __restrict__ overlap,
                                                       double* __restrict__ eta) {
-  const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= L) return;
+  __shared__ double2 part[kRedSlices][kRedX];
+  const uint32_t xl = threadIdx.x % kRedX, sl = threadIdx.x / kRedX;
+  const uint32_t l = blockIdx.x * kRedX + xl;
   double re = 0.0, im = 0.0;
-  for (uint32_t b = 0; b < n_blocks; ++b) {
-    const double2 v = partial[(uint64_t)b * L + l];
-    re += v.x;
-    im += v.y;
+  if (l < L) {
+    const uint32_t b0 = (uint32_t)((uint64_t)n_blocks * sl / kRedSlices);
+    const uint32_t b1 = (uint32_t)((uint64_t)n_blocks * (sl + 1) / kRedSlices);
+#pragma unroll 4
+    for (uint32_t b = b0; b < b1; ++b) {
+      const double2 v = partial[(uint64_t)b * L + l];
+      re += v.x;
+      im += v.y;
+    }
+  }
+  part[sl][xl] = make_double2(re, im);
+  __syncthreads();
+  if (sl != 0 || l >= L) return;
+  re = im = 0.0;
+  for (uint32_t k = 0; k < kRedSlices; ++k) {
+    re += part[k][xl].x;
+    im += part[k][xl].y;
   }
   overlap[l] = make_double2(re, im);
   eta[l] = ldexp(re * re + im * im, (int)n);
@@ -530,13 +549,22 @@ __global__ __launch_bounds__(256) void k_eta_sum(const double* __restrict__ eta,
 
 }  // namespace
 
-constexpr uint32_t kTermGroups = 512;  // waves per batch of 64 states, each over chi / 512 terms
+// Waves per batch of 64 states, each over chi / groups terms: 512, and with
+// few batches as many more as fill the chip (3 waves per SIMD, 3072 in all): a
+// wave's terms are a serial chain, and 2 batches of 512 waves left two thirds
+// of the places empty (n = 20, chi = 3001, 100 states: 126 us, with 1536 groups
+// 59 us).  A multiple of 8 (the XCD-aware block order).
+uint32_t term_groups(uint64_t chi, uint32_t n_batches) {
+  const uint32_t want = std::max<uint32_t>(512u, 3072u / n_batches);
+  const uint32_t g = (uint32_t)std::min<uint64_t>(want, chi);
+  return g >= 8u ? g & ~7u : g;
+}
 
 InnerPlan inner_plan(const TermsView& T, uint32_t L) {
   InnerPlan P;
   P.Lp = (L + 63u) / 64u * 64u;
   P.n_batches = P.Lp / 64u;
-  P.n_groups = (uint32_t)std::min<uint64_t>(kTermGroups, T.chi);
+  P.n_groups = term_groups(T.chi, P.n_batches);
   P.partial_elems = (size_t)P.n_groups * L;
   P.work_words = (size_t)T.chi * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
   return P;
@@ -575,7 +603,7 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_inner_reduce, dim3((L + 255) / 256), dim3(256), 0, st, partial, P.n_groups, L,
+  hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, P.n_groups, L,
                      T.n, overlap, eta);
   e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -430,15 +430,33 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   if (lane == 0u) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
 }
 
+// overlap_l = the sum of the groups' partials in FP64, in a fixed order: 8
+// states and 32 slices of the groups per block, the slice sums added in slice
+// order (one thread per state walking 512 groups took 123 us).
+constexpr uint32_t kRedX = 8, kRedSlices = 32;
 __global__ __launch_bounds__(256) void k_inner_ch_reduce(const double2* __restrict__ partial, uint32_t groups,
                                                          uint32_t L, double2* __restrict__ overlap) {
-  const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= L) return;
+  __shared__ double2 part[kRedSlices][kRedX];
+  const uint32_t xl = threadIdx.x % kRedX, sl = threadIdx.x / kRedX;
+  const uint32_t l = blockIdx.x * kRedX + xl;
   double re = 0.0, im = 0.0;
-  for (uint32_t g = 0; g < groups; ++g) {
-    const double2 v = partial[(uint64_t)g * L + l];
-    re += v.x;
-    im += v.y;
+  if (l < L) {
+    const uint32_t g0 = (uint32_t)((uint64_t)groups * sl / kRedSlices);
+    const uint32_t g1 = (uint32_t)((uint64_t)groups * (sl + 1) / kRedSlices);
+#pragma unroll 4
+    for (uint32_t g = g0; g < g1; ++g) {
+      const double2 v = partial[(uint64_t)g * L + l];
+      re += v.x;
+      im += v.y;
+    }
+  }
+  part[sl][xl] = make_double2(re, im);
+  __syncthreads();
+  if (sl != 0 || l >= L) return;
+  re = im = 0.0;
+  for (uint32_t k = 0; k < kRedSlices; ++k) {
+    re += part[k][xl].x;
+    im += part[k][xl].y;
   }
   overlap[l] = make_double2(re, im);
 }
@@ -498,7 +516,7 @@ hipError_t launch_inner_ch(const uint64_t* rec_k, const double2* b_k, uint64_t c
                      L, n, groups, bra_blocks, partial, err);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_inner_ch_reduce, dim3((L + 255u) / 256u), dim3(256), 0, st, partial, groups, L, overlap);
+  hipLaunchKernelGGL(k_inner_ch_reduce, dim3((L + kRedX - 1u) / kRedX), dim3(256), 0, st, partial, groups, L, overlap);
   e = hipGetLastError();
   if (e != hipSuccess || !total) return e;
   hipLaunchKernelGGL(k_inner_ch_total, dim3(1), dim3(256), 0, st, overlap, b_bra, L, total);
