@@ -136,7 +136,7 @@ KERNEL_SOURCES = {
     "k_evolve": ["evolve_kernel.hpp", "evolve.hip", "evolve_l4.hip", "evolve_l8.hip",
                  "evolve_wide.hip", "evolve_w64.hip", "prefix.hip", "device_common.hpp", "internal.hpp",
                  "api.hip"],
-    "k_evolve_lds": ["evolve_lds.hip", "hrow.hpp", "evolve_w64.hip", "evolve.hip", "prefix.hip",
+    "k_evolve_cols": ["evolve_cols.hpp", "bitops.hpp", "evolve_w64.hip", "evolve.hip", "prefix.hip",
                      "device_common.hpp", "internal.hpp", "api.hip"],
     "k_amp<float>": ["amplitude.hip", "device_common.hpp", "internal.hpp", "api.hip"],
     "k_inner_pairs": ["inner.hip", "device_common.hpp", "internal.hpp", "api.hip"],
@@ -172,10 +172,10 @@ def counter_traffic(kernel):
 
 
 def shape_name(value):
-    """Evolution mapping of a lanes value: lanes per term and where the rows live."""
+    """Evolution mapping of a lanes value: lanes per term and what they hold."""
     lanes = value & 0xff
-    where = "LDS" if value & 0x100 else "registers"
-    return f"{lanes} lanes/term, rows in {where}"
+    what = "columns" if value & 0x100 else "rows"
+    return f"{lanes} lanes/term, {what} in registers"
 
 
 def mean_popcount(words):
@@ -703,7 +703,7 @@ def main():
                          "hardware byte counters can be scaled against a kernel of known traffic")
     ap.add_argument("--evolve-lanes", type=lambda v: int(v, 0), default=-1,
                     help="evolution mapping: -1 autotunes during warmup (default); otherwise a lanes "
-                         "value (e.g. 0x108 = 8 lanes per term, rows in LDS), so that counter runs "
+                         "value (e.g. 0x108 = 8 lanes per term, columns in registers), so that counter runs "
                          "repeat the launches of a timed run")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -803,9 +803,9 @@ def main():
     ms_reset = float(np.mean(phase["reset"]))
     executed_apps = sum(ev_stats[k] for k in ("H", "CX", "CZ", "S", "cond"))
     if ms_ev >= ms_amp:
-        dom = (f"{'k_evolve_lds' if lanes & B.CHSIM_EVOLVE_LDS else 'k_evolve'}<{lanes & 0xff},...> "
+        dom = (f"{'k_evolve_cols' if lanes & B.CHSIM_EVOLVE_LDS else 'k_evolve'}<{lanes & 0xff},...> "
                f"(CH-form evolution, {shape_name(lanes)}; all evolution launches of one step)")
-        traffic = counter_traffic("k_evolve_lds" if lanes & B.CHSIM_EVOLVE_LDS else "k_evolve")
+        traffic = counter_traffic("k_evolve_cols" if lanes & B.CHSIM_EVOLVE_LDS else "k_evolve")
         roofline = roof("alu", ops_sv / (ms_ev / 1e3) / 1e12, INT32_PEAK_OPS / 1e12, "TOP/s (int32)",
                         MEASURED.get("valu"), kernel=dom, traffic=traffic,
                         traffic_unit="bytes per launch (rocprofv3 FETCH_SIZE x 2 + WRITE_SIZE)",

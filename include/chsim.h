@@ -410,8 +410,10 @@ chsim_status chsim_decompose_ccz(uint32_t a, uint32_t b, uint32_t c, double coef
  * EVOLVE_LANES: lanes per term in the evolution kernel (4, 8, 16, 32 or 64;
  * a wave holds 64 / lanes terms, and each lane holds ceil(n / lanes) tableau
  * rows in registers; lanes * ceil(n / lanes) must not exceed 64), or
- * lanes | CHSIM_EVOLVE_LDS with lanes 4, 8 or 16 (lanes * 16 >= n): the rows
- * of every term stay in LDS and the lanes of a term share them.  -1 =
+ * lanes | CHSIM_EVOLVE_LDS with lanes 4, 8 or 16 (lanes * 16 >= n): the columns
+ * of every term's tableaux in registers, ceil(n / lanes) per lane.  The default
+ * takes, span by span, the fastest of the column mappings and one term per
+ * wave by estimate.  -1 =
  * autotune: the next chsim_apply_clifford that starts from |0^n> times every
  * shape on the real gate list (hipEvents), keeps the fastest, and leaves the
  * same terms any shape would.  Results never depend on the knob.
@@ -439,7 +441,7 @@ chsim_status chsim_set_tuning(chsim_ctx* ctx, uint32_t inst, uint32_t knob, int3
 
 /* Current value of a knob.  For EVOLVE_LANES, timings_ms[8] receives the
  * autotuner's timings in ms for lanes 4, 8, 16, 32, 64 with rows in
- * registers and lanes 4, 8, 16 with rows in LDS (0 where not timed); for
+ * registers and lanes 4, 8, 16 with columns in registers (0 where not timed); for
  * AMP_STRINGS, timings_ms[0..1] = the autotuner's timings for 256 and 512;
  * for PREFIX_SHARE, timings_ms[0] = checkpoint levels of the last planned
  * evolution and timings_ms[1] = its estimated cost relative to evolving

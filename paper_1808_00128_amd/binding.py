@@ -296,7 +296,7 @@ class Context:
 
     def set_evolve_lanes(self, lanes, inst=0):
         """Lanes per term of the evolution kernel (4, 8, 16, 32, 64 with rows in
-        registers; 4, 8, 16 | CHSIM_EVOLVE_LDS with rows in LDS; 0 = default;
+        registers; 4, 8, 16 | CHSIM_EVOLVE_LDS with columns in registers; 0 = default;
         -1 = autotune at the next evolution from |0^n>)."""
         _check(lib().chsim_set_tuning(self._h, inst, CHSIM_TUNE_EVOLVE_LANES, int(lanes)))
 

@@ -72,19 +72,19 @@ struct DevBuf {
 };
 
 // Evolution shapes the autotuner times, in the order of the reported
-// timings: lanes per term (| CHSIM_EVOLVE_LDS for rows in LDS).
+// timings: lanes per term (| CHSIM_EVOLVE_LDS for columns in registers).
 constexpr int kTuneShapes = 8;
 constexpr int kTuneLanes[kTuneShapes] = {4, 8, 16, 32, 64, 4 | CHSIM_EVOLVE_LDS, 8 | CHSIM_EVOLVE_LDS,
                                          16 | CHSIM_EVOLVE_LDS};
 
-// EvolveShape of a tuning value (lanes, with CHSIM_EVOLVE_LDS for LDS rows).
+// EvolveShape of a tuning value (lanes, with CHSIM_EVOLVE_LDS for columns).
 EvolveShape shape_of_value(uint32_t n, int value) {
   EvolveShape s = evolve_shape_for(n, value & ~CHSIM_EVOLVE_LDS);
-  s.lds = (value & CHSIM_EVOLVE_LDS) != 0;
+  s.cols = (value & CHSIM_EVOLVE_LDS) != 0;
   return s;
 }
 
-int value_of_shape(EvolveShape s) { return s.lanes | (s.lds ? CHSIM_EVOLVE_LDS : 0); }
+int value_of_shape(EvolveShape s) { return s.lanes | (s.cols ? CHSIM_EVOLVE_LDS : 0); }
 
 struct Instance {
   uint32_t n = 0, n_slot = 0, mode = 0;
@@ -117,7 +117,7 @@ struct Instance {
   bool plan_valid = false;
   uint64_t plan_key = 0;
   std::vector<uint32_t> plan_cut;       // gate position after each checkpoint level
-  std::vector<int> plan_lanes;          // mapping of each checkpoint span (0: the instance's)
+  std::vector<int> plan_lanes;          // mapping of each checkpoint span and of the last one
   std::vector<uint32_t> plan_span_off;  // level k's slots: [span_off[k], span_off[k+1])
   std::vector<uint16_t> plan_slot_h;
   std::vector<uint8_t> plan_width_h;
@@ -522,16 +522,15 @@ struct GateCost {
 };
 constexpr GateCost kCostReg8 = {{0.87, 0.76, 0.67, 0.46}, {4.23, 2.52, 2.21, 1.57}};
 constexpr GateCost kCostReg16 = {{0.70, 0.55, 0.50, 0.40}, {4.10, 2.70, 2.40, 1.80}};
-constexpr GateCost kCostWave = {{0.47, 0.28, 0.28, 0.29}, {11.9, 5.04, 4.18, 4.32}};
-constexpr GateCost kCostLds4 = {{2.32, 0.39, 0.30, 0.30}, {5.19, 0.80, 0.62, 0.63}};
-constexpr GateCost kCostLds8 = {{1.48, 0.39, 0.30, 0.30}, {4.67, 0.95, 0.77, 0.78}};
-constexpr GateCost kCostLds16 = {{1.05, 0.39, 0.30, 0.29}, {5.80, 1.43, 1.21, 1.26}};
+constexpr GateCost kCostWave = {{0.48, 0.27, 0.26, 0.24}, {11.75, 4.64, 3.46, 3.90}};
+constexpr GateCost kCostCols4 = {{1.20, 0.37, 0.25, 0.17}, {3.28, 0.89, 0.47, 0.25}};
+constexpr GateCost kCostCols8 = {{0.76, 0.27, 0.20, 0.17}, {3.99, 1.06, 0.58, 0.42}};
+constexpr GateCost kCostCols16 = {{0.64, 0.27, 0.21, 0.17}, {5.81, 1.38, 0.95, 0.74}};
 constexpr double kLevelCostUs = 45.0;  // prefix-id kernels and a launch per level
 
-// Cost table of the mapping a span would run with (the whole-wave mapping
-// for lanes = 64, the register tables otherwise).
+// Cost table of a mapping (the whole-wave one for 32 lanes too).
 const GateCost& cost_of(EvolveShape s) {
-  if (s.lds) return s.lanes == 4 ? kCostLds4 : s.lanes == 8 ? kCostLds8 : kCostLds16;
+  if (s.cols) return s.lanes == 4 ? kCostCols4 : s.lanes == 8 ? kCostCols8 : kCostCols16;
   if (s.lanes == 64 || s.lanes == 32) return kCostWave;
   return s.lanes >= 16 ? kCostReg16 : kCostReg8;
 }
@@ -541,11 +540,17 @@ int gate_kind(const DGate& g) {
 }
 
 // Estimated time of `items` work items through gates with `cnt[kind]` gates
-// of each kind; the row count scales the per-item throughput term.  A
-// mapping that holds at most `cap` items on the chip at once runs whole
-// rounds of cap items at full throughput and a last partial round, which is
-// charged like a launch of that many items alone (latency-bound when small).
-double span_us(const GateCost& c, const double cnt[4], double items, double row_scale, double cap) {
+// of each kind.  The row count scales the per-item throughput term and, for the
+// column mappings, three quarters of a lone wave's latency (H with 4 lanes per
+// term: n = 12 0.40 and 1.07 us, 24 0.53 and 1.44, 40 0.89 and 2.75, 50 1.20 and
+// 3.28).  A mapping that holds at most
+// `cap` items on the chip at once runs whole rounds of cap items at full
+// throughput and a last partial round, which is charged like a launch of that
+// many items alone (latency-bound when small).
+double span_us(EvolveShape s, const double cnt[4], double items, uint32_t n) {
+  const GateCost& c = cost_of(s);
+  const double rows = (double)n / 50.0, cap = (double)evolve_capacity(s, n);
+  const double lat = s.cols ? 0.25 + 0.75 * rows : 1.0;
   double full = 0.0, rest = items;
   if (cap > 0 && items > cap) {
     full = std::floor(items / cap) * cap;
@@ -553,10 +558,35 @@ double span_us(const GateCost& c, const double cnt[4], double items, double row_
   }
   double t = 0.0;
   for (int k = 0; k < 4; ++k) {
-    const double per = c.thr[k] * row_scale / 65536.0;
-    t += cnt[k] * (full * per + (rest > 0 ? std::max(c.lat[k], rest * per) : 0.0));
+    const double per = c.thr[k] * (s.lanes == 64 ? 1.0 : 0.12 + 0.88 * rows) / 65536.0;
+    t += cnt[k] * (full * per + (rest > 0 ? std::max(c.lat[k] * lat, rest * per) : 0.0));
   }
   return t;
+}
+
+// The mapping of a span: the one the caller set or one term per wave, whichever
+// is estimated faster; with the default (lanes 0) the best of the column
+// mappings and one term per wave.
+EvolveShape span_shape(const Instance& I, EvolveShape set, const double cnt[4], double items, double* us) {
+  const EvolveShape wave = evolve_shape_for(I.n, 64);
+  EvolveShape best = set.lanes ? set : evolve_default_shape(I.n);
+  double t = span_us(best, cnt, items, I.n);
+  auto consider = [&](EvolveShape s) {
+    const double u = span_us(s, cnt, items, I.n);
+    if (u < t) {
+      t = u;
+      best = s;
+    }
+  };
+  if (set.lanes == 0)
+    for (int lanes : {8, 16}) {
+      EvolveShape s = evolve_shape_for(I.n, lanes);
+      s.cols = true;
+      consider(s);
+    }
+  consider(wave);
+  if (us) *us = t;
+  return best;
 }
 
 uint32_t branch_bits(uint32_t nb) {
@@ -611,6 +641,11 @@ std::vector<double> estimate_distinct(const Instance& I, const std::vector<uint1
   return D;
 }
 
+// The mapping of a launch over every term: the caller's, or the default's best.
+EvolveShape last_shape(const Instance& I, EvolveShape set, const double cnt[4]) {
+  return set.lanes ? set : span_shape(I, set, cnt, (double)I.chi, nullptr);
+}
+
 // Choose checkpoint levels (slot occurrences) and the mapping of each span
 // to minimise the estimated time: a span from level i to level j runs the
 // gates between them on the (estimated) distinct prefixes at j, bounded
@@ -624,6 +659,11 @@ void plan_prefix(Instance& I, const std::vector<DGate>& dg, EvolveShape shape) {
   I.plan_slot_h.clear();
   I.plan_width_h.clear();
   I.plan_frac = 1.0;
+  {
+    double cnt[4] = {0, 0, 0, 0};
+    for (const DGate& g : dg) cnt[gate_kind(g)] += 1.0;
+    I.plan_lanes.push_back(value_of_shape(last_shape(I, shape, cnt)));
+  }
   // Slot occurrences: a SLOT_SPOW gate, or a run of conditional gates of one slot.
   std::vector<uint16_t> occ;
   std::vector<uint32_t> end;
@@ -649,17 +689,19 @@ void plan_prefix(Instance& I, const std::vector<DGate>& dg, EvolveShape shape) {
   for (size_t j = 0; j < m; ++j) C[j + 1] = Cw[end[j]];
   const std::array<double, 4> Ct = Cw[dg.size()];
   const double chi = (double)I.chi;
-  const double rows = (double)I.n / 50.0;  // the table was measured at n = 50
-  const double cap = (double)evolve_capacity(shape, I.n);
   const std::vector<double> D = estimate_distinct(I, occ);
   const bool force = I.prefix_mode == 2;
   auto seg = [&](size_t i, size_t j, double items, int* lanes) {
-    double cnt[4];
+    double cnt[4], t = 0.0;
     for (int k = 0; k < 4; ++k) cnt[k] = (j <= m ? C[j][k] : Ct[k]) - C[i][k];
-    const double tp = span_us(cost_of(shape), cnt, items, rows, cap);
-    const double tw = span_us(kCostWave, cnt, items, rows, 0.0);
-    if (lanes) *lanes = tw < tp ? 64 : 0;
-    return std::min(tp, tw);
+    if (j > m) {  // the last span: every term
+      const EvolveShape s = last_shape(I, shape, cnt);
+      if (lanes) *lanes = value_of_shape(s);
+      return span_us(s, cnt, items, I.n);
+    }
+    const EvolveShape s = span_shape(I, shape, cnt, items, &t);
+    if (lanes) *lanes = value_of_shape(s);
+    return t;
   };
   auto work = [&](size_t i, size_t j, double items) {  // weighted gate applications
     double w = 0;
@@ -696,6 +738,7 @@ void plan_prefix(Instance& I, const std::vector<DGate>& dg, EvolveShape shape) {
   std::vector<size_t> levels;
   for (size_t j = last; j != 0; j = (size_t)from[j]) levels.push_back(j);
   std::reverse(levels.begin(), levels.end());
+  I.plan_lanes.clear();
   size_t prev = 0;
   for (size_t j : levels) {
     for (size_t t = prev; t < j; ++t) {
@@ -709,6 +752,9 @@ void plan_prefix(Instance& I, const std::vector<DGate>& dg, EvolveShape shape) {
     I.plan_lanes.push_back(lanes);
     prev = j;
   }
+  int lanes = 0;
+  seg(prev, m + 1, chi, &lanes);
+  I.plan_lanes.push_back(lanes);
   I.plan_frac = plain > 0 ? total / plain : 1.0;
 }
 
@@ -771,7 +817,6 @@ Instance::SpanStat span_stat(const std::vector<DGate>& dg, uint32_t g0, uint32_t
 
 chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& dg, EvolveShape shape,
                         bool from_zero, hipStream_t s) {
-  if (shape.lanes == 0) shape = evolve_default_shape(I.n);
   const uint32_t ng = (uint32_t)dg.size();
   const uint32_t n_occ_all = (uint32_t)ctx->occ_start.size();
   // Slot occurrences whose first gate lies in [g0, g1).
@@ -784,11 +829,13 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
   I.last_spans.clear();
   if (!from_zero || I.prefix_mode == 0) {
     I.last_spans.push_back(span_stat(dg, 0, ng, -1, I.chi));
+    double cnt[4] = {0, 0, 0, 0};
+    for (const DGate& g : dg) cnt[gate_kind(g)] += 1.0;
     HIP_TRY(launch_evolve(I.view(), ctx->gates.p, ng, ctx->slotseq.p, n_occ_all, from_zero, ctx->err.p,
-                          shape, s));
+                          last_shape(I, shape, cnt), s));
     return CHSIM_OK;
   }
-  const uint64_t key = gates_key(I, ctx->dg_hash) ^ ((uint64_t)(shape.lanes | (shape.lds ? 0x100 : 0)) << 48);
+  const uint64_t key = gates_key(I, ctx->dg_hash) ^ ((uint64_t)(shape.lanes | (shape.cols ? 0x100 : 0)) << 48);
   if (!I.plan_valid || I.plan_key != key) {
     plan_prefix(I, dg, shape);
     I.plan_key = key;
@@ -804,7 +851,8 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
   const size_t K = I.plan_cut.size();
   if (K == 0) {
     I.last_spans.push_back(span_stat(dg, 0, ng, -1, I.chi));
-    HIP_TRY(launch_evolve(I.view(), ctx->gates.p, ng, ctx->slotseq.p, n_occ_all, true, ctx->err.p, shape, s));
+    HIP_TRY(launch_evolve(I.view(), ctx->gates.p, ng, ctx->slotseq.p, n_occ_all, true, ctx->err.p,
+                          shape_of_value(I.n, I.plan_lanes[0]), s));
     return CHSIM_OK;
   }
   const uint64_t chi = I.chi, n = I.n;
@@ -862,8 +910,8 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
     J.n_occ = occ_range(g0, g1, &o0);
     J.slot_seq = ctx->slotseq.p + o0;
     I.last_spans.push_back(span_stat(dg, g0, g1, (int)k, 0));
-    const EvolveShape span_shape = I.plan_lanes[k] ? evolve_shape_for(I.n, I.plan_lanes[k]) : shape;
-    HIP_TRY(launch_evolve_job(J, ctx->gates.p + g0, g1 - g0, k == 0, ctx->err.p, span_shape, s));
+    HIP_TRY(launch_evolve_job(J, ctx->gates.p + g0, g1 - g0, k == 0, ctx->err.p,
+                              shape_of_value(I.n, I.plan_lanes[k]), s));
     prev_id = ctx->pf_id[k % 2].p;
     g0 = g1;
   }
@@ -884,7 +932,7 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
   J.n_occ = occ_range(g0, ng, &o0);
   J.slot_seq = ctx->slotseq.p + o0;
   I.last_spans.push_back(span_stat(dg, g0, ng, -1, chi));
-  HIP_TRY(launch_evolve_job(J, ctx->gates.p + g0, ng - g0, false, ctx->err.p, shape, s));
+  HIP_TRY(launch_evolve_job(J, ctx->gates.p + g0, ng - g0, false, ctx->err.p, shape_of_value(I.n, I.plan_lanes[K]), s));
   return CHSIM_OK;
 }
 
@@ -948,7 +996,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
         push_gate(dg, g);
       }
     }
-    // One padding entry past the last gate: the LDS kernel reads the gate
+    // One padding entry past the last gate: the column kernels read the gate
     // after the current one without a bound check.
     static const DGate kPadGate = {OP_S, 0, 0, 0, 0, 0, 0};
     HIP_TRY(ctx->gates.ensure(dg.size() + 1));

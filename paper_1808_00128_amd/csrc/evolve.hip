@@ -77,22 +77,26 @@ EvolveShape evolve_shape_for(uint32_t n, int lanes) {
   return s;
 }
 
-// Default: rows in LDS, 8 lanes per term (4 for n <= 16).
+// Default: columns in registers, 4 lanes per term.
 EvolveShape evolve_default_shape(uint32_t n) {
-  EvolveShape s = evolve_shape_for(n, n <= 16 ? 4 : 8);
-  s.lds = true;
+  EvolveShape s = evolve_shape_for(n, 4);
+  s.cols = true;
   return s;
 }
 
 uint64_t evolve_capacity(EvolveShape s, uint32_t n) {
-  return s.lds ? evolve_lds_capacity(s.lanes, n) : 0u;
+  if (!s.cols) return 0u;
+  int dev = 0, cus = 0;
+  hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
+  return (uint64_t)cus * 4u * (uint64_t)evolve_cols_waves(s.lanes, evolve_shape_for(n, s.lanes).rows) * 64u /
+         (uint64_t)s.lanes;
 }
 
 // Instantiated shapes: lanes in {4, 8, 16, 32, 64} with rows = ceil(n / lanes)
-// and lanes * rows <= 64; rows in LDS: lanes in {4, 8, 16} (gamma of a lane's
-// rows packed in 16 bits).
+// and lanes * rows <= 64; columns in registers: lanes in {4, 8, 16}.
 bool evolve_shape_supported(EvolveShape s, uint32_t n) {
-  if (s.lds)
+  if (s.cols)
     return (s.lanes == 4 || s.lanes == 8 || s.lanes == 16) && n >= 1 && n <= 64 &&
            (uint32_t)s.lanes * 16u >= n;
   const bool lanes_ok = s.lanes == 4 || s.lanes == 8 || s.lanes == 16 || s.lanes == 32 || s.lanes == 64;
@@ -104,7 +108,13 @@ hipError_t launch_evolve_job(const EvolveJob& J, const DGate* gates, uint32_t n_
   const uint32_t n = J.dst.n;
   if (shape.lanes == 0) shape = evolve_default_shape(n);
   if (!evolve_shape_supported(shape, n)) return hipErrorInvalidValue;
-  if (shape.lds) return launch_evolve_lds(shape.lanes, J, gates, n_gates, from_zero, err, st);
+  if (shape.cols) {
+    const int cols = evolve_shape_for(n, shape.lanes).rows;
+    if (shape.lanes == 16) return launch_evolve_c16(cols, J, gates, n_gates, from_zero, err, st);
+    if (shape.lanes == 8) return launch_evolve_c8(cols, J, gates, n_gates, from_zero, err, st);
+    return cols <= 10 ? launch_evolve_c4a(cols, J, gates, n_gates, from_zero, err, st)
+                      : launch_evolve_c4b(cols, J, gates, n_gates, from_zero, err, st);
+  }
   if (shape.lanes == 4) return launch_evolve_l4(shape.rows, J, gates, n_gates, from_zero, err, st);
   if (shape.lanes == 8) return launch_evolve_l8(shape.rows, J, gates, n_gates, from_zero, err, st);
   if (shape.lanes == 64) return launch_evolve_w64(J, gates, n_gates, from_zero, err, st);

@@ -93,10 +93,10 @@ hipError_t launch_choose(const TermsView& T, const SlotTable* slots, uint32_t mo
                          double scale, hipStream_t st);
 // Evolution mapping: `lanes` lanes per term (4, 8, 16, 32 or 64; 64 / lanes
 // terms per wave) and `rows` = ceil(n / lanes) tableau rows per lane.  0 = choose.
-// lds: rows resident in LDS (evolve_lds.hip) instead of registers.
+// cols: tableau columns in registers (evolve_cols.hpp), `rows` of them per lane.
 struct EvolveShape {
   int lanes = 0, rows = 0;
-  bool lds = false;
+  bool cols = false;
 };
 EvolveShape evolve_shape_for(uint32_t n, int lanes);
 EvolveShape evolve_default_shape(uint32_t n);
@@ -135,8 +135,14 @@ hipError_t launch_evolve_l8(int rows, const EvolveJob& J, const DGate* gates, ui
                             bool from_zero, uint32_t* err, hipStream_t st);
 hipError_t launch_evolve_wide(int lanes, int rows, const EvolveJob& J, const DGate* gates,
                               uint32_t n_gates, bool from_zero, uint32_t* err, hipStream_t st);
-hipError_t launch_evolve_lds(int lanes, const EvolveJob& J, const DGate* gates, uint32_t n_gates,
-                             bool from_zero, uint32_t* err, hipStream_t st);
+hipError_t launch_evolve_c4a(int cols, const EvolveJob& J, const DGate* gates, uint32_t n_gates, bool from_zero,
+                             uint32_t* err, hipStream_t st);
+hipError_t launch_evolve_c4b(int cols, const EvolveJob& J, const DGate* gates, uint32_t n_gates, bool from_zero,
+                             uint32_t* err, hipStream_t st);
+hipError_t launch_evolve_c8(int cols, const EvolveJob& J, const DGate* gates, uint32_t n_gates, bool from_zero,
+                            uint32_t* err, hipStream_t st);
+hipError_t launch_evolve_c16(int cols, const EvolveJob& J, const DGate* gates, uint32_t n_gates, bool from_zero,
+                             uint32_t* err, hipStream_t st);
 // Projective gates (I + P_j) / 2, j < count, applied in order to every term of
 // T in place (CH forms and b), with the Hermitian Pauli
 // P_j = i^{a[j]} X(x[j]) Z(z[j]) (a[j] = popcount(x[j] & z[j]) mod 2).
@@ -149,7 +155,12 @@ struct ProjGates {
 hipError_t launch_project(const TermsView& T, const ProjGates& P, uint32_t* err, hipStream_t st);
 hipError_t launch_evolve_w64(const EvolveJob& J, const DGate* gates, uint32_t n_gates, bool from_zero,
                              uint32_t* err, hipStream_t st);
-uint64_t evolve_lds_capacity(int lanes, uint32_t n);
+// Waves per SIMD of the column kernel, asked of the compiler: state and
+// temporaries take about 6 C + 48 registers (3 C + 48 up to 32 qubits).
+constexpr int evolve_cols_waves(int lanes, int cols) {
+  const int regs = (lanes * cols > 32 ? 6 : 3) * cols + 48;
+  return regs <= 64 ? 8 : regs <= 80 ? 6 : regs <= 96 ? 5 : regs <= 128 ? 4 : 3;
+}
 hipError_t launch_evolve(const TermsView& T, const DGate* gates, uint32_t n_gates,
                          const uint32_t* slot_seq, uint32_t n_occ, bool from_zero, uint32_t* err,
                          EvolveShape shape, hipStream_t st);
