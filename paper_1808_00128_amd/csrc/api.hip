@@ -318,6 +318,38 @@ void merge_diagonal_branches(const Instance& I, const SlotTable& st, std::vector
   }
 }
 
+// Move every diagonal slot (a power of S, or the net gates of diagonal
+// branches) as late as it commutes: past every gate but a Hadamard on, or a CX
+// into, one of its qubits.  Terms that agree so far then share more gates before
+// the slot's choice splits them (about 100 gates per slot on a random circuit
+// of 50 qubits).  L[S_q] and L[CZ_qr] touch rows q, r of M and gamma through rows
+// q, r of G alone; the passed gates change neither those rows of G nor, since
+// F G^T = I, the phases they give, so the CH form is the same bit for bit.
+void defer_diagonal_slots(std::vector<DGate>& dg) {
+  for (size_t i = dg.size(); i-- > 0;) {
+    if (!(dg[i].cond & kSlotStart)) continue;
+    size_t end = i + 1;  // the slot's gates
+    while (end < dg.size() && (dg[end].cond & kCondApply) && !(dg[end].cond & kSlotStart)) ++end;
+    uint64_t qubits = 0;
+    bool diagonal = true;
+    for (size_t k = i; k < end; ++k) {
+      qubits |= 1ull << dg[k].q;
+      if (dg[k].op == OP_CZ) qubits |= 1ull << dg[k].r;
+      else if (dg[k].op != OP_SLOT_SPOW && dg[k].op != OP_SPOW) diagonal = false;
+    }
+    if (!diagonal) continue;
+    // A stop inside another slot's gates goes back to that slot's start.
+    size_t to = end, k = end;
+    for (; k < dg.size(); ++k) {
+      const DGate& g = dg[k];
+      if (!(g.cond & kCondApply) || (g.cond & kSlotStart)) to = k;
+      if ((g.op == OP_H && (qubits >> g.q & 1u)) || (g.op == OP_CX && (qubits >> g.r & 1u))) break;
+    }
+    if (k == dg.size()) to = k;
+    if (to > end) std::rotate(dg.begin() + i, dg.begin() + end, dg.begin() + to);
+  }
+}
+
 chsim_status build_slots(Instance& I, const chsim_instance& in) {
   I.slots_h.clear();
   I.bgates_h.clear();
@@ -996,6 +1028,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
         push_gate(dg, g);
       }
     }
+    defer_diagonal_slots(dg);
     // One padding entry past the last gate: the column kernels read the gate
     // after the current one without a bound check.
     static const DGate kPadGate = {OP_S, 0, 0, 0, 0, 0, 0};

@@ -78,3 +78,22 @@ def test_general_slot_branches(B, monkeypatch, n, lanes):  # noqa: F811
             assert np.array_equal(got[f][a], want[f]), (f, a)
         for f in ("v", "s", "omega"):
             assert int(got[f][a]) == want[f], (f, a)
+
+
+@pytest.mark.parametrize("share", [0, 2])
+def test_deferred_diagonal_slots(B, share):  # noqa: F811
+    """Slots before, between and right at the gates that stop them (a Hadamard
+    on, a CX into one of their qubits), several on one qubit, CCZ among them."""
+    n = 7
+    H, S, CX, CZ, SL, CCZ = W.OP_H, W.OP_S, W.OP_CX, W.OP_CZ, W.OP_SLOT, W.OP_CCZ
+    gates = [(H, q, 0) for q in range(n)]
+    gates += [(SL, 0, 0, 0.3), (CX, 0, 1), (CZ, 0, 2), (S, 0, 0), (SL, 0, 0, 2.1), (SL, 1, 0, 1.0), (CX, 2, 0),
+              (CCZ, 3, 4, 5), (CX, 3, 1), (H, 6, 0), (CX, 1, 4), (CCZ, 0, 3, 6), (SL, 5, 0, 4.0), (H, 5, 0), (SL, 2, 0, 0.7),
+              (CX, 2, 6), (H, 3, 0), (S, 2, 0), (CZ, 2, 5), (H, 0, 0), (SL, 6, 0, 5.0)]
+    circ = W.from_list(n, gates)
+    chi = 300
+    say(f"deferred slots share={share}")
+    ctx = B.Context([dict(circuit=circ, chi=chi, mode="sparsify", seed=8)])
+    ctx.set_prefix_share(share)
+    ctx.apply_circuit(circ)
+    compare_terms(ctx, O.Terms(circ, chi, O.SPARSIFY, seed=8), np.arange(chi, dtype=np.uint64))
