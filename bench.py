@@ -358,12 +358,19 @@ METRO_WINDOW = 4
 
 
 def own_chain_step_bytes(chi, n_chain, win=METRO_WINDOW):
-    """HBM bytes of one single-flip step as the kernel moves them (one flip bit
-    per step shared by the chains): each chain's cached word read (8 B) and
-    written once per window (8 / win B), the rows F_j, M_j, gamma_j (17 B) of
-    the proposal bit and of the window's pending steps ((win + 1) / 2 on
+    """HBM bytes of one single-flip step when every launch takes one step (one
+    flip bit per step shared by the chains): each chain's cached word read (8 B)
+    and written once per window (8 / win B), the rows F_j, M_j, gamma_j (17 B)
+    of the proposal bit and of the window's pending steps ((win + 1) / 2 on
     average), and the term's constants (33 B)."""
     return float(chi * (8 * n_chain + 8 * n_chain / win + 17 * (1 + (win + 1) / 2) + 33))
+
+
+def pair_chain_step_bytes(chi, n_chain, win=METRO_WINDOW):
+    """The same as the kernel moves them, two steps per launch: the cached word
+    read once per two steps (4 B), the pending rows ((win + 2) / 2 per launch)
+    and the constants once per two steps."""
+    return float(chi * (4 * n_chain + 8 * n_chain / win + 17 * (1 + (win + 2) / 4) + 33 / 2))
 
 
 def table_chain_step_bytes(chi, n_chain):
@@ -413,16 +420,16 @@ def bench_learned(torch, B, W, stats, steps=1000, n_chain=64, chi=1 << 20, eps=0
     plain["hip_graph"] = graph
     sbytes = table_chain_step_bytes(chi, n_chain)
     achieved = sbytes * steps / (ms / 1e3) / 1e9
-    obytes = own_chain_step_bytes(chi, n_chain)
+    obytes = pair_chain_step_bytes(chi, n_chain)
     plain["roofline"] = roof("hbm", achieved, HBM_PEAK_BPS / 1e9, "GB/s", MEASURED.get("hbm"),
-                             kernel="k_propose_gather (single flips, shared j, cache writes deferred "
-                                    f"over windows of {METRO_WINDOW} steps) + k_metro_accept",
+                             kernel="k_propose_pair (single flips, shared j, two steps per launch, "
+                                    f"cache writes deferred over windows of {METRO_WINDOW} steps) + k_metro_accept",
                              traffic=None, bytes_per_step=sbytes,
                              count="chi (16 chains + 17 + 33) B per step (state r/w, row j, constants)",
                              bytes_per_step_own=obytes,
-                             own_count=f"chi (8 chains + 8 chains / {METRO_WINDOW} + 17 (1 + "
-                                       f"{(METRO_WINDOW + 1) / 2}) + 33) B per step (state read, "
-                                       "state written once per window, proposal and pending rows, constants)",
+                             own_count=f"chi (4 chains + 8 chains / {METRO_WINDOW} + 17 (1 + "
+                                       f"{(METRO_WINDOW + 2) / 4}) + 33 / 2) B per step (state read once per "
+                                       "two steps, written once per window, proposal and pending rows, constants)",
                              frac_own_count=round(obytes * steps / (ms / 1e3) / HBM_PEAK_BPS, 4),
                              bytes_per_step_all_rows=chain_step_bytes(chi, n, n_chain))
     delta = max(1, int(round(plain["tau_int"])))

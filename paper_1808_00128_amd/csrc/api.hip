@@ -1681,7 +1681,7 @@ chsim_status chsim_metropolis_init(chsim_ctx* ctx, uint32_t inst, uint32_t n_cha
   HIP_TRY(hipMemsetAsync(I.mpmask.p, 0, n_chain * sizeof(uint64_t), s));
   HIP_TRY(I.mx.ensure(n_chain));
   HIP_TRY(I.mamp.ensure(n_chain));
-  HIP_TRY(I.mpartial.ensure((size_t)n_chain * tiles));
+  HIP_TRY(I.mpartial.ensure((size_t)3 * n_chain * tiles));  // three sums per pair of steps
   HIP_TRY(hipMemcpyAsync(I.mx.p, x0, n_chain * 8, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
   MetroView mv = metro_view(I);
   HIP_TRY(launch_metro_init(I.view(), mv, s));

@@ -74,7 +74,7 @@ struct MetroView {
   uint64_t* pmask;        // per chain: flip mask accepted at the previous flip-mask step, or 0
   uint64_t* x;            // per chain
   double2* amp;           // per chain: <x|psi>
-  double2* partial;       // [n_chain][n_tiles]
+  double2* partial;       // up to three planes of [n_chain][n_tiles]
   const uint32_t* jstream;
   const double* ustream;
   uint64_t* trace;        // may be null

@@ -8,12 +8,16 @@
 // and <y|phi_alpha> follows from (u', mu') as in Eq. (amplitude1), O(1) words
 // per term and chain.
 //
-// Kernels per step: (1) k_propose_gather (single flips; the cache is brought
-// up to date once per window of kMetroWin steps, in place) or k_propose (flip
-// masks: the tile's rows staged in LDS; the cache is brought up to date with
-// an accepted mask at the next step, in place): lanes over terms, reduce
-// sum_alpha b_alpha <y|phi_alpha> over the 256-term tile in FP64; (2) one workgroup per chain: add the tiles' partials in a fixed
+// Kernels: (1) k_propose_pair (single flips; two steps per launch, the second
+// for either outcome of the first, the cache brought up to date once per
+// window of kMetroWin steps) or k_propose (flip masks: the tile's rows staged in
+// LDS; the cache is brought up to date with an accepted mask at the next step,
+// in place): lanes over terms, sums of b_alpha <y|phi_alpha> over the 256-term
+// tile in FP64; (2) one workgroup per chain: add the tiles' partials in a fixed
 // order, r = |A(y)|^2 / |A(x)|^2 in FP64, accept iff U < r.
+#include <algorithm>
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -275,75 +279,171 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
   }
 }
 
-// Single-flip proposal step with deferred cache updates.  Lanes over terms
-// (each lane takes four terms of the 256-term tile), waves over chains.  A
-// chain's cached (u, mu) is brought up to date only once per window of
-// kMetroWin steps: step t of the window that starts at t0 reads the cache as
-// of t0, applies the flips the chain accepted at steps t0 .. t-1 (right
+// Two single-flip steps per launch, with deferred cache updates.  Lanes over
+// terms (each lane takes four terms of the 256-term tile), waves over chains.
+//
+// Speculation.  Steps t and t + 1 propose bits j1 and j2 that are known before
+// either is decided, so one reading of a chain's cached words serves both: the
+// sums for y = x + e_j1 (step t) and, for step t + 1, for x + e_j2 (step t
+// rejected) and x + e_j1 + e_j2 (accepted).  The accept kernel takes both
+// decisions.  That is three values per two steps instead of two, for half the
+// reads of the cache and half the launches.
+//
+// Deferred updates.  A chain's cached (u, mu) is brought up to date only once
+// per window of kMetroWin steps: a pair of steps in the window that starts at t0
+// reads the cache as of t0, applies the flips the chain accepted since (right
 // products by their P_j in step order: the same arithmetic as updating after
-// every accepted step), then the proposal's P_j.  The first step of the next
-// window (and a final pass without a proposal at the end of a call) writes
-// the brought-up-to-date cache back in place.  The tile's rows of chain 0's
-// flip bits at the pending steps are staged in LDS once and serve every
-// chain whose bit at that step is the same (every chain, when the chains
-// share the flip bit of a step); a chain with another bit reads its row from
-// the term store.  So per chain and step only the 8-byte cache word of each
-// term is read, and it is written once per window.
+// every accepted step), then the proposals' P_j.  The first pair of the next
+// window (and a final pass without a proposal at the end of a call) writes the
+// brought-up-to-date cache back in place.
+//
+// Rows.  kSlots64, kSlots32 (n <= 30: one 32-bit half): the tile's rows of chain
+// 0's bits at the pending and proposed steps are staged in LDS and serve every
+// chain whose bit at that step is the same (every chain, when the chains share
+// the flip bit of a step); a chain with another bit reads its row from the term
+// store.  kPacked (n <= 15): every row of the tile is staged, F, M and gamma of a
+// row and term in one word, so any chain's bits cost one LDS read.
+//
+// Values.  With gamma_j + 2 par(F_j & v & s) in place of gamma_j, mu carries
+// 2 par(u & v & s) along (added once when a cached word is read), and a term's
+// value is one of four, b 2^{-|v|/2} e^{i pi omega/4} i^mu, read from LDS ([mu][term]:
+// no bank conflicts), or zero outside the support.  The 12 sums of two chains
+// (three values, re and im) are reduced over the wave together: the halves of
+// the wave exchange two sums at a time (v_permlane32_swap, then 16), so 12
+// become 3 before the 16 lanes of a row are added by DPP moves: 63 instructions
+// against about 240 for twelve trees.
+//
+// VALU issue bounds it: 102 instructions per 64 terms, chain and pair of steps at
+// n = 50 (about 190 of the 283 µs per launch at chi = 2^20 and 64 chains with one
+// flip bit; 537 MB read, and as much written by every second launch).  Before, one
+// step per launch with the values computed per proposal: 196 µs per step, now 141;
+// n = 12, chi = 2^16, 64 chains with their own bits (kPacked): 29 and 10.7.
 constexpr uint32_t kGWaves = 4;
 constexpr uint32_t kGSub = kMetroTile / 64;  // terms per lane
-constexpr uint32_t kModeWrite = 1u, kModePropose = 2u;
+constexpr uint32_t kModeWrite = 1u;
+enum { kSlots64 = 0, kSlots32 = 1, kPacked = 2 };
+constexpr uint32_t kSlots = kMetroWin + 2;  // pending steps, then the two proposals
+constexpr uint32_t kPackedMaxN = 15, kSlots32MaxN = 30;
 
-template <int CP>
-__global__ __launch_bounds__(64 * kGWaves) void k_propose_gather(TermsView T, MetroView Mv,
-                                                                 uint32_t step, uint32_t pbase,
-                                                                 uint32_t npend, uint32_t mode) {
-  // Slots 0 .. npend-1: rows of chain 0's bits at the pending steps; slot
-  // kMetroWin: the row of chain 0's proposal bit.
-  constexpr uint32_t kSlots = kMetroWin + 1;
-  __shared__ uint64_t sF[kSlots][kMetroTile], sM[kSlots][kMetroTile];
-  __shared__ uint8_t sG[kSlots][kMetroTile];
-  const uint32_t lane = threadIdx.x & 63u, wave = uniform32(threadIdx.x >> 6);
+// a + b over the halves of the wave: lanes 0-31 hold a's sum, lanes 32-63 b's.
+__device__ __forceinline__ double swap_add32(double a, double b) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+// The same over the 16-lane rows of each half: rows 0, 2 keep a, rows 1, 3 take b.
+__device__ __forceinline__ double swap_add16(double a, double b) {
+  const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
+         __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ double row_sum(double x) {
+  x += dpp_f64<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x += dpp_f64<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  x += dpp_f64<0x141>(x);  // row_half_mirror
+  x += dpp_f64<0x140>(x);  // row_mirror
+  return x;
+}
+
+template <int kMode>
+__global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, MetroView Mv, uint32_t step,
+                                                               uint32_t nprop, uint32_t pbase, uint32_t npend,
+                                                               uint32_t mode) {
+  constexpr bool k64 = kMode == kSlots64, kAll = kMode == kPacked;
+  using Word = typename std::conditional<k64, uint64_t, uint32_t>::type;
+  extern __shared__ __align__(16) uint8_t smem[];
+  // Values [5][256] (the fifth row zero), then the rows.
+  double2* const val = reinterpret_cast<double2*>(smem);
+  uint8_t* const rows = smem + 5u * kMetroTile * sizeof(double2);
+  Word* const sF = reinterpret_cast<Word*>(rows);                                 // [kSlots][256]
+  Word* const sM = sF + kSlots * kMetroTile;                                      // [kSlots][256]
+  uint8_t* const sG = reinterpret_cast<uint8_t*>(sM + kSlots * kMetroTile);       // [kSlots][256]
+  uint32_t* const sP = reinterpret_cast<uint32_t*>(rows);                         // [n][256], kPacked
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform32(tid >> 6);
   const uint32_t n = T.n, nc = Mv.n_chain;
   const uint64_t chi = T.chi;
   const uint64_t tile0 = (uint64_t)blockIdx.x * kMetroTile;
   const bool full = tile0 + kMetroTile <= chi;  // block-uniform
-  const bool write = mode & kModeWrite, prop = mode & kModePropose;
+  const bool write = mode & kModeWrite;
   // Term offsets within the tile, clamped to the last term in a partial tile:
-  // past chi a lane reads that term's words and contributes zero (its
-  // weight is zero) and writes nothing.
+  // past chi a lane reads that term's words, contributes zero (its values are
+  // zero) and writes nothing.
   const uint32_t last = (uint32_t)(chi - 1ull - tile0);
-  uint32_t ao[kGSub];
+  {
+    // The thread's own term: values and rows.
+    const uint32_t mine = min(tid, last);
+    const uint64_t a = tile0 + mine;
+    const uint64_t v = T.v[a], s = T.s[a], vs = v & s;
+    if (nprop) {
+      const TermAmpConst c = load_const(T, a);
+      const double h = 0.70710678118654752440;
+      const bool in = tid <= last;
+      double wr = (c.w & 1u) ? (c.w0r - c.w0i) * h : c.w0r, wi = (c.w & 1u) ? (c.w0r + c.w0i) * h : c.w0i;
+      for (uint32_t m = 0; m < 4u; ++m) {  // times i^m: exact
+        val[((m + 4u - (c.w >> 1)) & 3u) * kMetroTile + tid] = in ? make_double2(wr, wi) : make_double2(0.0, 0.0);
+        const double t = wr;
+        wr = -wi;
+        wi = t;
+      }
+      val[4u * kMetroTile + tid] = make_double2(0.0, 0.0);
+    }
+    if (kAll) {
+      for (uint32_t p = 0; p < n; ++p) {
+        const uint64_t at = (uint64_t)p * chi + a;
+        const uint32_t f = (uint32_t)T.F[at];
+        const uint32_t g = ((uint32_t)T.gamma[at] + 2u * (uint32_t)__popc(f & (uint32_t)vs)) & 3u;
+        sP[p * kMetroTile + tid] = f | ((uint32_t)T.M[at] << 15) | (g << 30);
+      }
+    } else {
 #pragma unroll
-  for (uint32_t sb = 0; sb < kGSub; ++sb) ao[sb] = min(sb * 64u + lane, last);
-  uint32_t Wj[kSlots];
-#pragma unroll
-  for (uint32_t s = 0; s < kSlots; ++s) {
-    Wj[s] = ~0u;
-    const bool use = s < kMetroWin ? s < npend : prop;
-    if (use) {
-      Wj[s] = uniform32(Mv.jstream[s < kMetroWin ? pbase + s : step]) % n;
-      const uint64_t off = (uint64_t)Wj[s] * chi + tile0 + min(threadIdx.x, last);
-      sF[s][threadIdx.x] = T.F[off];
-      sM[s][threadIdx.x] = T.M[off];
-      sG[s][threadIdx.x] = T.gamma[off];
+      for (uint32_t q = 0; q < kSlots; ++q) {
+        const bool use = q < kMetroWin ? q < npend : q - kMetroWin < nprop;
+        if (!use) continue;
+        const uint32_t j = uniform32(Mv.jstream[q < kMetroWin ? pbase + q : step + (q - kMetroWin)]) % n;
+        const uint64_t at = (uint64_t)j * chi + a, f = T.F[at];
+        sF[q * kMetroTile + tid] = (Word)f;
+        sM[q * kMetroTile + tid] = (Word)T.M[at];
+        sG[q * kMetroTile + tid] = (uint8_t)((T.gamma[at] + 2u * (uint32_t)__popcll(f & vs)) & 3u);
+      }
     }
   }
-  __syncthreads();
-  TermAmpConst c[kGSub];
+  uint32_t Wj[kSlots];
+#pragma unroll
+  for (uint32_t q = 0; q < kSlots; ++q) {
+    const bool use = q < kMetroWin ? q < npend : q - kMetroWin < nprop;
+    Wj[q] = !kAll && use ? uniform32(Mv.jstream[q < kMetroWin ? pbase + q : step + (q - kMetroWin)]) % n : ~0u;
+  }
+  uint32_t ao[kGSub];
+  Word nv[kGSub], snv[kGSub], vs[kGSub];
 #pragma unroll
   for (uint32_t sb = 0; sb < kGSub; ++sb) {
-    if (prop) c[sb] = load_const(T, tile0 + ao[sb]);
-    if (sb * 64u + lane > last) c[sb].w0r = c[sb].w0i = 0.0;
+    ao[sb] = min(sb * 64u + lane, last);
+    const uint64_t v = T.v[tile0 + ao[sb]], s = T.s[tile0 + ao[sb]];
+    nv[sb] = (Word)~v;  // u and s have no bits at or above n
+    snv[sb] = (Word)(s & ~v);
+    vs[sb] = (Word)(v & s);
   }
-  const uint32_t pmask = (1u << npend) - 1u;  // npend <= kMetroWin < 32
-  // Right product by P_j of step slot s for the lane's terms: the staged row
-  // when the chain's bit j is chain 0's, else the term store's.
-  auto flip = [&](uint64_t (&u)[kGSub], uint32_t (&mu)[kGSub], uint32_t s, uint32_t j) {
-    if (j == Wj[s]) {  // wave-uniform
+  __syncthreads();
+  auto popc = [](Word x) { return (uint32_t)(k64 ? __popcll((uint64_t)x) : __popc((uint32_t)x)); };
+  // Right product by P_j (step slot q) for the lane's terms.
+  auto flip = [&](Word (&u)[kGSub], uint32_t (&mu)[kGSub], uint32_t q, uint32_t j) {
+    if constexpr (kAll) {
 #pragma unroll
       for (uint32_t sb = 0; sb < kGSub; ++sb) {
-        u[sb] ^= sF[s][sb * 64u + lane];
-        mu[sb] += (uint32_t)sG[s][sb * 64u + lane] + 2u * __popcll(u[sb] & sM[s][sb * 64u + lane]);
+        const uint32_t w = sP[j * kMetroTile + sb * 64u + lane];
+        u[sb] ^= (Word)(w & 0x7FFFu);
+        mu[sb] += (w >> 30) + 2u * popc(u[sb] & (Word)(w >> 15));  // u has 15 bits
+      }
+    } else if (j == Wj[q]) {  // wave-uniform
+#pragma unroll
+      for (uint32_t sb = 0; sb < kGSub; ++sb) {
+        const uint32_t at = q * kMetroTile + sb * 64u + lane;
+        u[sb] ^= sF[at];
+        mu[sb] += (uint32_t)sG[at] + 2u * popc(u[sb] & sM[at]);
       }
     } else {
       const uint64_t* F = T.F + ((uint64_t)j * chi + tile0);
@@ -351,93 +451,144 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_gather(TermsView T, Me
       const uint8_t* g = T.gamma + ((uint64_t)j * chi + tile0);
 #pragma unroll
       for (uint32_t sb = 0; sb < kGSub; ++sb) {
-        u[sb] ^= F[ao[sb]];
-        mu[sb] += (uint32_t)g[ao[sb]] + 2u * __popcll(u[sb] & M[ao[sb]]);
+        const Word f = (Word)F[ao[sb]];
+        u[sb] ^= f;
+        mu[sb] += (uint32_t)g[ao[sb]] + 2u * popc(f & vs[sb]) + 2u * popc(u[sb] & (Word)M[ao[sb]]);
       }
     }
   };
-  // The wave's chains are ch = wave + kGWaves i.  Their per-chain words (the
-  // pending mask, the proposal bit and the pending steps' bits) are read for
-  // 64 chains at once, chain i % 64 in lane i % 64, and taken from there by
-  // lane reads, so that no wait for them also waits for the cache words in
-  // flight.
-  const uint32_t n_mine = nc > wave ? (nc - wave + kGWaves - 1u) / kGWaves : 0u;
-  uint32_t m_pm = 0u, m_j = 0u, m_js[kMetroWin];
+  // Sum of the lane's four terms' values.
+  auto value = [&](const Word (&u)[kGSub], const uint32_t (&mu)[kGSub], double& re, double& im) {
+#pragma unroll
+    for (uint32_t sb = 0; sb < kGSub; ++sb) {
+      const bool off = ((u[sb] & nv[sb]) ^ snv[sb]) != (Word)0;
+      const uint32_t m = off ? 4u : mu[sb] & 3u;
+      const double2 x = val[m * kMetroTile + sb * 64u + lane];
+      re = sb ? re + x.x : x.x;
+      im = sb ? im + x.y : x.y;
+    }
+  };
+  // The wave's chains are ch = w0 + n_waves i.  Their per-chain words (the
+  // pending mask and the bits of the pending and proposed steps) are read for 64
+  // chains at once, chain i % 64 in lane i % 64, and taken from there by lane
+  // reads, so that no wait for them also waits for the cache words in flight.
+  const uint32_t w0 = blockIdx.y * kGWaves + wave, n_waves = gridDim.y * kGWaves;
+  const uint32_t n_mine = nc > w0 ? (nc - w0 + n_waves - 1u) / n_waves : 0u;
+  const uint32_t pmask = (1u << npend) - 1u;  // npend <= kMetroWin < 32
+  const size_t plane = (size_t)nc * Mv.n_tiles;
   for (uint32_t i0 = 0; i0 < n_mine; i0 += 64u) {
+    uint32_t m_pm, m_js[kSlots];
     {
       const uint32_t i = i0 + lane;
-      const bool ok = i < n_mine;
-      const uint32_t ch = ok ? wave + kGWaves * i : wave;
+      const uint32_t ch = i < n_mine ? w0 + n_waves * i : w0;
       const uint64_t jrow = (uint64_t)ch * Mv.n_steps;
       m_pm = npend ? Mv.pend[ch] & pmask : 0u;
-      m_j = prop ? Mv.jstream[jrow + step] % n : 0u;
 #pragma unroll
-      for (uint32_t s = 0; s < kMetroWin; ++s) m_js[s] = s < npend ? Mv.jstream[jrow + pbase + s] % n : 0u;
+      for (uint32_t q = 0; q < kSlots; ++q) {
+        const bool use = q < kMetroWin ? q < npend : q - kMetroWin < nprop;
+        m_js[q] = use ? Mv.jstream[jrow + (q < kMetroWin ? pbase + q : step + (q - kMetroWin))] % n : 0u;
+      }
     }
     const uint32_t i_end = min(n_mine - i0, 64u);
-    // CP chains per pass: all their cache words are requested before any is
-    // combined.
-    for (uint32_t k0 = 0; k0 < i_end; k0 += (uint32_t)CP) {
-      uint64_t st[CP][kGSub];
+    // Two chains per pass: all their cache words are requested before any is
+    // combined (an odd last chain is taken twice and stored once).
+    for (uint32_t k0 = 0; k0 < i_end; k0 += 2u) {
+      uint64_t st[2][kGSub];
 #pragma unroll
-      for (int h = 0; h < CP; ++h) {
-        const uint32_t k = k0 + (uint32_t)h < i_end ? k0 + (uint32_t)h : k0;
-        const uint32_t ch = wave + kGWaves * (i0 + k);
-        const uint64_t* sp = Mv.state + ((uint64_t)ch * chi + tile0);
+      for (uint32_t h = 0; h < 2u; ++h) {
+        const uint32_t k = min(k0 + h, i_end - 1u);
+        const uint64_t* sp = Mv.state + ((uint64_t)(w0 + n_waves * (i0 + k)) * chi + tile0);
 #pragma unroll
         for (uint32_t sb = 0; sb < kGSub; ++sb) st[h][sb] = sp[ao[sb]];
       }
+      double sum[12];  // [chain][value][re, im]
 #pragma unroll
-      for (int h = 0; h < CP; ++h) {
-        const uint32_t k = k0 + (uint32_t)h;
-        if (k >= i_end) break;  // wave-uniform
-        const uint32_t ch = wave + kGWaves * (i0 + k);
-        uint64_t u[kGSub];
+      for (uint32_t h = 0; h < 2u; ++h) {
+        const uint32_t k = min(k0 + h, i_end - 1u);
+        Word u[kGSub];
         uint32_t mu[kGSub];
 #pragma unroll
         for (uint32_t sb = 0; sb < kGSub; ++sb) {
-          u[sb] = st[h][sb] & kUMask;
-          mu[sb] = (uint32_t)(st[h][sb] >> 62);
+          u[sb] = (Word)(st[h][sb] & kUMask);
+          mu[sb] = (uint32_t)(st[h][sb] >> 62) + 2u * popc(u[sb] & vs[sb]);
         }
         const uint32_t pm = (uint32_t)__builtin_amdgcn_readlane((int)m_pm, (int)k);
 #pragma unroll
-        for (uint32_t s = 0; s < kMetroWin; ++s)
-          if ((pm >> s) & 1u) flip(u, mu, s, (uint32_t)__builtin_amdgcn_readlane((int)m_js[s], (int)k));
-        if (write) {
-          uint64_t* sp = Mv.state + ((uint64_t)ch * chi + tile0);
-          if (full) {
+        for (uint32_t q = 0; q < kMetroWin; ++q)
+          if ((pm >> q) & 1u) flip(u, mu, q, (uint32_t)__builtin_amdgcn_readlane((int)m_js[q], (int)k));
+        if (write && k == k0 + h) {
+          uint64_t* sp = Mv.state + ((uint64_t)(w0 + n_waves * (i0 + k)) * chi + tile0);
 #pragma unroll
-            for (uint32_t sb = 0; sb < kGSub; ++sb) sp[sb * 64u + lane] = u[sb] | ((uint64_t)(mu[sb] & 3u) << 62);
-          } else {
-#pragma unroll
-            for (uint32_t sb = 0; sb < kGSub; ++sb)
-              if (sb * 64u + lane <= last) sp[sb * 64u + lane] = u[sb] | ((uint64_t)(mu[sb] & 3u) << 62);
+          for (uint32_t sb = 0; sb < kGSub; ++sb) {
+            const uint32_t m = (mu[sb] + 2u * popc(u[sb] & vs[sb])) & 3u;
+            if (full || sb * 64u + lane <= last) sp[sb * 64u + lane] = (uint64_t)u[sb] | ((uint64_t)m << 62);
           }
         }
-        if (!prop) continue;
-        flip(u, mu, kMetroWin, (uint32_t)__builtin_amdgcn_readlane((int)m_j, (int)k));
-        double2 t0 = term_value(c[0], u[0], mu[0] & 3u);
-        double re = t0.x, im = t0.y;
+        if (nprop == 0u) continue;
+        const uint32_t j1 = (uint32_t)__builtin_amdgcn_readlane((int)m_js[kMetroWin], (int)k);
+        const uint32_t j2 = (uint32_t)__builtin_amdgcn_readlane((int)m_js[kMetroWin + 1], (int)k);
+        Word u1[kGSub];
+        uint32_t mu1[kGSub];
 #pragma unroll
-        for (uint32_t sb = 1; sb < kGSub; ++sb) {
-          const double2 val = term_value(c[sb], u[sb], mu[sb] & 3u);
-          re += val.x;
-          im += val.y;
+        for (uint32_t sb = 0; sb < kGSub; ++sb) {
+          u1[sb] = u[sb];
+          mu1[sb] = mu[sb];
         }
-        re = wave_sum0(re);
-        im = wave_sum0(im);
-        if (lane == 0) Mv.partial[(uint64_t)ch * Mv.n_tiles + blockIdx.x] = make_double2(re, im);
+        double* const sm = sum + 6 * h;
+        flip(u1, mu1, kMetroWin, j1);
+        value(u1, mu1, sm[0], sm[1]);
+        if (nprop == 2u) {
+          flip(u1, mu1, kMetroWin + 1u, j2);
+          value(u1, mu1, sm[2], sm[3]);
+          flip(u, mu, kMetroWin + 1u, j2);
+          value(u, mu, sm[4], sm[5]);
+        } else {
+          sm[2] = sm[3] = sm[4] = sm[5] = 0.0;
+        }
+      }
+      if (nprop == 0u) continue;
+      // 12 sums over 64 lanes: r[k] holds sums 4 k, 4 k + 2, 4 k + 1, 4 k + 3 in its rows.
+      double r[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        r[k] = row_sum(swap_add16(swap_add32(sum[4 * k], sum[4 * k + 1]), swap_add32(sum[4 * k + 2], sum[4 * k + 3])));
+      const uint32_t rr = lane >> 4, kk = lane & 15u;
+      const double x = kk == 0u ? r[0] : kk == 1u ? r[1] : r[2];
+      const uint32_t f = 4u * kk + ((rr & 1u) << 1 | rr >> 1);  // [chain][value][re, im]
+      const uint32_t h = f >= 6u ? 1u : 0u, g = f - 6u * h;
+      if (kk < 3u && k0 + h < i_end && (g < 2u || nprop == 2u)) {
+        const uint32_t ch = w0 + n_waves * (i0 + k0 + h);
+        double* const out = reinterpret_cast<double*>(Mv.partial + (g >> 1) * plane + (size_t)ch * Mv.n_tiles + blockIdx.x);
+        out[g & 1u] = x;
       }
     }
   }
 }
 
-// Single flips gather rows per term (deferred cache updates); flip masks
-// (several rows per chain) read the tile's rows once through LDS.
-hipError_t launch_gather(const TermsView& T, MetroView& Mv, uint32_t step, uint32_t pbase,
-                         uint32_t npend, uint32_t mode, hipStream_t st) {
-  hipLaunchKernelGGL(k_propose_gather<2>, dim3(Mv.n_tiles), dim3(64 * kGWaves), 0, st, T, Mv, step,
-                     pbase, npend, mode);
+// The rows' form: packed while n bits of F and M and two of gamma fit a word
+// (chi = 2^16, 64 chains with their own bits, n = 12: 10.7 µs per step; the term
+// store's rows read per chain took 29), 32-bit halves up to n = 30 (M and F in one
+// register each), 64-bit words above.  Workgroups along the chains: with few tiles the chains are split over more
+// workgroups (the tile's rows staged by each), up to about four per compute
+// unit; a wave keeps at least two chains, the pair of one pass.
+uint32_t chain_splits(uint32_t n_tiles, uint32_t n_chain) {
+  const uint32_t want = (1024u + n_tiles - 1u) / n_tiles, most = (n_chain + 2u * kGWaves - 1u) / (2u * kGWaves);
+  return std::max(1u, std::min(want, most));
+}
+
+hipError_t launch_pair(const TermsView& T, MetroView& Mv, uint32_t step, uint32_t nprop, uint32_t pbase,
+                       uint32_t npend, uint32_t mode, hipStream_t st) {
+  const dim3 grid(Mv.n_tiles, chain_splits(Mv.n_tiles, Mv.n_chain));
+  const size_t vals = 5u * kMetroTile * sizeof(double2);
+  if (T.n <= kPackedMaxN)
+    hipLaunchKernelGGL(k_propose_pair<kPacked>, grid, dim3(64 * kGWaves), vals + (size_t)T.n * kMetroTile * 4u, st, T,
+                       Mv, step, nprop, pbase, npend, mode);
+  else if (T.n <= kSlots32MaxN)
+    hipLaunchKernelGGL(k_propose_pair<kSlots32>, grid, dim3(64 * kGWaves), vals + kSlots * kMetroTile * 9u, st, T, Mv,
+                       step, nprop, pbase, npend, mode);
+  else
+    hipLaunchKernelGGL(k_propose_pair<kSlots64>, grid, dim3(64 * kGWaves), vals + kSlots * kMetroTile * 17u, st, T, Mv,
+                       step, nprop, pbase, npend, mode);
   return hipGetLastError();
 }
 
@@ -453,38 +604,65 @@ hipError_t launch_masks(const TermsView& T, MetroView& Mv, const uint64_t* mask,
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_metro_accept(MetroView Mv, uint32_t step) {
+// Steps `step` and, with nprop = 2, step + 1 of a chain: the sums of the tiles'
+// partials (plane 0: the first proposal; planes 1 and 2: the second after the
+// first was accepted, rejected) and the decisions.
+__global__ __launch_bounds__(256) void k_metro_accept(MetroView Mv, uint32_t step, uint32_t nprop) {
   __shared__ double2 scratch[4];
   const uint32_t ch = blockIdx.x;
-  double2 acc = make_double2(0.0, 0.0);
-  for (uint32_t t = threadIdx.x; t < Mv.n_tiles; t += 256u) {
-    const double2 v = Mv.partial[(uint64_t)ch * Mv.n_tiles + t];
-    acc.x += v.x;
-    acc.y += v.y;
+  const size_t plane = (size_t)Mv.n_chain * Mv.n_tiles;
+  double2 acc[3];
+  const double2* p = Mv.partial + (size_t)ch * Mv.n_tiles;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) acc[q] = make_double2(0.0, 0.0);
+  if (nprop == 2u) {
+    for (uint32_t t = threadIdx.x; t < Mv.n_tiles; t += 256u) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const double2 v = p[q * plane + t];
+        acc[q].x += v.x;
+        acc[q].y += v.y;
+      }
+    }
+  } else {
+    for (uint32_t t = threadIdx.x; t < Mv.n_tiles; t += 256u) {
+      const double2 v = p[t];
+      acc[0].x += v.x;
+      acc[0].y += v.y;
+    }
   }
-  const double2 ay = block_sum(acc, scratch);
-  if (threadIdx.x == 0) {
-    const uint64_t idx = (uint64_t)ch * Mv.n_steps + step;
-    const double2 ax = Mv.amp[ch];
+  double2 a[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    a[q] = make_double2(0.0, 0.0);
+    if (q == 0 || nprop == 2u) a[q] = block_sum(acc[q], scratch);
+  }
+  if (threadIdx.x != 0) return;
+  uint64_t x = Mv.x[ch];
+  double2 ax = Mv.amp[ch];
+  // The steps' bits in the chain's window of deferred cache updates.
+  const uint32_t w = step % kMetroWin;
+  uint32_t pend = w ? Mv.pend[ch] : 0u;
+  uint32_t took = 0u;
+  for (uint32_t k = 0; k < nprop; ++k) {
+    const uint64_t idx = (uint64_t)ch * Mv.n_steps + step + k;
+    const double2 ay = k == 0u ? a[0] : took ? a[1] : a[2];
     const double px = ax.x * ax.x + ax.y * ax.y;
     const double py = ay.x * ay.x + ay.y * ay.y;
     const double r = py / px;
     const double U = Mv.ustream[idx];
-    const uint32_t acc_ = (px > 0.0) && (r >= 1.0 || U < r);
-    uint64_t x = Mv.x[ch];
-    // The step's bit in the chain's window of deferred cache updates.
-    const uint32_t w = step % kMetroWin;
-    uint32_t pend = w ? Mv.pend[ch] : 0u;
-    if (acc_) {
+    took = (px > 0.0) && (r >= 1.0 || U < r);
+    if (took) {
       x ^= 1ull << (Mv.jstream[idx] % Mv.n_qubits);
-      Mv.x[ch] = x;
-      Mv.amp[ch] = ay;
-      pend |= 1u << w;
+      ax = ay;
+      pend |= 1u << (w + k);
     }
-    Mv.pend[ch] = pend;
     if (Mv.trace) Mv.trace[idx] = x;
-    if (Mv.accepted) Mv.accepted[idx] = (uint8_t)acc_;
+    if (Mv.accepted) Mv.accepted[idx] = (uint8_t)took;
   }
+  Mv.x[ch] = x;
+  Mv.amp[ch] = ax;
+  Mv.pend[ch] = pend;
 }
 
 }  // namespace
@@ -499,25 +677,26 @@ hipError_t launch_metro_init(const TermsView& T, MetroView& Mv, hipStream_t st) 
 }
 
 hipError_t launch_metro_steps(const TermsView& T, MetroView& Mv, uint32_t n_steps, hipStream_t st) {
+  static_assert(kMetroWin % 2 == 0, "a pair of steps lies in one window");
   if (n_steps == 0) return hipSuccess;
-  for (uint32_t t = 0; t < n_steps; ++t) {
-    // Step t applies the accepted flips of its window's earlier steps; the
-    // first step of a window (t > 0) applies the whole previous window and
+  for (uint32_t t = 0; t < n_steps; t += 2u) {
+    // Steps t, t + 1 apply the accepted flips of their window's earlier steps;
+    // the first pair of a window (t > 0) applies the whole previous window and
     // writes the caches back.
+    const uint32_t nprop = std::min(2u, n_steps - t);
     const uint32_t w = t % kMetroWin;
     const bool close = w == 0 && t > 0;
     const uint32_t pbase = close ? t - kMetroWin : t - w, npend = close ? kMetroWin : w;
-    hipError_t e = launch_gather(T, Mv, t, pbase, npend,
-                                 kModePropose | (close ? kModeWrite : 0u), st);
+    hipError_t e = launch_pair(T, Mv, t, nprop, pbase, npend, close ? kModeWrite : 0u, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_metro_accept, dim3(Mv.n_chain), dim3(256), 0, st, Mv, t);
+    hipLaunchKernelGGL(k_metro_accept, dim3(Mv.n_chain), dim3(256), 0, st, Mv, t, nprop);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   // The last window's accepted flips, so that every chain's current cache is
   // up to date when the call returns.
   const uint32_t t0 = (n_steps - 1u) / kMetroWin * kMetroWin;
-  return launch_gather(T, Mv, 0, t0, n_steps - t0, kModeWrite, st);
+  return launch_pair(T, Mv, 0, 0, t0, n_steps - t0, kModeWrite, st);
 }
 
 hipError_t launch_propose(const TermsView& T, MetroView& Mv, const uint64_t* mask, uint32_t mode,
