@@ -109,7 +109,7 @@ __device__ __forceinline__ double2 block_sum(double2 v, double2* scratch) {
   return r;
 }
 
-// Initial Q_x for every chain (the O(k n^2) start-up cost) and the tile sums of
+// Few chains: the initial Q_x of every chain (the O(k n^2) start-up cost) and the tile sums of
 // <x_c|psi>.
 __global__ __launch_bounds__(256) void k_metro_init(TermsView T, MetroView Mv) {
   __shared__ double2 scratch[4];
@@ -166,6 +166,12 @@ __global__ __launch_bounds__(256) void k_chain_amp(MetroView Mv) {
 // w + 8, ...; a chain's masks are wave-uniform, so the loops over their set
 // bits do not diverge and each term's rows leave HBM once per step for all
 // chains.
+//
+// With kInit it is the chains' start: Q_x = prod_{j in x} P_j from the
+// identity (no cache word is read), the cache words are written, and the sums are
+// those of <x|psi>.  Reading the rows once for all chains instead of once per
+// chain: n = 50, chi = 2^20, 64 chains 880 µs (3944 with the term store's
+// rows read by each chain); n = 12, chi = 2^16: 41 and 105.
 constexpr uint32_t kSub = 64;
 constexpr int kCW = 8;           // chains per wave in one pass
 constexpr uint32_t kPWaves = 8;  // waves per block: kPWaves * kCW = 64 chains per pass
@@ -173,6 +179,7 @@ constexpr uint32_t kPThreads = 64 * kPWaves;
 constexpr int kStage = (int)((64 * kSub + kPThreads - 1) / kPThreads);  // staging loads per thread
 static_assert(kStage % 2 == 0, "staged in two halves");
 
+template <bool kInit>
 __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv,
                                                        const uint64_t* __restrict__ mask,
                                                        uint32_t mode) {
@@ -183,7 +190,8 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
   uint8_t* sG = reinterpret_cast<uint8_t*>(sM + (size_t)n * kSub);  // [n][64]
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform32(tid >> 6);
   const uint64_t chi = T.chi;
-  const bool pend = mode & kProposeApplyPending, prop = mode & kProposeMasks;
+  const bool pend = !kInit && (mode & kProposeApplyPending), prop = kInit || (mode & kProposeMasks);
+  const uint64_t nmask = (1ull << n) - 1ull;  // n <= 62
   // Right product by P_j for every set bit j of mm.
   auto apply = [&](uint64_t& u, uint32_t& mu, uint64_t mm) {
     while (mm) {
@@ -201,10 +209,16 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
     for (int k = 0; k < kCW; ++k) {
       const uint32_t ch = cg + wave + kPWaves * (uint32_t)k;
       const bool on = ch < Mv.n_chain;
-      m[k] = on && prop ? uniform64(mask[ch]) : 0ull;
+      m[k] = on && prop ? uniform64(kInit ? Mv.x[ch] & nmask : mask[ch]) : 0ull;
       pm[k] = on && pend ? uniform64(Mv.pmask[ch]) : 0ull;
       accr[k] = 0.0;
       acci[k] = 0.0;
+    }
+    // At the start only the rows of some chain's bits are read (one chain has half of them).
+    uint64_t rows = ~0ull;
+    if (kInit) {
+      rows = cg + lane < Mv.n_chain ? Mv.x[cg + lane] : 0ull;  // the pass's 64 chains, one per lane
+      for (int k = 32; k >= 1; k >>= 1) rows |= __shfl_xor(rows, k);
     }
     for (uint32_t sub = 0; sub < kMetroTile / kSub; ++sub) {
       const uint64_t base = (uint64_t)blockIdx.x * kMetroTile + (uint64_t)sub * kSub;
@@ -221,7 +235,7 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
           const uint32_t i = tid + (uint32_t)(half * (kStage / 2) + r) * kPThreads;
           const uint32_t p = i / kSub, t = i % kSub;
           const uint64_t at = base + t;
-          const bool in = i < n * kSub && at < chi;
+          const bool in = i < n * kSub && at < chi && ((rows >> p) & 1ull);
           rf[r] = in ? T.F[(uint64_t)p * chi + at] : 0ull;
           rm[r] = in ? T.M[(uint64_t)p * chi + at] : 0ull;
           rg[r] = in ? T.gamma[(uint64_t)p * chi + at] : 0u;
@@ -243,15 +257,16 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
 #pragma unroll
       for (int k = 0; k < kCW; ++k) {
         const uint32_t ch = cg + wave + kPWaves * (uint32_t)k;
-        st[k] = (live && (m[k] | pm[k]) != 0ull) ? Mv.state[(uint64_t)ch * chi + a] : 0ull;
+        st[k] = (!kInit && live && (m[k] | pm[k]) != 0ull) ? Mv.state[(uint64_t)ch * chi + a] : 0ull;
       }
       TermAmpConst c{};
       if (live && prop) c = load_const(T, a);
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < kCW; ++k) {
-        if ((m[k] | pm[k]) == 0ull || !live) continue;  // nothing to do, no such chain, or past chi
         const uint32_t ch = cg + wave + kPWaves * (uint32_t)k;
+        // Nothing to do, no such chain, or past chi.
+        if (((m[k] | pm[k]) == 0ull && !(kInit && ch < Mv.n_chain)) || !live) continue;
         uint64_t u = st[k] & kUMask;
         uint32_t mu = (uint32_t)(st[k] >> 62);
         if (pm[k]) {
@@ -259,8 +274,9 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
           mu &= 3u;
           Mv.state[(uint64_t)ch * chi + a] = u | ((uint64_t)mu << 62);
         }
-        if (m[k] == 0ull) continue;  // y = x: no proposal
+        if (m[k] == 0ull && !kInit) continue;  // y = x: no proposal
         apply(u, mu, m[k]);
+        if (kInit) Mv.state[(uint64_t)ch * chi + a] = u | ((uint64_t)(mu & 3u) << 62);
         const double2 val = term_value(c, u, mu & 3u);
         accr[k] += val.x;
         acci[k] += val.y;
@@ -592,15 +608,16 @@ hipError_t launch_pair(const TermsView& T, MetroView& Mv, uint32_t step, uint32_
   return hipGetLastError();
 }
 
+template <bool kInit>
 hipError_t launch_masks(const TermsView& T, MetroView& Mv, const uint64_t* mask, uint32_t mode,
                         hipStream_t st) {
   const size_t sm = (size_t)T.n * kSub * 17;
   if (sm > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_propose,
+    const hipError_t e = hipFuncSetAttribute((const void*)k_propose<kInit>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_propose, dim3(Mv.n_tiles), dim3(kPThreads), sm, st, T, Mv, mask, mode);
+  hipLaunchKernelGGL(k_propose<kInit>, dim3(Mv.n_tiles), dim3(kPThreads), sm, st, T, Mv, mask, mode);
   return hipGetLastError();
 }
 
@@ -668,9 +685,16 @@ __global__ __launch_bounds__(256) void k_metro_accept(MetroView Mv, uint32_t ste
 }  // namespace
 
 hipError_t launch_metro_init(const TermsView& T, MetroView& Mv, hipStream_t st) {
-  const uint32_t tiles = Mv.n_tiles;
-  hipLaunchKernelGGL(k_metro_init, dim3(tiles), dim3(kMetroTile), 0, st, T, Mv);
-  hipError_t e = hipGetLastError();
+  // From 8 chains on the tile's rows are staged once for all of them; below, each
+  // chain reads its own bits' rows (n = 50, chi = 2^18, host time of the call:
+  // 1 chain 43 µs and 63 staged, 8 chains 75 and 71, 64 chains 328 and 140).
+  hipError_t e;
+  if (Mv.n_chain >= 8u) {
+    e = launch_masks<true>(T, Mv, nullptr, 0u, st);
+  } else {
+    hipLaunchKernelGGL(k_metro_init, dim3(Mv.n_tiles), dim3(kMetroTile), 0, st, T, Mv);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_chain_amp, dim3(Mv.n_chain), dim3(256), 0, st, Mv);
   return hipGetLastError();
@@ -701,7 +725,7 @@ hipError_t launch_metro_steps(const TermsView& T, MetroView& Mv, uint32_t n_step
 
 hipError_t launch_propose(const TermsView& T, MetroView& Mv, const uint64_t* mask, uint32_t mode,
                           hipStream_t st) {
-  return launch_masks(T, Mv, mask, mode, st);
+  return launch_masks<false>(T, Mv, mask, mode, st);
 }
 
 }  // namespace chsim
