@@ -139,8 +139,8 @@ KERNEL_SOURCES = {
     "k_evolve_cols": ["evolve_cols.hpp", "bitops.hpp", "evolve_w64.hip", "evolve.hip", "prefix.hip",
                      "device_common.hpp", "internal.hpp", "api.hip"],
     "k_amp<float>": ["amplitude.hip", "device_common.hpp", "internal.hpp", "api.hip"],
-    "k_inner_pairs": ["inner.hip", "device_common.hpp", "internal.hpp", "api.hip"],
-    "k_inner_ch_pairs": ["inner_ch.hip", "device_common.hpp", "internal.hpp", "api.hip"],
+    "k_quad_pairs": ["quad_pairs.hip", "inner.hip", "bitops.hpp", "device_common.hpp", "internal.hpp", "api.hip"],
+    "k_quad_pairs(ch)": ["quad_pairs.hip", "inner_ch.hip", "bitops.hpp", "device_common.hpp", "internal.hpp", "api.hip"],
 }
 
 
@@ -209,8 +209,8 @@ def bench_norm(torch, B, W, L=1024):
             "eta_mean": eta_mean, "eta_sem": float(np.std(eta, ddof=1) / np.sqrt(L)),
             "mean_v_weight": mean_v,
             "roofline": roof("alu", achieved, INT32_PEAK_OPS / 1e12, "TOP/s (int32)", MEASURED.get("valu"),
-                             kernel="k_inner_prep + k_inner_pairs (lane = equatorial state)",
-                             traffic=counter_traffic("k_inner_pairs"), ops_per_pair=ops_pair,
+                             kernel="k_quad_prep + k_quad_pairs (bit-sliced, 128 states per wave)",
+                             traffic=counter_traffic("k_quad_pairs"), ops_per_pair=ops_pair,
                              count="6 n^2 + 2 (|v| + 1)^2 int32 ops per (term, A)")}
 
 
@@ -251,8 +251,8 @@ def bench_inner_ch(torch, B, W, L=256):
             "eta_mean": float(eta.mean()), "eta_sem": float(eta.std(ddof=1) / np.sqrt(L)),
             "mean_v_weight_bra": mean_popcount(vb), "mean_v_weight_ket": mean_popcount(vk),
             "roofline": roof("alu", achieved, INT32_PEAK_OPS / 1e12, "TOP/s (int32)", MEASURED.get("valu"),
-                             kernel="k_chrec + k_inner_ch_pairs (one wave per pair, lane = row)",
-                             traffic=counter_traffic("k_inner_ch_pairs"), ops_per_pair=ops_pair,
+                             kernel="k_chrec + k_quad_prep + k_quad_pairs (bit-sliced, 128 states per wave)",
+                             traffic=counter_traffic("k_quad_pairs(ch)"), ops_per_pair=ops_pair,
                              count="2 (2 n^2 + 3 (|v| + 1)^2) int32 ops per pair (64-bit word operations x 2)")}
 
 

@@ -37,7 +37,7 @@ EXTRA_FLAGS = {
 # of the columns alive (454 spilled registers instead of none at n = 50).
 EXTRA_FLAGS.update({
     name: ["-mllvm", "-structurizecfg-skip-uniform-regions=true"]
-    for name in ("evolve_c4a.hip", "evolve_c4b.hip", "evolve_c8.hip", "evolve_c16.hip")
+    for name in ("evolve_c4a.hip", "evolve_c4b.hip", "evolve_c8.hip", "evolve_c16.hip", "quad_pairs.hip")
 })
 
 

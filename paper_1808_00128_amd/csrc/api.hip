@@ -1595,16 +1595,19 @@ chsim_status chsim_inner_products_ch(chsim_ctx* ctx, uint32_t inst, uint32_t bra
   if ((st = ensure_materialised(K, s))) return st;
   if ((st = ensure_materialised(Bt, s))) return st;
   const uint32_t n = K.n, L = (uint32_t)Bt.chi;
-  HIP_TRY(ctx->chrec_k.ensure(inner_ch_record_words(n, K.chi)));
-  HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
+  const InnerChPlan ip = inner_ch_plan(n, K.chi, L);
+  if (ip.pairs || bra_inst == inst) {
+    HIP_TRY(ctx->chrec_k.ensure(inner_ch_record_words(n, K.chi)));
+    HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
+  }
   const uint64_t* rec_b = ctx->chrec_k.p;
   if (bra_inst != inst) {
     HIP_TRY(ctx->chrec_b.ensure(inner_ch_record_words(n, Bt.chi)));
     HIP_TRY(launch_inner_ch_records(Bt.view(), ctx->chrec_b.p, s));
     rec_b = ctx->chrec_b.p;
   }
-  const uint32_t groups = inner_ch_groups(K.chi, L);
-  HIP_TRY(ctx->partial.ensure((size_t)groups * L));
+  HIP_TRY(ctx->partial.ensure(ip.partial_elems));
+  HIP_TRY(ctx->inner_work.ensure(ip.quad.words));
   double2* ovd;
   if (dev) ovd = reinterpret_cast<double2*>(overlap);
   else {
@@ -1620,7 +1623,7 @@ chsim_status chsim_inner_products_ch(chsim_ctx* ctx, uint32_t inst, uint32_t bra
     }
   }
   HIP_TRY(hipMemsetAsync(ctx->err.p, 0, sizeof(uint32_t), s));
-  HIP_TRY(launch_inner_ch(ctx->chrec_k.p, K.b.p, K.chi, rec_b, Bt.b.p, L, n, groups, ctx->partial.p, ovd, totd,
+  HIP_TRY(launch_inner_ch(K.view(), Bt.view(), ip, ctx->chrec_k.p, rec_b, ctx->inner_work.p, ctx->partial.p, ovd, totd,
                           ctx->err.p, s));
   if (!dev) {
     HIP_TRY(hipMemcpyAsync(overlap, ovd, (size_t)L * sizeof(double2), hipMemcpyDeviceToHost, s));

@@ -10,13 +10,14 @@
 // variables with the identity sum_{x1,x2} (-1)^{x1 x2 + mu1 x1 + mu2 x2} =
 // 2 (-1)^{mu1 mu2} (Eq. (eq5)).
 //
-// Mapping.  A per-term prologue (one wave per term, lane = row) stores the
-// term's rows and columns of G and K_J = G^T J G with the vectors the pair
-// step needs, restricted to supp(v) and compressed to |v| bits (only the
-// variables in supp(v) enter B); K_J is shared by every equatorial state
-// since K is linear in A + J.  The pair kernel gives each lane one
-// equatorial state A (64 per wave) and walks the terms (pair_term below);
-// with |v| < 32 every word of a term's Z_2 form fits 32 bits.
+// Terms with at most kQuadMaxVars variables, so all of them for n up to that, go
+// to the bit-sliced kernels (quad_pairs.hip).  The kernels here take the rest: a
+// per-term prologue (one wave per term, lane = row) stores the term's rows and
+// columns of G and K_J = G^T J G with the vectors the pair step needs, restricted to
+// supp(v) and compressed to |v| bits (only the variables in supp(v) enter B); K_J
+// is shared by every equatorial state since K is linear in A + J.  The pair kernel
+// gives each lane one equatorial state A (64 per wave) and walks the terms
+// (pair_term below).
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -210,25 +211,11 @@ __global__ __launch_bounds__(256) void k_inner_atrans(const uint64_t* __restrict
   planes[Lp + l] = hi;
 }
 
-template <typename Word>
-__device__ __forceinline__ Word rlw(Word x, uint32_t src);
-template <>
-__device__ __forceinline__ uint32_t rlw<uint32_t>(uint32_t x, uint32_t src) {
-  return rl32(x, src);
-}
-template <>
-__device__ __forceinline__ uint64_t rlw<uint64_t>(uint64_t x, uint32_t src) {
-  return rl64(x, src);
-}
 // All ones if bit 0 of b is set.
-template <typename Word>
-__device__ __forceinline__ Word wmask(uint64_t b) {
-  return (Word)0 - (Word)(b & 1u);
-}
+__device__ __forceinline__ uint64_t wmask(uint64_t b) { return 0ull - (b & 1ull); }
 
 // One term against the wave's 64 equatorial states (lane = state), in the
-// term's compressed variables (bit a' = the a'-th qubit of supp(v)): Word is
-// 32 bits when the Z_2 form's |v| + 1 variables fit, else 64.  Everything
+// term's compressed variables (bit a' = the a'-th qubit of supp(v)).  Everything
 // that depends only on the term is wave-uniform:
 //   Z_c = A_c G and W_c = U_c G (U = strictly upper part of A) by lookup in
 //   tables of XORs of G's rows, four rows per table (Four Russians);
@@ -238,48 +225,48 @@ __device__ __forceinline__ Word wmask(uint64_t b) {
 //   s K_A s^T = y^T A y mod 4 with y = G s.
 // Each lane then eliminates its own Z_2 form (rows in LDS, pivots chosen per
 // lane) and adds b_alpha <phi_A|phi_alpha> to its state's sum.
-template <typename Word, int NS, int NMAX>
+template <int NS, int NMAX>
 __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32_t n, uint32_t nv, uint32_t lane,
                                           uint32_t l, uint32_t L, const uint64_t* __restrict__ atl, uint32_t Lp,
                                           uint64_t adlo, uint64_t adhi, uint32_t omega, uint32_t sv, double2 bb,
-                                          Word* __restrict__ gtab, void* __restrict__ srow, double& accr,
+                                          uint64_t* __restrict__ gtab, void* __restrict__ srow, double& accr,
                                           double& acci) {
   constexpr uint32_t kChunks = (NMAX + 3) / 4;
-  const Word Gl = lane < n ? (Word)r[lane] : (Word)0;
+  const uint64_t Gl = lane < n ? (uint64_t)r[lane] : (uint64_t)0;
   const uint64_t Gtl = lane < nv ? r[n + lane] : 0ull;
-  const Word KJl = lane < nv ? (Word)r[2u * n + lane] : (Word)0;
-  const Word kjdlo = (Word)uniform64(r[3u * n]), kjdhi = (Word)uniform64(r[3u * n + 1u]);
-  const Word skj = (Word)uniform64(r[3u * n + 2u]);
+  const uint64_t KJl = lane < nv ? (uint64_t)r[2u * n + lane] : (uint64_t)0;
+  const uint64_t kjdlo = uniform64(r[3u * n]), kjdhi = uniform64(r[3u * n + 1u]);
+  const uint64_t skj = uniform64(r[3u * n + 2u]);
   const uint64_t y = uniform64(r[3u * n + 3u]);
   const uint32_t sksj = uniform32((uint32_t)r[3u * n + 4u]);
-  const Word sc = (Word)uniform64(r[3u * n + 5u]);
+  const uint64_t sc = uniform64(r[3u * n + 5u]);
   // Lookup tables: gtab[k][e] = XOR of G rows 4k + i over the bits i of e
   // (zero for chunks at or past n, so every chunk of NMAX can be looked up).
   for (uint32_t k = 0; k < kChunks; ++k) {
-    Word t = 0;
+    uint64_t t = 0;
     for (uint32_t i = 0; i < 4u; ++i) {
       const uint32_t row = 4u * k + i;
-      if (row < n) t ^= rlw<Word>(Gl, row) & wmask<Word>(lane >> i);
+      if (row < n) t ^= rl64(Gl, row) & wmask(lane >> i);
     }
     if (lane < 16u) gtab[k * 16u + lane] = t;
   }
   __builtin_amdgcn_wave_barrier();
-  // With 64-bit words the rows of only 32 lanes fit the LDS region at once:
-  // the two halves of the wave take the term one after the other.
-  constexpr bool kWide = sizeof(Word) == 8;
-  const uint32_t stride = kWide ? 32u : 64u, slot = kWide ? (lane & 31u) : lane;
-  Word* const S = reinterpret_cast<Word*>(srow);
-  for (uint32_t h = 0; h < (kWide ? 2u : 1u); ++h) {
-    if (kWide && (lane >> 5) != h) continue;
+  // The rows of only 32 lanes fit the LDS region at once: the two halves of the
+  // wave take the term one after the other.
+  constexpr uint32_t stride = 32u;
+  const uint32_t slot = lane & 31u;
+  uint64_t* const S = reinterpret_cast<uint64_t*>(srow);
+  for (uint32_t h = 0; h < 2u; ++h) {
+    if ((lane >> 5) != h) continue;
     // One pass over A's rows.
-    Word Sacc[NS];
+    uint64_t Sacc[NS];
 #pragma unroll
     for (int a = 0; a < NS; ++a) Sacc[a] = 0;
-    Word D = 0, sKA = 0;
+    uint64_t D = 0, sKA = 0;
     uint64_t tU = 0;
     uint64_t Anext = atl[0];
     for (uint32_t c = 0; c < n; ++c) {
-      const Word Gc = rlw<Word>(Gl, c);
+      const uint64_t Gc = rl64(Gl, c);
       const uint64_t Ac = Anext;
       if (c + 1u < n) Anext = atl[(uint64_t)(c + 1u) * Lp];  // next row in flight
       const uint64_t upc = (c == 63u) ? 0ull : (~0ull << (c + 1u));
@@ -288,18 +275,18 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
       // issued at once; above the chunk holding c the nibbles of A_c and U_c
       // agree, that chunk takes a lookup of its own, below it U_c is zero.
       const uint32_t kc = c >> 2;
-      Word tz[kChunks];
+      uint64_t tz[kChunks];
 #pragma unroll
       for (uint32_t k = 0; k < kChunks; ++k) tz[k] = gtab[k * 16u + (uint32_t)((Ac >> (4u * k)) & 15ull)];
-      Word W = gtab[kc * 16u + (uint32_t)((Uc >> (4u * kc)) & 15ull)];
-      Word Z = 0;
+      uint64_t W = gtab[kc * 16u + (uint32_t)((Uc >> (4u * kc)) & 15ull)];
+      uint64_t Z = 0;
 #pragma unroll
       for (uint32_t k = 0; k < kChunks; ++k) {
         Z ^= tz[k];
-        W ^= tz[k] & wmask<Word>(k > kc);
+        W ^= tz[k] & wmask(k > kc);
       }
       D ^= Gc & W;
-      sKA ^= Gc & wmask<Word>(par64(Ac & y));
+      sKA ^= Gc & wmask(par64(Ac & y));
       if ((y >> c) & 1ull) tU ^= Uc & y;
       // K_A rows on supp(v): S_a ^= Z_c for the a with G_ca = 1 (a uniform
       // test per row: only those rows do any vector work).
@@ -308,34 +295,34 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
         if ((Gc >> a) & 1u) Sacc[a] ^= Z;
     }
     // B on supp(v): Bd_a = K_aa + 2 (s_a + (sK)_a) with K = K_J + K_A.
-    const Word skl = skj ^ sKA;
-    Word kap = 0, lam = 0;
+    const uint64_t skl = skj ^ sKA;
+    uint64_t kap = 0, lam = 0;
     for (uint32_t a = 0; a < nv; ++a) {
       const uint64_t ga = rl64(Gtl, a);
       const uint32_t kd = (uint32_t)((kjdlo >> a) & 1u) + 2u * (uint32_t)((kjdhi >> a) & 1u) +
                           (uint32_t)__popcll(ga & adlo) + 2u * (uint32_t)__popcll(ga & adhi) +
                           2u * (uint32_t)((D >> a) & 1u);
       const uint32_t bd = (kd + 2u * (uint32_t)(((sc ^ skl) >> a) & 1u)) & 3u;
-      kap |= (Word)(bd & 1u) << a;
-      lam |= (Word)(bd >> 1) << a;
+      kap |= (uint64_t)(bd & 1u) << a;
+      lam |= (uint64_t)(bd >> 1) << a;
     }
     const uint32_t sks = (sksj + (uint32_t)__popcll(y & adlo) + 2u * (uint32_t)__popcll(y & adhi) +
                           2u * par64(tU)) & 3u;
     // Z_2 form of Eq. (Q) on supp(v) and one extra variable e = |v|.
     const uint32_t e = nv;
-    const Word eb = (Word)1 << e;
-    const Word Rset = (Word)((eb << 1) - (Word)1);
+    const uint64_t eb = (uint64_t)1 << e;
+    const uint64_t Rset = (uint64_t)((eb << 1) - (uint64_t)1);
 #pragma unroll
     for (int a = 0; a < NS; ++a) {
       if ((uint32_t)a < nv) {
-        const Word odd = (kap >> a) & (Word)1;
-        const Word row = (((rlw<Word>(KJl, (uint32_t)a) ^ Sacc[a]) ^ (kap & ((Word)0 - odd))) &
-                          ~((Word)1 << a)) | (odd << e);
+        const uint64_t odd = (kap >> a) & (uint64_t)1;
+        const uint64_t row = (((rl64(KJl, (uint32_t)a) ^ Sacc[a]) ^ (kap & ((uint64_t)0 - odd))) &
+                          ~((uint64_t)1 << a)) | (odd << e);
         S[(uint32_t)a * stride + slot] = row;
       }
     }
     S[e * stride + slot] = kap;
-    Word lr = lam, li = lam | eb, rem = Rset, iso = 0;
+    uint64_t lr = lam, li = lam | eb, rem = Rset, iso = 0;
     uint32_t sr = 0, si = 0, nel = 0;
     // Eliminate a pair (a, b) with S_ab = 1 at a time (Eq. (eq5)); pivots per
     // lane.  A variable whose row is zero has no neighbour and never gains
@@ -343,64 +330,56 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
     // pair), and its linear coefficients no longer change: it is set aside.
     for (;;) {
       uint32_t a = 0;
-      Word Sa = 0;
+      uint64_t Sa = 0;
       while (rem != 0) {
-        a = kWide ? (uint32_t)__builtin_ctzll((uint64_t)rem) : (uint32_t)__builtin_ctz((uint32_t)rem);
+        a = (uint32_t)__builtin_ctzll(rem);
         Sa = S[a * stride + slot];
         if (Sa != 0) break;
-        iso |= (Word)1 << a;
-        rem &= ~((Word)1 << a);
+        iso |= (uint64_t)1 << a;
+        rem &= ~((uint64_t)1 << a);
       }
       if (!__builtin_amdgcn_ballot_w64(rem != 0)) break;
       // Rows that no lane still holds are zero in every lane: only the
       // union of the remaining variables needs the update.
       const uint32_t remUl = wave_or32((uint32_t)rem);
-      const uint32_t remUh = kWide ? wave_or32((uint32_t)((uint64_t)rem >> 32)) : 0u;
+      const uint32_t remUh = wave_or32((uint32_t)(rem >> 32));
       if (rem != 0) {
-        const uint32_t b = kWide ? (uint32_t)__builtin_ctzll((uint64_t)Sa) : (uint32_t)__builtin_ctz((uint32_t)Sa);
-        const Word Sb = S[b * stride + slot];
-        const Word ab = ((Word)1 << a) | ((Word)1 << b);
-        const Word m1 = Sa & ~ab, m2 = Sb & ~ab;
+        const uint32_t b = (uint32_t)__builtin_ctzll(Sa);
+        const uint64_t Sb = S[b * stride + slot];
+        const uint64_t ab = ((uint64_t)1 << a) | ((uint64_t)1 << b);
+        const uint64_t m1 = Sa & ~ab, m2 = Sb & ~ab;
         // Row c ^= (S_ac ? row b : 0) ^ (S_bc ? row a : 0), outside a, b; on
         // 32-bit halves, the tests as sign-extending bit-field extracts (c is
         // wave-uniform, so rows c < 32 and c >= 32 take separate loops).
         const uint32_t m1l = (uint32_t)m1, m2l = (uint32_t)m2, nabl = ~(uint32_t)ab;
-        if constexpr (kWide) {
-          const uint32_t m1h = (uint32_t)((uint64_t)m1 >> 32), m2h = (uint32_t)((uint64_t)m2 >> 32);
-          const uint32_t nabh = ~(uint32_t)((uint64_t)ab >> 32);
-          auto upd = [&](uint32_t c, uint32_t k1, uint32_t k2) {
-            const uint64_t Sc = S[c * stride + slot];
-            const uint32_t Sl = ((uint32_t)Sc ^ (m2l & k1) ^ (m1l & k2)) & nabl;
-            const uint32_t Sh = ((uint32_t)(Sc >> 32) ^ (m2h & k1) ^ (m1h & k2)) & nabh;
-            S[c * stride + slot] = (Word)(((uint64_t)Sh << 32) | Sl);
-          };
-          for (uint32_t m = (uint32_t)Rset & remUl; m; m &= m - 1u) {
-            const uint32_t c = (uint32_t)__builtin_ctz(m);
-            upd(c, bit_mask32(m1l, c), bit_mask32(m2l, c));
-          }
-          for (uint32_t m = (uint32_t)((uint64_t)Rset >> 32) & remUh; m; m &= m - 1u) {
-            const uint32_t c = (uint32_t)__builtin_ctz(m);
-            upd(32u + c, bit_mask32(m1h, c), bit_mask32(m2h, c));
-          }
-        } else {
-          for (uint32_t m = (uint32_t)Rset & remUl; m; m &= m - 1u) {
-            const uint32_t c = (uint32_t)__builtin_ctz(m);
-            const uint32_t Sc = (uint32_t)S[c * stride + slot];
-            S[c * stride + slot] = (Word)((Sc ^ (m2l & bit_mask32(m1l, c)) ^ (m1l & bit_mask32(m2l, c))) & nabl);
-          }
+        const uint32_t m1h = (uint32_t)((uint64_t)m1 >> 32), m2h = (uint32_t)((uint64_t)m2 >> 32);
+        const uint32_t nabh = ~(uint32_t)((uint64_t)ab >> 32);
+        auto upd = [&](uint32_t c, uint32_t k1, uint32_t k2) {
+          const uint64_t Sc = S[c * stride + slot];
+          const uint32_t Sl = ((uint32_t)Sc ^ (m2l & k1) ^ (m1l & k2)) & nabl;
+          const uint32_t Sh = ((uint32_t)(Sc >> 32) ^ (m2h & k1) ^ (m1h & k2)) & nabh;
+          S[c * stride + slot] = (uint64_t)(((uint64_t)Sh << 32) | Sl);
+        };
+        for (uint32_t m = (uint32_t)Rset & remUl; m; m &= m - 1u) {
+          const uint32_t c = (uint32_t)__builtin_ctz(m);
+          upd(c, bit_mask32(m1l, c), bit_mask32(m2l, c));
+        }
+        for (uint32_t m = (uint32_t)((uint64_t)Rset >> 32) & remUh; m; m &= m - 1u) {
+          const uint32_t c = (uint32_t)__builtin_ctz(m);
+          upd(32u + c, bit_mask32(m1h, c), bit_mask32(m2h, c));
         }
         S[a * stride + slot] = 0;
         S[b * stride + slot] = 0;
         {
-          const Word la = (lr >> a) & (Word)1, lbb = (lr >> b) & (Word)1;
+          const uint64_t la = (lr >> a) & (uint64_t)1, lbb = (lr >> b) & (uint64_t)1;
           sr ^= (uint32_t)(la & lbb);
-          lr ^= (m2 & ((Word)0 - la)) ^ (m1 & ((Word)0 - lbb)) ^ (m1 & m2);
+          lr ^= (m2 & ((uint64_t)0 - la)) ^ (m1 & ((uint64_t)0 - lbb)) ^ (m1 & m2);
           lr &= ~ab;
         }
         {
-          const Word la = (li >> a) & (Word)1, lbb = (li >> b) & (Word)1;
+          const uint64_t la = (li >> a) & (uint64_t)1, lbb = (li >> b) & (uint64_t)1;
           si ^= (uint32_t)(la & lbb);
-          li ^= (m2 & ((Word)0 - la)) ^ (m1 & ((Word)0 - lbb)) ^ (m1 & m2);
+          li ^= (m2 & ((uint64_t)0 - la)) ^ (m1 & ((uint64_t)0 - lbb)) ^ (m1 & m2);
           li &= ~ab;
         }
         rem &= ~ab;
@@ -408,7 +387,7 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
       }
     }
     __builtin_amdgcn_wave_barrier();
-    const int rr = kWide ? __popcll((uint64_t)iso) : __popc((uint32_t)iso);
+    const int rr = __popcll(iso);
     const bool re_nz = (lr & iso) == 0, im_nz = (li & iso) == 0;
     // Re Z = (-1)^sr 2^{nel + r - 1}, Im Z likewise; both non-zero only with equal exponents.
     if (l < L && (re_nz || im_nz)) {
@@ -437,20 +416,16 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
   }
 }
 
-// LDS of one pair wave: the lookup tables (NMAX <= 64: 16 chunks of 16
-// 64-bit entries) and the elimination rows, 64 lanes x 32 variables of 32
-// bits or 32 lanes x (n + 1) variables of 64 bits.
+// LDS of one pair wave: the lookup tables (16 chunks of 16 entries) and the
+// elimination rows, 32 lanes x (n + 1) variables.
 __host__ __device__ constexpr uint32_t inner_gtab_bytes() { return 16u * 16u * 8u; }
-__host__ __device__ constexpr uint32_t inner_srow_bytes(uint32_t n) {
-  return (n + 1u) * 32u * 8u > 32u * 64u * 4u ? (n + 1u) * 32u * 8u : 32u * 64u * 4u;
-}
+__host__ __device__ constexpr uint32_t inner_srow_bytes(uint32_t n) { return (n + 1u) * 32u * 8u; }
 
 // One wave per (term group, batch of 64 states); lane = state.  The block
 // index maps XCD-aware: workgroups are dealt to the 8 XCDs in turn, and the
 // batches of one term group are consecutive on one XCD, so a term's record
 // is read from HBM once per XCD-resident group rather than once per batch.
-template <int NMAX>
-__global__ __launch_bounds__(64, NMAX <= 40 ? 3 : 2) void k_inner_pairs(TermsView Tv, const uint64_t* __restrict__ rec,
+__global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, const uint64_t* __restrict__ rec,
                                                     const uint64_t* __restrict__ at,
                                                     const uint64_t* __restrict__ planes, uint32_t L,
                                                     uint32_t Lp, uint32_t n_groups, uint32_t n_batches,
@@ -485,13 +460,10 @@ __global__ __launch_bounds__(64, NMAX <= 40 ? 3 : 2) void k_inner_pairs(TermsVie
       continue;
     }
     const uint32_t nv = (uint32_t)__popcll(v);
+    if (nv <= kQuadMaxVars) continue;  // taken by the bit-sliced kernels
     const uint32_t sv = par64(Tv.s[term] & v);
-    if (nv < 32u)
-      pair_term<uint32_t, (NMAX < 32 ? NMAX : 32), NMAX>(r, n, nv, lane, l, L, atl, Lp, adlo, adhi, omega, sv, bb,
-                                                         reinterpret_cast<uint32_t*>(gtab), srow, accr, acci);
-    else
-      pair_term<uint64_t, NMAX, NMAX>(r, n, nv, lane, l, L, atl, Lp, adlo, adhi, omega, sv, bb,
-                                      reinterpret_cast<uint64_t*>(gtab), srow, accr, acci);
+    pair_term<64, 64>(r, n, nv, lane, l, L, atl, Lp, adlo, adhi, omega, sv, bb, reinterpret_cast<uint64_t*>(gtab), srow,
+                      accr, acci);
   }
   if (bad && lane == 0u) atomicOr(err, 1u);
   if (l < L) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
@@ -550,10 +522,8 @@ __global__ __launch_bounds__(256) void k_eta_sum(const double* __restrict__ eta,
 }  // namespace
 
 // Waves per batch of 64 states, each over chi / groups terms: 512, and with
-// few batches as many more as fill the chip (3 waves per SIMD, 3072 in all): a
-// wave's terms are a serial chain, and 2 batches of 512 waves left two thirds
-// of the places empty (n = 20, chi = 3001, 100 states: 126 us, with 1536 groups
-// 59 us).  A multiple of 8 (the XCD-aware block order).
+// few batches as many more as fill the chip: a wave's terms are a serial chain.  A
+// multiple of 8 (the XCD-aware block order).
 uint32_t term_groups(uint64_t chi, uint32_t n_batches) {
   const uint32_t want = std::max<uint32_t>(512u, 3072u / n_batches);
   const uint32_t g = (uint32_t)std::min<uint64_t>(want, chi);
@@ -562,17 +532,20 @@ uint32_t term_groups(uint64_t chi, uint32_t n_batches) {
 
 InnerPlan inner_plan(const TermsView& T, uint32_t L) {
   InnerPlan P;
+  P.quad = quad_plan(T.n, T.chi, L, 0);
+  P.wide = T.n > kQuadMaxVars;
   P.Lp = (L + 63u) / 64u * 64u;
   P.n_batches = P.Lp / 64u;
   P.n_groups = term_groups(T.chi, P.n_batches);
-  P.partial_elems = (size_t)P.n_groups * L;
-  P.work_words = (size_t)T.chi * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
+  P.partial_elems = (size_t)(P.quad.rows + (P.wide ? P.n_groups : 0u)) * L;
+  P.work_words = P.quad.words;
+  if (P.wide) P.work_words += (size_t)T.chi * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
   return P;
 }
 
-hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t* Adiag, uint32_t L,
-                        const InnerPlan& P, double2* partial, uint64_t* work, double2* overlap,
-                        double* eta, double* eta_sum, uint32_t* err, hipStream_t st) {
+// Terms with more than kQuadMaxVars variables (n > kQuadMaxVars).
+static hipError_t launch_wide(const TermsView& T, const uint64_t* Aoff, const uint8_t* Adiag, uint32_t L,
+                              const InnerPlan& P, double2* partial, uint64_t* work, uint32_t* err, hipStream_t st) {
   const uint32_t n = T.n;
   uint64_t* rec = work;
   uint64_t* at = rec + (size_t)T.chi * inner_rec_words(n);
@@ -583,28 +556,24 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
                      at, planes);
   const size_t sm = (size_t)inner_gtab_bytes() + inner_srow_bytes(n);
   const dim3 grid(P.n_groups * P.n_batches);
-  switch ((n + 7u) / 8u) {
-#define CHSIM_INNER_CASE(k)                                                                          \
-  case k:                                                                                            \
-    hipLaunchKernelGGL(k_inner_pairs<8 * k>, grid, dim3(64), sm, st, T, rec, at, planes, L, P.Lp,     \
-                       P.n_groups, P.n_batches, partial, err);                                       \
-    break;
-    CHSIM_INNER_CASE(1)
-    CHSIM_INNER_CASE(2)
-    CHSIM_INNER_CASE(3)
-    CHSIM_INNER_CASE(4)
-    CHSIM_INNER_CASE(5)
-    CHSIM_INNER_CASE(6)
-    CHSIM_INNER_CASE(7)
-    CHSIM_INNER_CASE(8)
-#undef CHSIM_INNER_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, P.n_groups, L,
-                     T.n, overlap, eta);
+  hipLaunchKernelGGL(k_inner_pairs, grid, dim3(64), sm, st, T, rec, at, planes, L, P.Lp, P.n_groups, P.n_batches, partial,
+                     err);
+  return hipGetLastError();
+}
+
+hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t* Adiag, uint32_t L,
+                        const InnerPlan& P, double2* partial, uint64_t* work, double2* overlap,
+                        double* eta, double* eta_sum, uint32_t* err, hipStream_t st) {
+  const uint32_t n = T.n;
+  hipError_t e;
+  if ((e = launch_quad_prep(T, P.quad, work, st)) != hipSuccess) return e;
+  if ((e = launch_quad_equatorial(Aoff, Adiag, n, L, P.quad, work, st)) != hipSuccess) return e;
+  if ((e = launch_quad_pairs(T, L, P.quad, work, partial, st)) != hipSuccess) return e;
+  if (P.wide && (e = launch_wide(T, Aoff, Adiag, L, P, partial + (size_t)P.quad.rows * L, work + P.quad.words, err,
+                                 st)) != hipSuccess)
+    return e;
+  const uint32_t rows = P.quad.rows + (P.wide ? P.n_groups : 0u);
+  hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, rows, L, n, overlap, eta);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_eta_sum, dim3(1), dim3(256), 0, st, eta, L, eta_sum);

@@ -24,7 +24,10 @@
 //   * Z(E) by the lift of Eq. (Q) and pair elimination (Eqs. (identity), (eq5)).
 // The paper states the O(n^3) cost and defers this method to earlier work.
 //
-// Mapping.  A prologue writes a record per term (one wave per term, lane =
+// Mapping.  From a few bras on, and for forms of at most kQuadMaxVars variables, the
+// bit-sliced kernels take the pairs, a bra's equations as further variables (n = 40,
+// chi = 2^16, 256 bras: 4.4 ms, one wave per pair 26.6).  Below and beyond: a
+// prologue writes a record per term (one wave per term, lane =
 // row): the columns and rows of G, the columns of F, the rows of Bs and a few
 // words.  The pair kernel runs one wave per (bra state, group of ket terms),
 // lane i holding row or variable i, so every step is O(1) or O(n) wave-wide
@@ -39,6 +42,13 @@ namespace chsim {
 namespace {
 
 constexpr int kCHWaves = 4;
+// Bra states from which the bit-sliced kernels take over: their cost is that of 128
+// states, 2.0 (n = 20), 4.5 (40) and 8 (46) times as much for forms of up to 27, 44
+// and 59 variables, where a wave per pair costs its share per bra (16 bras: n = 20,
+// chi = 3000: 909 µs and 215; n = 40, chi = 20000: 1808 and 991; n = 46, chi = 30000:
+// 3153 and 3479, with 24 bras 4106 and 3506).
+constexpr uint32_t sliced_min_bras(uint32_t n) { return n <= 28u ? 8u : n <= 44u ? 12u : 20u; }
+constexpr uint32_t kSlicedSlots = 32;  // constraints held per bra; more go to the pair kernel
 
 __host__ __device__ constexpr uint32_t chrec_words(uint32_t n) { return 6u * n + 6u; }
 
@@ -211,7 +221,7 @@ __device__ __forceinline__ LiftOut lift_eliminate(Word S, Word kap, Word lam, Wo
 __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
     const uint64_t* __restrict__ rec_k, const double2* __restrict__ b_k, uint64_t chi_k,
     const uint64_t* __restrict__ rec_b, uint32_t L, uint32_t n, uint32_t groups, uint32_t bra_blocks,
-    double2* __restrict__ partial, uint32_t* __restrict__ err) {
+    const uint32_t* __restrict__ stat, uint32_t slots, double2* __restrict__ partial, uint32_t* __restrict__ err) {
   const uint32_t lane = threadIdx.x & 63u;
   uint32_t group, bblock;
   if (groups % 8u == 0u) {
@@ -224,6 +234,12 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   }
   const uint32_t l = bblock * kCHWaves + uniform32(threadIdx.x >> 6);
   if (l >= L) return;  // whole waves
+  // Kets whose form fits the bit-sliced kernels are theirs.
+  const uint32_t nw = !stat || stat[2] > slots ? 1u << 20 : stat[2];
+  if (stat && stat[0] + nw <= kQuadMaxVars) {
+    if (lane == 0u) partial[(uint64_t)group * L + l] = make_double2(0.0, 0.0);
+    return;
+  }
   const uint32_t R = chrec_words(n);
   const bool act = lane < n;
   const uint64_t lb = 1ull << lane;
@@ -274,6 +290,7 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   uint32_t bad = 0;
   for (uint64_t a = group; a < chi_k; a += groups) {
     const uint64_t* rk = rec_k + a * R;
+    if (stat && (uint32_t)__popcll(uniform64(rk[6u * n + 4u])) + nw <= kQuadMaxVars) continue;
     const uint64_t colGk = act ? rk[lane] : 0ull;
     const uint64_t Growk = act ? rk[n + lane] : 0ull;
     const uint64_t Bsk = act ? rk[3u * n + lane] : 0ull;
@@ -497,7 +514,7 @@ hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_
   return hipGetLastError();
 }
 
-uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
+static uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
   // About 2^17 waves in all, at least one ket term per group, a multiple of
   // 8 groups when there are 8 or more (the XCD-aware block order).
   const uint64_t want = std::max<uint64_t>(1, (uint64_t)(1u << 17) / std::max<uint32_t>(L, 1u));
@@ -505,21 +522,41 @@ uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
   return (uint32_t)(g >= 8 ? g & ~7ull : g);
 }
 
-hipError_t launch_inner_ch(const uint64_t* rec_k, const double2* b_k, uint64_t chi_k, const uint64_t* rec_b,
-                           const double2* b_bra, uint32_t L, uint32_t n, uint32_t groups, double2* partial,
-                           double2* overlap, double2* total, uint32_t* err, hipStream_t st) {
-  const uint32_t bra_blocks = (L + kCHWaves - 1) / kCHWaves;
-  const uint64_t blocks = (uint64_t)bra_blocks * groups;
-  if (blocks == 0) return hipSuccess;
-  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_inner_ch_pairs, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, rec_k, b_k, chi_k, rec_b,
-                     L, n, groups, bra_blocks, partial, err);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_inner_ch_reduce, dim3((L + kRedX - 1u) / kRedX), dim3(256), 0, st, partial, groups, L, overlap);
+InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L) {
+  InnerChPlan P{};
+  P.sliced = L >= sliced_min_bras(n);
+  if (P.sliced) P.quad = quad_plan(n, chi_k, L, std::min(n, kSlicedSlots));
+  P.pairs = !P.sliced || 2u * n > kQuadMaxVars;
+  P.groups = P.pairs ? inner_ch_groups(chi_k, L) : 0u;
+  P.partial_elems = (size_t)(P.quad.rows + P.groups) * L;
+  return P;
+}
+
+hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, const uint64_t* rec_k,
+                           const uint64_t* rec_b, uint64_t* work, double2* partial, double2* overlap, double2* total,
+                           uint32_t* err, hipStream_t st) {
+  const uint32_t n = K.n, L = (uint32_t)Tb.chi;
+  hipError_t e;
+  if (P.sliced) {
+    if ((e = launch_quad_prep(K, P.quad, work, st)) != hipSuccess) return e;
+    if ((e = launch_quad_bras(Tb, rec_b, chrec_words(n), L, P.quad, work, st)) != hipSuccess) return e;
+    if ((e = launch_quad_pairs(K, L, P.quad, work, partial, st)) != hipSuccess) return e;
+  }
+  if (P.pairs) {
+    const uint32_t bra_blocks = (L + kCHWaves - 1) / kCHWaves;
+    const uint64_t blocks = (uint64_t)bra_blocks * P.groups;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_inner_ch_pairs, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, rec_k, K.b, K.chi, rec_b, L,
+                       n, P.groups, bra_blocks, P.sliced ? quad_stat(P.quad, work) : nullptr, P.quad.slots,
+                       partial + (size_t)P.quad.rows * L, err);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_inner_ch_reduce, dim3((L + kRedX - 1u) / kRedX), dim3(256), 0, st, partial,
+                     P.quad.rows + P.groups, L, overlap);
   e = hipGetLastError();
   if (e != hipSuccess || !total) return e;
-  hipLaunchKernelGGL(k_inner_ch_total, dim3(1), dim3(256), 0, st, overlap, b_bra, L, total);
+  hipLaunchKernelGGL(k_inner_ch_total, dim3(1), dim3(256), 0, st, overlap, Tb.b, L, total);
   return hipGetLastError();
 }
 

@@ -285,10 +285,32 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
                            uint32_t max_steps, bool fp32c, const uint64_t* prefix_d, uint32_t n_inst,
                            uint64_t total_x, hipStream_t st);
 
+// Pairs of a term and a state by bit-sliced elimination (quad_pairs.hip), for
+// forms of at most kQuadMaxVars variables (|v| of the term plus the states'
+// constraints, of which a batch holds `slots`): records of the terms, slices of the
+// states, counts (max |v|, 64 - min |v|, max constraints) in `words` 8-byte words,
+// and `rows` rows of L partial sums.
+constexpr uint32_t kQuadMaxVars = 59;
+struct QuadPlan {
+  uint32_t n_batches, slots, ne1, rows;
+  size_t rec_words, slice_words, words;
+};
+QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots);
+uint32_t* quad_stat(const QuadPlan& P, uint64_t* work);
+hipError_t launch_quad_prep(const TermsView& T, const QuadPlan& P, uint64_t* work, hipStream_t st);
+hipError_t launch_quad_equatorial(const uint64_t* Aoff, const uint8_t* Adiag, uint32_t n, uint32_t L,
+                                  const QuadPlan& P, uint64_t* work, hipStream_t st);
+hipError_t launch_quad_bras(const TermsView& Tb, const uint64_t* chrec, uint32_t chrec_words, uint32_t L,
+                            const QuadPlan& P, uint64_t* work, hipStream_t st);
+hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, uint64_t* work, double2* partial,
+                             hipStream_t st);
+
 // Inner products with equatorial states: L states in batches of 64 (Lp =
 // L rounded up), partial sums per term group, and a device workspace of
 // work_words 8-byte words (per-term records and A rearranged by state).
 struct InnerPlan {
+  QuadPlan quad;
+  bool wide;  // terms with more variables than the bit-sliced kernels take are possible
   uint32_t Lp, n_batches, n_groups;
   size_t partial_elems, work_words;
 };
@@ -304,10 +326,17 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
 // and no free index for the Z_2 lift.
 size_t inner_ch_record_words(uint32_t n, uint64_t chi);
 hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_t st);
-uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L);
-hipError_t launch_inner_ch(const uint64_t* rec_k, const double2* b_k, uint64_t chi_k, const uint64_t* rec_b,
-                           const double2* b_bra, uint32_t L, uint32_t n, uint32_t groups, double2* partial,
-                           double2* overlap, double2* total, uint32_t* err, hipStream_t st);
+struct InnerChPlan {
+  QuadPlan quad;
+  bool sliced, pairs;  // bit-sliced kernels; one wave per pair (few bras, or forms too large for the others)
+  uint32_t groups;
+  size_t partial_elems;
+};
+InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L);
+// rec_k is read by the pair kernel only (plan.pairs).
+hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, const uint64_t* rec_k,
+                           const uint64_t* rec_b, uint64_t* work, double2* partial, double2* overlap, double2* total,
+                           uint32_t* err, hipStream_t st);
 
 // Metropolis.
 hipError_t launch_metro_init(const TermsView& T, MetroView& Mv, hipStream_t st);
