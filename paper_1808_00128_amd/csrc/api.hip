@@ -2375,7 +2375,7 @@ chsim_status chsim_mlp_create(chsim_ctx* ctx, uint32_t n, uint32_t hidden, uint3
   *out = nullptr;
   if (!ctx) return fail(CHSIM_EINVAL, "null context");
   if (n < 1 || n > 64) return fail(CHSIM_EINVAL, "n = %u outside [1, 64]", n);
-  if (hidden == 0 || hidden % 16 || hidden > 1024) return fail(CHSIM_EINVAL, "hidden = %u", hidden);
+  if (hidden == 0 || hidden % 16 || hidden > kMaxHidden) return fail(CHSIM_EINVAL, "hidden = %u", hidden);
   if (max_batch == 0) return fail(CHSIM_EINVAL, "max_batch = 0");
   if (!params) return fail(CHSIM_EINVAL, "null parameters");
   HIP_TRY(hipSetDevice(ctx->device));
@@ -2388,10 +2388,10 @@ chsim_status chsim_mlp_create(chsim_ctx* ctx, uint32_t n, uint32_t hidden, uint3
   const uint64_t cnt = d.L.count();
   const size_t B = max_batch, H = hidden;
   d.part_cap = (uint64_t)1 << 19;
-  bool ok = mlp_alloc(m, &d.part, d.part_cap) == hipSuccess && mlp_alloc(m, &d.p, cnt) == hipSuccess && mlp_alloc(m, &d.grad, cnt) == hipSuccess &&
+  bool ok = mlp_alloc(m, &d.part, mlp_part_floats(d.part_cap)) == hipSuccess && mlp_alloc(m, &d.p, cnt) == hipSuccess && mlp_alloc(m, &d.grad, cnt) == hipSuccess &&
             mlp_alloc(m, &d.adam_m, cnt) == hipSuccess && mlp_alloc(m, &d.adam_v, cnt) == hipSuccess &&
             mlp_alloc(m, &d.wb, d.L.wb_count()) == hipSuccess &&
-            mlp_alloc(m, &d.a0, B * n) == hipSuccess && mlp_alloc(m, &d.a1, B * H) == hipSuccess &&
+            mlp_alloc(m, &d.a1, B * H) == hipSuccess &&
             mlp_alloc(m, &d.a2, B * H) == hipSuccess && mlp_alloc(m, &d.z1, B * H) == hipSuccess &&
             mlp_alloc(m, &d.z2, B * H) == hipSuccess && mlp_alloc(m, &d.logits, B * n) == hipSuccess &&
             mlp_alloc(m, &d.gf, B * n) == hipSuccess && mlp_alloc(m, &d.dz1, B * H) == hipSuccess &&
@@ -2480,9 +2480,7 @@ chsim_status chsim_mlp_loss_grad(chsim_mlp* mlp, const uint64_t* x, const uint64
   if (st) return st;
   st = stage_in(mlp->tin, target, batch, false, s, &td);
   if (st) return st;
-  double zero = 0.0;
-  HIP_TRY(hipMemcpyAsync(mlp->loss.p, &zero, sizeof(double), hipMemcpyHostToDevice, s));
-  HIP_TRY(mlp_loss_grad(d, xd, td, batch, mlp->loss.p, s));
+  HIP_TRY(mlp_loss_grad(d, xd, td, batch, mlp->loss.p, true, false, 0.f, s));
   double lsum = 0.0;
   HIP_TRY(hipMemcpyAsync(&lsum, mlp->loss.p, sizeof(double), hipMemcpyDeviceToHost, s));
   if (grads) HIP_TRY(hipMemcpyAsync(grads, d.grad, d.L.count() * sizeof(float), hipMemcpyDeviceToHost, s));
@@ -2507,12 +2505,9 @@ chsim_status chsim_mlp_train(chsim_mlp* mlp, const uint64_t* x, const uint64_t* 
   st = stage_in(mlp->tin, target, count, dev, s, &td);
   if (st) return st;
   for (uint32_t e = 0; e < epochs; ++e) {
-    double zero = 0.0;
-    HIP_TRY(hipMemcpyAsync(mlp->loss.p, &zero, sizeof(double), hipMemcpyHostToDevice, s));
     for (uint64_t b0 = 0; b0 < count; b0 += batch) {
       const uint32_t B = (uint32_t)std::min<uint64_t>(batch, count - b0);
-      HIP_TRY(mlp_loss_grad(d, xd + b0, td + b0, B, mlp->loss.p, s));
-      HIP_TRY(mlp_adam(d, lr, s));
+      HIP_TRY(mlp_loss_grad(d, xd + b0, td + b0, B, mlp->loss.p, b0 == 0, true, lr, s));
     }
     if (epoch_loss) {
       double lsum = 0.0;

@@ -52,6 +52,8 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 //   EPI_BIAS_RELU: z = acc + bias[j]; Cf = z; Cb = bf16(max(z, 0)).
 //   EPI_BIAS: Cf = acc + bias[j]  (no activation; logits).
 //   EPI_MASK: v = acc * (mask[i][j] > 0); Cf = v; Cb = bf16(v).
+//   EPI_BCE: l = acc + bias[j]; Cf = l, and the loss and its gradient (bce_value).
+// An operand can be the features s_j = 1 - 2 x_j of the bits of x (xa, xb).
 //
 // 32 x 32 output tile per 256-thread workgroup (2 x 2 waves, one 16 x 16
 // MFMA tile each), K staged 64 at a time through LDS (four MFMAs per wave per
@@ -62,7 +64,7 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 // sums in a fixed order before the epilogue, so results do not depend on
 // scheduling.
 // ---------------------------------------------------------------------------
-enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS = 2, EPI_MASK = 3 };
+enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS = 2, EPI_MASK = 3, EPI_BCE = 4 };
 
 // Small batches (inference in the chain, up to kFusedMaxBatch rows) take one
 // fused kernel for the whole network instead of features + three products.
@@ -84,8 +86,30 @@ struct GemmArgs {
   uint16_t* Cb;       // may be null
   int ldc;
   int kc;             // K extent of one split (multiple of kGK)
-  float* part;        // [splits][M][N] partial sums when gridDim.z > 1
+  float* part;        // [splits][M][N] partial sums when split
+  const uint64_t* xa; // A(i, k) = feature k of x[i], if not null
+  const uint64_t* xb; // B(k, j) = feature j of x[k], if not null
+  // EPI_BCE
+  const uint64_t* t;
+  float* gf;
+  uint16_t* gb;
+  double* loss;
+  double* clear;      // set to zero, if not null (a loss that a later product adds to)
 };
+
+// s_j = 1 - 2 x_j as BF16.
+__device__ __forceinline__ uint16_t feature(uint64_t x, int j) {
+  return ((x >> j) & 1ull) ? (uint16_t)0xBF80 /* -1 */ : (uint16_t)0x3F80;
+}
+
+// Loss term softplus(l) - t l of one logit; g = (sigmoid(l) - t) / (B n).
+__device__ __forceinline__ double bce_value(float l, bool tb, uint32_t count, float& gv) {
+  const float tv = tb ? 1.f : 0.f;
+  const float sg = 1.f / (1.f + expf(-l));
+  gv = (sg - tv) / (float)count;
+  const double ld = (double)l;
+  return (ld > 0 ? ld + log1p(exp(-ld)) : log1p(exp(ld))) - (double)tv * ld;
+}
 
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, int row, int col, float v) {
   const int64_t o = (int64_t)row * g.ldc + col;
@@ -128,13 +152,17 @@ __device__ __forceinline__ void stage_index(int q, bool k_fast, int& i, int& k) 
 
 __device__ __forceinline__ void stage_load(const uint16_t* __restrict__ P, int64_t s_row, int64_t s_k,
                                            int rows, int r0, int k0, int kend, bool k_fast,
-                                           uint16_t (&v)[8]) {
+                                           const uint64_t* __restrict__ x, bool x_by_k, uint16_t (&v)[8]) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     int i, k;
     stage_index(q, k_fast, i, k);
     const int gi = r0 + i, gk = k0 + k;
-    v[q] = (gi < rows && gk < kend) ? P[(int64_t)gi * s_row + (int64_t)gk * s_k] : (uint16_t)0;
+    const bool in = gi < rows && gk < kend;
+    if (x)
+      v[q] = in ? (x_by_k ? feature(x[gk], gi) : feature(x[gi], gk)) : (uint16_t)0;
+    else
+      v[q] = in ? P[(int64_t)gi * s_row + (int64_t)gk * s_k] : (uint16_t)0;
   }
 }
 
@@ -147,18 +175,32 @@ __device__ __forceinline__ void stage_store(uint16_t (*S)[kGRow], bool k_fast, c
   }
 }
 
-__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
+// Add the 256 threads' loss terms to *loss.
+__device__ __forceinline__ void block_loss(double lv, double* loss) {
+  __shared__ double part[256];
+  part[threadIdx.x] = lv;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) atomicAdd(loss, part[0]);
+}
+
+// Tile (bx, by) of the product, K split bz of nz (nz > 1: to the partial sums).
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz, int nz) {
   __shared__ __align__(16) uint16_t As[kGT][kGRow];  // [m][k]
   __shared__ __align__(16) uint16_t Bs[kGT][kGRow];  // [n][k]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.x * kGT, n0 = blockIdx.y * kGT;
-  const int kbeg = blockIdx.z * g.kc;
+  const int m0 = bx * kGT, n0 = by * kGT;
+  const int kbeg = bz * g.kc;
   const int kend = min(g.K, kbeg + g.kc);
   const bool a_kf = g.sak == 1, b_kf = g.sbk == 1;
+  if (g.clear && bx + by + bz == 0 && tid == 0) *g.clear = 0.0;
   uint16_t va[8], vb[8];
-  stage_load(g.A, g.sai, g.sak, g.M, m0, kbeg, kend, a_kf, va);
-  stage_load(g.B, g.sbj, g.sbk, g.N, n0, kbeg, kend, b_kf, vb);
+  stage_load(g.A, g.sai, g.sak, g.M, m0, kbeg, kend, a_kf, g.xa, false, va);
+  stage_load(g.B, g.sbj, g.sbk, g.N, n0, kbeg, kend, b_kf, g.xb, true, vb);
   // 16x16x32 operands: lane l holds A[l % 16][k] and B[k][l % 16] for the
   // eight k = 8 (l / 16) .. +7 of each 32-wide step (the same k for both, so
   // the contraction does not depend on their order inside the instruction);
@@ -171,8 +213,8 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
     stage_store(Bs, b_kf, vb);
     __syncthreads();
     if (k0 + kGK < kend) {
-      stage_load(g.A, g.sai, g.sak, g.M, m0, k0 + kGK, kend, a_kf, va);
-      stage_load(g.B, g.sbj, g.sbk, g.N, n0, k0 + kGK, kend, b_kf, vb);
+      stage_load(g.A, g.sai, g.sak, g.M, m0, k0 + kGK, kend, a_kf, g.xa, false, va);
+      stage_load(g.B, g.sbj, g.sbk, g.N, n0, k0 + kGK, kend, b_kf, g.xb, true, vb);
     }
 #pragma unroll
     for (int kk = 0; kk < kGK; kk += 32) {
@@ -182,15 +224,36 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
     }
   }
   const int col = n0 + wn * 16 + (lane & 15);
+  if (g.epi == EPI_BCE) {
+    double lv = 0.0;
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm * 16 + (lane >> 4) * 4 + r;
+      if (row >= g.M || col >= g.N) continue;
+      const int64_t o = (int64_t)row * g.ldc + col;
+      const float l = acc[r] + g.bias[col];
+      float gv;
+      lv += bce_value(l, (g.t[row] >> col) & 1ull, (uint32_t)(g.M * g.N), gv);
+      g.Cf[o] = l;
+      g.gf[o] = gv;
+      g.gb[o] = f2bf(gv);
+    }
+    block_loss(lv, g.loss);
+    return;
+  }
   for (int r = 0; r < 4; ++r) {
     const int row = m0 + wm * 16 + (lane >> 4) * 4 + r;
     if (row >= g.M || col >= g.N) continue;
-    if (gridDim.z == 1)
+    if (nz == 1)
       gemm_epilogue(g, row, col, acc[r]);
     else
-      g.part[((int64_t)blockIdx.z * g.M + row) * g.N + col] = acc[r];
+      g.part[((int64_t)bz * g.M + row) * g.N + col] = acc[r];
   }
 }
+
+__global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
+  gemm_tile(g, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
+}
+
 
 // Sum of the K-split partials in split order, then the epilogue.
 __global__ __launch_bounds__(256) void k_gemm_splitk(GemmArgs g, int splits) {
@@ -202,7 +265,8 @@ __global__ __launch_bounds__(256) void k_gemm_splitk(GemmArgs g, int splits) {
   gemm_epilogue(g, (int)(e / g.N), (int)(e % g.N), v);
 }
 
-static hipError_t gemm(GemmArgs g, const MLPDev& d, hipStream_t st) {
+// K splits of a product, and g.kc for them.
+static int gemm_splits(GemmArgs& g, const MLPDev& d) {
   const int bm = (g.M + kGT - 1) / kGT, bn = (g.N + kGT - 1) / kGT;
   const int blocks = bm * bn;
   const int n_kt = (g.K + kGK - 1) / kGK;
@@ -213,7 +277,12 @@ static hipError_t gemm(GemmArgs g, const MLPDev& d, hipStream_t st) {
   }
   const int kt_per = (n_kt + splits - 1) / splits;
   g.kc = kt_per * kGK;
-  splits = (n_kt + kt_per - 1) / kt_per;
+  return (n_kt + kt_per - 1) / kt_per;
+}
+
+static hipError_t gemm(GemmArgs g, const MLPDev& d, hipStream_t st) {
+  const int bm = (g.M + kGT - 1) / kGT, bn = (g.N + kGT - 1) / kGT;
+  const int splits = gemm_splits(g, d);
   g.part = d.part;
   hipLaunchKernelGGL(k_gemm_bf16, dim3(bm, bn, splits), dim3(256), 0, st, g);
   if (splits > 1) {
@@ -223,88 +292,99 @@ static hipError_t gemm(GemmArgs g, const MLPDev& d, hipStream_t st) {
   return hipGetLastError();
 }
 
-// s_j = 1 - 2 x_j as BF16, [B][n].
-__global__ __launch_bounds__(256) void k_features(const uint64_t* __restrict__ x, uint32_t B, uint32_t n,
-                                                  uint16_t* __restrict__ a0) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * n) return;
-  const uint32_t b = i / n, j = i % n;
-  a0[i] = ((x[b] >> j) & 1ull) ? (uint16_t)0xBF80 /* -1 */ : (uint16_t)0x3F80 /* +1 */;
-}
-
-// g = (sigmoid(l) - t) / (B n); loss partial sums softplus(l) - t l.
+// Loss and gradient of logits that are already there (the fused forward pass).
 __global__ __launch_bounds__(256) void k_bce_grad(const float* __restrict__ logits,
                                                   const uint64_t* __restrict__ t, uint32_t B,
                                                   uint32_t n, float* __restrict__ g,
                                                   uint16_t* __restrict__ gb,
                                                   double* __restrict__ loss_acc) {
-  __shared__ double part[256];
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   double lv = 0.0;
   if (i < B * n) {
     const uint32_t b = i / n, j = i % n;
-    const float l = logits[i];
-    const float tv = ((t[b] >> j) & 1ull) ? 1.f : 0.f;
-    const float sg = 1.f / (1.f + expf(-l));
-    const float gv = (sg - tv) / (float)(B * n);
+    float gv;
+    lv = bce_value(logits[i], (t[b] >> j) & 1ull, B * n, gv);
     g[i] = gv;
     gb[i] = f2bf(gv);
-    const double ld = (double)l;
-    lv = (ld > 0 ? ld + log1p(exp(-ld)) : log1p(exp(ld))) - (double)tv * ld;
   }
-  part[threadIdx.x] = lv;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicAdd(loss_acc, part[0]);
+  block_loss(lv, loss_acc);
 }
 
-// db[j] = sum_b d[b][j] (FP32, fixed order) in two passes: split y of
-// k_colsum_part sums rows [y R, (y + 1) R) with 4 row groups of 64 columns per
-// workgroup; k_colsum_fin adds the splits in order.
-__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ d, uint32_t B, uint32_t N,
-                                                     uint32_t R, float* __restrict__ part) {
+// The parameters' gradients once the layers' input gradients are there: the three
+// weight products (K = batch, most of them split over K) and the three bias sums
+// db[j] = sum_b d[b][j], all in one launch; then one launch that adds the splits in
+// order and, in training, takes the Adam step and refreshes the BF16 weights.
+// Neither depends on the other five products and sums, each of which is too small
+// to fill the chip: 15 launches of 4-6 µs each before (n = 50, H = 256, 1024 rows:
+// loss and gradients of host arrays in 225 µs, 168 now).
+struct GradGroup {
+  GemmArgs g[3];      // W3, W2, W1
+  const float* d[3];  // sources of b3, b2, b1
+  uint32_t N[3];
+  float* cpart[3];    // [csplits][N]
+  uint32_t B, R, csplits;
+  int splits[3];
+  uint32_t first[7];  // workgroups before each product and sum
+};
+
+// Rows [y R, (y + 1) R) of 64 columns, 4 row groups.
+__device__ __forceinline__ void colsum_tile(const float* __restrict__ d, uint32_t B, uint32_t N, uint32_t R,
+                                            uint32_t bx, uint32_t by, float* __restrict__ part) {
   __shared__ float red[4][64];
   const uint32_t c = threadIdx.x & 63u, grp = threadIdx.x >> 6;
-  const uint32_t j = blockIdx.x * 64u + c;
-  const uint32_t b0 = blockIdx.y * R, b1 = min(B, b0 + R);
+  const uint32_t j = bx * 64u + c;
+  const uint32_t b0 = by * R, b1 = min(B, b0 + R);
   float s = 0.f;
   if (j < N)
     for (uint32_t b = b0 + grp; b < b1; b += 4u) s += d[(uint64_t)b * N + j];
   red[grp][c] = s;
   __syncthreads();
-  if (grp == 0 && j < N) part[(uint64_t)blockIdx.y * N + j] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+  if (grp == 0 && j < N) part[(uint64_t)by * N + j] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
-__global__ __launch_bounds__(256) void k_colsum_fin(const float* __restrict__ part, uint32_t splits,
-                                                    uint32_t N, float* __restrict__ db) {
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  float s = 0.f;
-  for (uint32_t z = 0; z < splits; ++z) s += part[(uint64_t)z * N + j];
-  db[j] = s;
+__global__ __launch_bounds__(256) void k_grad_parts(GradGroup G) {
+  uint32_t b = blockIdx.x;
+  int k = 0;
+  while (k < 5 && b >= G.first[k + 1]) ++k;
+  b -= G.first[k];
+  if (k < 3) {
+    const GemmArgs& g = G.g[k];
+    const uint32_t bm = (uint32_t)(g.M + kGT - 1) / kGT, bn = (uint32_t)(g.N + kGT - 1) / kGT;
+    gemm_tile(g, (int)(b % bm), (int)(b / bm % bn), (int)(b / (bm * bn)), G.splits[k]);
+  } else {
+    const uint32_t bx = (G.N[k - 3] + 63u) / 64u;
+    colsum_tile(G.d[k - 3], G.B, G.N[k - 3], G.R, b % bx, b / bx, G.cpart[k - 3]);
+  }
 }
 
-static hipError_t colsum(const MLPDev& d, const float* src, uint32_t B, uint32_t N, float* db,
-                         hipStream_t st) {
-  uint32_t splits = std::min<uint32_t>(32u, (B + 63u) / 64u);
-  while (splits > 1 && (uint64_t)splits * N > d.part_cap) --splits;
-  const uint32_t R = (B + splits - 1) / splits;
-  hipLaunchKernelGGL(k_colsum_part, dim3((N + 63) / 64, splits), dim3(256), 0, st, src, B, N, R, d.part);
-  hipLaunchKernelGGL(k_colsum_fin, dim3((N + 255) / 256), dim3(256), 0, st, d.part, splits, N, db);
-  return hipGetLastError();
-}
-
-// Adam on the packed FP32 parameters, then refresh the BF16 weight copies.
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float* __restrict__ g,
-                                              float* __restrict__ m, float* __restrict__ v,
-                                              uint64_t count, float lr, float c1, float c2,
-                                              MLPLayout L, uint16_t* __restrict__ wb) {
+__global__ __launch_bounds__(256) void k_grad_finish(GradGroup G, MLPLayout L, float* __restrict__ grad, bool adam,
+                                                     float* __restrict__ p, float* __restrict__ m,
+                                                     float* __restrict__ v, float lr, float c1, float c2,
+                                                     uint16_t* __restrict__ wb) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float gi = g[i];
+  if (i >= L.count()) return;
+  // The parameter's layer k (W3 b3, W2 b2, W1 b1) and its place there.
+  const uint64_t w0[3] = {L.off_W3(), L.off_W2(), L.off_W1()}, b0[3] = {L.off_b3(), L.off_b2(), L.off_b1()};
+  const int k = i >= w0[0] ? 0 : i >= w0[1] ? 1 : 2;
+  const uint64_t wk = k == 0 ? w0[0] : k == 1 ? w0[1] : w0[2], bk = k == 0 ? b0[0] : k == 1 ? b0[1] : b0[2];
+  float gi;
+  if (i >= bk) {
+    const uint32_t j = (uint32_t)(i - bk), N = k == 0 ? G.N[0] : k == 1 ? G.N[1] : G.N[2];
+    const float* part = k == 0 ? G.cpart[0] : k == 1 ? G.cpart[1] : G.cpart[2];
+    gi = 0.f;
+    for (uint32_t z = 0; z < G.csplits; ++z) gi += part[(uint64_t)z * N + j];
+  } else {
+    const int splits = k == 0 ? G.splits[0] : k == 1 ? G.splits[1] : G.splits[2];
+    const float* part = k == 0 ? G.g[0].part : k == 1 ? G.g[1].part : G.g[2].part;
+    if (splits == 1) {
+      gi = grad[i];
+    } else {
+      gi = 0.f;
+      for (int z = 0; z < splits; ++z) gi += part[(uint64_t)z * (bk - wk) + (i - wk)];
+    }
+  }
+  grad[i] = gi;
+  if (!adam) return;
   const float mi = 0.9f * m[i] + 0.1f * gi;
   const float vi = 0.999f * v[i] + 0.001f * gi * gi;
   m[i] = mi;
@@ -334,19 +414,24 @@ hipError_t mlp_refresh(MLPDev& d, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Forward for `B` inputs already expanded into d.a0.
-static hipError_t forward_a0(MLPDev& d, uint32_t B, float* logits, hipStream_t st) {
+// Forward in three products; with bce also the loss and its gradient (in the
+// last product's epilogue unless that is split over K).
+static hipError_t forward_products(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, const GemmArgs* bce,
+                                   bool& bce_done, double* clear, hipStream_t st) {
   const MLPLayout& L = d.L;
   const int n = (int)L.n, H = (int)L.H;
   GemmArgs g{};
-  // z1 = a0 W1^T + b1, a1 = bf16(relu(z1))
-  g.A = d.a0; g.sai = n; g.sak = 1;
+  // z1 = a0 W1^T + b1, a1 = bf16(relu(z1)), a0 the features
+  g.xa = x; g.sai = n; g.sak = 1;
+  g.clear = clear;
   g.B = d.wb + L.wb_W1(); g.sbk = 1; g.sbj = n;
   g.M = (int)B; g.N = H; g.K = n; g.epi = EPI_BIAS_RELU; g.bias = d.p + L.off_b1();
   g.Cf = d.z1; g.Cb = d.a1; g.ldc = H;
   hipError_t e = gemm(g, d, st);
   if (e != hipSuccess) return e;
   // z2 = a1 W2^T + b2, a2 = bf16(relu(z2))
+  g.xa = nullptr;
+  g.clear = nullptr;
   g.A = d.a1; g.sai = H; g.sak = 1;
   g.B = d.wb + L.wb_W2(); g.sbk = 1; g.sbj = H;
   g.N = H; g.K = H; g.bias = d.p + L.off_b2(); g.Cf = d.z2; g.Cb = d.a2; g.ldc = H;
@@ -356,65 +441,97 @@ static hipError_t forward_a0(MLPDev& d, uint32_t B, float* logits, hipStream_t s
   g.B = d.wb + L.wb_W3(); g.sbk = 1; g.sbj = H;
   g.N = n; g.K = H; g.epi = EPI_BIAS; g.bias = d.p + L.off_b3(); g.Cf = logits; g.Cb = nullptr;
   g.ldc = n;
+  if (bce && gemm_splits(g, d) == 1) {
+    g.epi = EPI_BCE; g.t = bce->t; g.gf = bce->gf; g.gb = bce->gb; g.loss = bce->loss;
+    bce_done = true;
+  }
   return gemm(g, d, st);
 }
 
 static bool fused_ok(const MLPDev& d);
-static hipError_t fused_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, hipStream_t st);
+static hipError_t fused_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, double* clear, hipStream_t st);
 
 hipError_t mlp_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, hipStream_t st) {
-  if (fused_ok(d) && B <= kFusedMaxBatch) return fused_forward(d, x, B, logits, st);
-  const uint32_t cnt = B * d.L.n;
-  hipLaunchKernelGGL(k_features, dim3((cnt + 255) / 256), dim3(256), 0, st, x, B, d.L.n, d.a0);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return forward_a0(d, B, logits, st);
+  if (fused_ok(d) && B <= kFusedMaxBatch) return fused_forward(d, x, B, logits, nullptr, st);
+  bool done = false;
+  return forward_products(d, x, B, logits, nullptr, done, nullptr, st);
 }
 
 hipError_t mlp_loss_grad(MLPDev& d, const uint64_t* x, const uint64_t* t, uint32_t B,
-                         double* loss_acc, hipStream_t st) {
+                         double* loss_acc, bool clear_loss, bool adam, float lr, hipStream_t st) {
   const MLPLayout& L = d.L;
   const int n = (int)L.n, H = (int)L.H;
-  hipError_t e = mlp_forward(d, x, B, d.logits, st);
+  hipError_t e;
+  bool done = false;
+  if (fused_ok(d) && B <= kFusedMaxBatch) {
+    e = fused_forward(d, x, B, d.logits, clear_loss ? loss_acc : nullptr, st);
+  } else {
+    GemmArgs bce{};
+    bce.t = t; bce.gf = d.gf; bce.gb = d.gb; bce.loss = loss_acc;
+    e = forward_products(d, x, B, d.logits, &bce, done, clear_loss ? loss_acc : nullptr, st);
+  }
   if (e != hipSuccess) return e;
-  const uint32_t cnt = B * L.n;
-  hipLaunchKernelGGL(k_bce_grad, dim3((cnt + 255) / 256), dim3(256), 0, st, d.logits, t, B, L.n,
-                     d.gf, d.gb, loss_acc);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (!done) {
+    const uint32_t cnt = B * L.n;
+    hipLaunchKernelGGL(k_bce_grad, dim3((cnt + 255) / 256), dim3(256), 0, st, d.logits, t, B, L.n,
+                       d.gf, d.gb, loss_acc);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   float* G = d.grad;
   GemmArgs g{};
-  // dW3[n][H] = gb^T a2
-  g.A = d.gb; g.sai = 1; g.sak = n; g.B = d.a2; g.sbk = H; g.sbj = 1;
-  g.M = n; g.N = H; g.K = (int)B; g.epi = EPI_STORE; g.Cf = G + L.off_W3(); g.Cb = nullptr; g.ldc = H;
-  if ((e = gemm(g, d, st)) != hipSuccess) return e;
-  if ((e = colsum(d, d.gf, B, (uint32_t)n, G + L.off_b3(), st)) != hipSuccess) return e;
   // dZ2 = (gb W3) * [z2 > 0]
   g.A = d.gb; g.sai = n; g.sak = 1; g.B = d.wb + L.wb_W3(); g.sbk = H; g.sbj = 1;
   g.M = (int)B; g.N = H; g.K = n; g.epi = EPI_MASK; g.mask = d.z2; g.Cf = d.dz2; g.Cb = d.gz2; g.ldc = H;
   if ((e = gemm(g, d, st)) != hipSuccess) return e;
-  // dW2[H][H] = gz2^T a1
-  g.A = d.gz2; g.sai = 1; g.sak = H; g.B = d.a1; g.sbk = H; g.sbj = 1;
-  g.M = H; g.N = H; g.K = (int)B; g.epi = EPI_STORE; g.Cf = G + L.off_W2(); g.Cb = nullptr; g.ldc = H;
-  if ((e = gemm(g, d, st)) != hipSuccess) return e;
-  if ((e = colsum(d, d.dz2, B, (uint32_t)H, G + L.off_b2(), st)) != hipSuccess) return e;
   // dZ1 = (gz2 W2) * [z1 > 0]
   g.A = d.gz2; g.sai = H; g.sak = 1; g.B = d.wb + L.wb_W2(); g.sbk = H; g.sbj = 1;
   g.M = (int)B; g.N = H; g.K = H; g.epi = EPI_MASK; g.mask = d.z1; g.Cf = d.dz1; g.Cb = d.gz1; g.ldc = H;
   if ((e = gemm(g, d, st)) != hipSuccess) return e;
+  GradGroup q{};
+  g = GemmArgs{};
+  g.K = (int)B; g.epi = EPI_STORE;
+  // dW3[n][H] = gb^T a2
+  g.A = d.gb; g.sai = 1; g.sak = n; g.B = d.a2; g.sbk = H; g.sbj = 1;
+  g.M = n; g.N = H; g.Cf = G + L.off_W3(); g.ldc = H;
+  q.g[0] = g;
+  // dW2[H][H] = gz2^T a1
+  g.A = d.gz2; g.sai = 1; g.sak = H; g.B = d.a1; g.sbk = H; g.sbj = 1;
+  g.M = H; g.N = H; g.Cf = G + L.off_W2(); g.ldc = H;
+  q.g[1] = g;
   // dW1[H][n] = gz1^T a0
-  g.A = d.gz1; g.sai = 1; g.sak = H; g.B = d.a0; g.sbk = n; g.sbj = 1;
-  g.M = H; g.N = n; g.K = (int)B; g.epi = EPI_STORE; g.Cf = G + L.off_W1(); g.Cb = nullptr; g.ldc = n;
-  if ((e = gemm(g, d, st)) != hipSuccess) return e;
-  return colsum(d, d.dz1, B, (uint32_t)H, G + L.off_b1(), st);
-}
-
-hipError_t mlp_adam(MLPDev& d, float lr, hipStream_t st) {
-  d.step += 1;
-  const float c1 = 1.f - powf(0.9f, (float)d.step);
-  const float c2 = 1.f - powf(0.999f, (float)d.step);
-  const uint64_t cnt = d.L.count();
-  hipLaunchKernelGGL(k_adam, dim3((uint32_t)((cnt + 255) / 256)), dim3(256), 0, st, d.p, d.grad,
-                     d.adam_m, d.adam_v, cnt, lr, c1, c2, d.L, d.wb);
+  g.A = d.gz1; g.sai = 1; g.sak = H; g.B = nullptr; g.xb = x; g.sbk = n; g.sbj = 1;
+  g.M = H; g.N = n; g.Cf = G + L.off_W1(); g.ldc = n;
+  q.g[2] = g;
+  q.d[0] = d.gf; q.d[1] = d.dz2; q.d[2] = d.dz1;
+  q.N[0] = (uint32_t)n; q.N[1] = q.N[2] = (uint32_t)H;
+  q.B = B;
+  const uint32_t cs = std::min<uint32_t>(kColSplits, (B + 63u) / 64u);
+  q.R = (B + cs - 1u) / cs;
+  q.csplits = cs;
+  uint32_t at = 0;
+  for (int k = 0; k < 3; ++k) {
+    GemmArgs& a = q.g[k];
+    q.splits[k] = gemm_splits(a, d);
+    a.part = d.part + (uint64_t)k * d.part_cap;
+    q.first[k] = at;
+    at += (uint32_t)(((a.M + kGT - 1) / kGT) * ((a.N + kGT - 1) / kGT) * q.splits[k]);
+  }
+  for (int k = 0; k < 3; ++k) {
+    q.cpart[k] = d.part + 3u * d.part_cap + (uint64_t)k * kColSplits * kMaxHidden;
+    q.first[3 + k] = at;
+    at += (q.N[k] + 63u) / 64u * cs;
+  }
+  q.first[6] = at;
+  hipLaunchKernelGGL(k_grad_parts, dim3(at), dim3(256), 0, st, q);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  float c1 = 1.f, c2 = 1.f;
+  if (adam) {
+    d.step += 1;
+    c1 = 1.f - powf(0.9f, (float)d.step);
+    c2 = 1.f - powf(0.999f, (float)d.step);
+  }
+  hipLaunchKernelGGL(k_grad_finish, dim3((uint32_t)((L.count() + 255) / 256)), dim3(256), 0, st, q, L, G, adam, d.p,
+                     d.adam_m, d.adam_v, lr, c1, c2, d.wb);
   return hipGetLastError();
 }
 
@@ -553,7 +670,7 @@ __device__ __forceinline__ void fused_layer(const uint16_t* As, int pa, int K,
 template <bool kDraw>
 __global__ __launch_bounds__(64 * kFWaves) void k_mlp_fused(MLPDev d, const uint64_t* __restrict__ x,
                                                    uint32_t B, float* __restrict__ logits,
-                                                   LearnedView Lv, uint32_t step) {
+                                                   LearnedView Lv, uint32_t step, double* clear) {
   __shared__ __align__(16) uint16_t A0[kFR * kFP0];
   __shared__ __align__(16) uint16_t A1[kFR * kFPH];
   __shared__ __align__(16) uint16_t A2[kFR * kFPH];
@@ -563,6 +680,7 @@ __global__ __launch_bounds__(64 * kFWaves) void k_mlp_fused(MLPDev d, const uint
   const uint32_t r0 = blockIdx.x * kFR;
   const int rows = (int)min((uint32_t)kFR, B - r0);
   const uint32_t tid = threadIdx.x;
+  if (clear && blockIdx.x == 0 && tid == 0) *clear = 0.0;
   if (kDraw) {
     // Wave r draws the mask of row r: lane j decides bit j (the comparisons
     // of draw_mask), one ballot assembles the mask.
@@ -600,9 +718,8 @@ __global__ __launch_bounds__(64 * kFWaves) void k_mlp_fused(MLPDev d, const uint
   for (uint32_t e = tid; e < (uint32_t)(kFR * 64); e += 64u * kFWaves) {
     const int r = (int)(e / 64), k = (int)(e % 64);
     uint16_t f = 0;
-    if (k < n && r < rows) f = ((sx[r] >> k) & 1ull) ? (uint16_t)0xBF80 /* -1 */ : (uint16_t)0x3F80;
+    if (k < n && r < rows) f = feature(sx[r], k);
     A0[r * kFP0 + k] = f;
-    if (!kDraw && k < n && r < rows) d.a0[(int64_t)(r0 + r) * n + k] = f;
   }
   __syncthreads();
   const int64_t o = (int64_t)r0 * H;
@@ -617,10 +734,11 @@ __global__ __launch_bounds__(64 * kFWaves) void k_mlp_fused(MLPDev d, const uint
               nullptr, out, n, rows);
 }
 
-static hipError_t fused_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, hipStream_t st) {
+static hipError_t fused_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, double* clear,
+                                hipStream_t st) {
   if (B == 0) return hipSuccess;
   hipLaunchKernelGGL(k_mlp_fused<false>, dim3((B + kFR - 1) / kFR), dim3(64 * kFWaves), 0, st, d, x, B, logits,
-                     LearnedView{}, 0u);
+                     LearnedView{}, 0u, clear);
   return hipGetLastError();
 }
 
@@ -706,7 +824,7 @@ hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& 
     if (fused) {
       // Masks, proposals and the network at the proposals in one kernel.
       hipLaunchKernelGGL(k_mlp_fused<true>, dim3((Lv.n_chain + kFR - 1) / kFR), dim3(64 * kFWaves), 0, st, d,
-                         nullptr, Lv.n_chain, nullptr, Lv, t);
+                         nullptr, Lv.n_chain, nullptr, Lv, t, (double*)nullptr);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
       hipLaunchKernelGGL(k_learned_mask, dim3((Lv.n_chain + 63) / 64), dim3(64), 0, st, Lv, t);

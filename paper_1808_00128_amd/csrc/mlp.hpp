@@ -43,14 +43,17 @@ struct MLPDev {
   float* adam_v = nullptr;
   uint16_t* wb = nullptr;
   // activations [cap][.]
-  uint16_t *a0 = nullptr, *a1 = nullptr, *a2 = nullptr;
+  uint16_t *a1 = nullptr, *a2 = nullptr;
   float *z1 = nullptr, *z2 = nullptr, *logits = nullptr;
   float *gf = nullptr, *dz1 = nullptr, *dz2 = nullptr;
   uint16_t *gb = nullptr, *gz1 = nullptr, *gz2 = nullptr;
-  // FP32 partial sums of K-split products and column sums
+  // FP32 partial sums of K-split products (three of up to part_cap) and of the
+  // three bias sums (mlp_part_floats in all)
   float* part = nullptr;
   uint64_t part_cap = 0;
 };
+constexpr uint32_t kColSplits = 32, kMaxHidden = 1024;
+constexpr uint64_t mlp_part_floats(uint64_t part_cap) { return 3u * part_cap + 3u * kColSplits * kMaxHidden; }
 
 struct LearnedView {
   uint32_t n, n_chain, n_steps;
@@ -69,9 +72,9 @@ struct LearnedView {
 
 hipError_t mlp_refresh(MLPDev& d, hipStream_t st);
 hipError_t mlp_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, hipStream_t st);
+// Loss sum (added to *loss_acc, cleared first with clear_loss) and gradients; with adam also the Adam step.
 hipError_t mlp_loss_grad(MLPDev& d, const uint64_t* x, const uint64_t* t, uint32_t B,
-                         double* loss_acc, hipStream_t st);
-hipError_t mlp_adam(MLPDev& d, float lr, hipStream_t st);
+                         double* loss_acc, bool clear_loss, bool adam, float lr, hipStream_t st);
 hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& Lv, MLPDev& d,
                                 uint32_t n_steps, hipStream_t st);
 
