@@ -656,9 +656,8 @@ hipError_t launch_amp_mfma_prep(const TermsView& T, uint8_t* rec, uint64_t* cond
   return hipGetLastError();
 }
 
-hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items, uint32_t n_split,
-                           uint32_t max_steps, bool fp32c, const uint64_t* prefix_d, uint32_t n_inst,
-                           uint64_t total_x, hipStream_t st) {
+hipError_t launch_amp_mfma_sums(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items,
+                                uint32_t n_split, uint32_t max_steps, bool fp32c, hipStream_t st) {
   // Two staged tiles (split items: head and values alone, two buffers per
   // wave), a table of zeros and the fixed condition operands; at the start the
   // same memory holds the four waves' feature words (8 S x strings x 4 bytes <=
@@ -682,6 +681,14 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
     else hipLaunchKernelGGL((k_amp_mfma<double, false>), dim3(n_split), dim3(256), sm, st, insts_d, it);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
+  return hipSuccess;
+}
+
+hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items, uint32_t n_split,
+                           uint32_t max_steps, bool fp32c, const uint64_t* prefix_d, uint32_t n_inst,
+                           uint64_t total_x, hipStream_t st) {
+  const hipError_t e = launch_amp_mfma_sums(insts_d, items_d, n_items, n_split, max_steps, fp32c, st);
+  if (e != hipSuccess) return e;
   const uint32_t blocks = (uint32_t)((total_x + kRedX - 1) / kRedX);
   hipLaunchKernelGGL(k_amp_mfma_reduce, dim3(blocks), dim3(256), 0, st, insts_d, prefix_d, n_inst);
   return hipGetLastError();

@@ -150,6 +150,9 @@ struct Instance {
   DevBuf<uint8_t> macc;
   // learned chain
   DevBuf<uint64_t> ly, lmask;
+  DevBuf<uint64_t> lplan;           // plan of the proposals' amplitudes, and the same on the host
+  std::vector<uint64_t> lplan_h;
+  DevBuf<double2> lsums;
   DevBuf<float> logit_x, logit_y;
   DevBuf<double> lumix, lubits;
   DevBuf<uint32_t> lj, lflips;
@@ -195,6 +198,7 @@ struct Instance {
     plan_slot.release(); plan_width.release(); plan_count.release();
     mstate0.release(); mpmask.release(); mx.release(); mtrace.release();
     mpend.release(); mj.release(); mamp.release(); mpartial.release(); mu.release(); macc.release();
+    lplan.release(); lplan_h.clear(); lsums.release();
     ly.release(); lmask.release(); logit_x.release(); logit_y.release(); lumix.release();
     lubits.release(); lj.release(); lflips.release();
   }
@@ -2364,6 +2368,63 @@ hipError_t mlp_alloc(chsim_mlp* m, T** p, size_t count) {
   return e;
 }
 
+// Learned steps take <y|psi> of the proposals from the matrix-core amplitude
+// kernel (n = 50, chi = 2^18, 64 chains: 45 µs per step; the chains' caches, with
+// every row read and each chain's cached words, 103) where its records are there,
+// or the call has steps enough to pay for them (8 x 58 µs against 250 µs).  The
+// kernel's cost is that of 64 strings and grows with n^2; with few chains the rows
+// are read sooner (n = 50, chi = 10^5, 8 chains, per step with the network 43 µs
+// from the caches and 48; n = 12, chi = 4000: 31 and 29).
+constexpr uint32_t kLearnedPrepSteps = 8, kLearnedChains = 16, kLearnedSmallN = 24;
+
+chsim_status plan_learned_amps(Instance& I, uint32_t n_steps, hipStream_t s, LearnedAmps* out, bool* use) {
+  *use = false;
+  if (I.n > kAmpMfmaMaxN || I.mfma_off || !(I.mfma_ready || n_steps >= kLearnedPrepSteps)) return CHSIM_OK;
+  if (I.n_chain < kLearnedChains && I.n > kLearnedSmallN) return CHSIM_OK;
+  chsim_status st = ensure_mfma_prep(I, s);
+  if (st || I.mfma_off) return st;
+  std::vector<AmpItem> items;
+  std::vector<uint32_t> tpr, rows;
+  uint32_t n_split = 0;
+  amp_mfma_plan({AmpRequestPlan{I.n, I.n_chain, I.chi}}, items, &n_split, tpr, rows);
+  if (I.lsums.ensure((size_t)rows[0] * I.n_chain) == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    return CHSIM_OK;
+  }
+  AmpMfmaInst a;
+  std::memset(&a, 0, sizeof a);
+  a.rec = I.mrec.p;
+  a.cond = I.mcond.p;
+  a.x = I.ly.p;
+  a.partial = I.lsums.p;
+  a.n = I.n;
+  a.steps = amp_mfma_steps(I.n);
+  a.tiles = (uint32_t)((I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile);
+  a.n_x = I.n_chain;
+  a.tiles_per_range = tpr[0];
+  a.rows = rows[0];
+  const size_t w_inst = (sizeof a / 8 + 1) & ~(size_t)1, w_items = items.size() * sizeof(AmpItem) / 8;  // items: 16 bytes
+  std::vector<uint64_t> words(w_inst + w_items, 0);
+  std::memcpy(words.data(), &a, sizeof a);
+  std::memcpy(words.data() + w_inst, items.data(), w_items * 8);
+  if (words != I.lplan_h) {
+    I.lplan_h.clear();
+    HIP_TRY(I.lplan.ensure(words.size()));
+    HIP_TRY(hipMemcpyAsync(I.lplan.p, words.data(), words.size() * 8, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    I.lplan_h = std::move(words);
+  }
+  out->inst = reinterpret_cast<const AmpMfmaInst*>(I.lplan.p);
+  out->items = reinterpret_cast<const AmpItem*>(I.lplan.p + w_inst);
+  out->n_items = (uint32_t)items.size();
+  out->n_split = n_split;
+  out->steps = a.steps;
+  out->rows = rows[0];
+  out->sums = I.lsums.p;
+  *use = true;
+  return CHSIM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2596,9 +2657,12 @@ chsim_status chsim_metropolis_step_learned(chsim_ctx* ctx, uint32_t inst, chsim_
       lv.n_flips = I.lflips.p;
     }
   }
+  LearnedAmps amps;
+  bool on_mfma = false;
+  if ((st = plan_learned_amps(I, n_steps, s, &amps, &on_mfma))) return st;
   // The network's output at the current states.
   HIP_TRY(mlp_forward(mlp->d, I.mx.p, I.n_chain, I.logit_x.p, s));
-  HIP_TRY(launch_learned_steps(I.view(), mv, lv, mlp->d, n_steps, s));
+  HIP_TRY(launch_learned_steps(I.view(), mv, lv, mlp->d, on_mfma ? &amps : nullptr, n_steps, s));
   if (!dev) {
     if (x_trace) HIP_TRY(hipMemcpyAsync(x_trace, mv.trace, cnt * 8, hipMemcpyDeviceToHost, s));
     if (accepted) HIP_TRY(hipMemcpyAsync(accepted, mv.accepted, cnt, hipMemcpyDeviceToHost, s));

@@ -281,6 +281,9 @@ hipError_t launch_amp_mfma_prep(const TermsView& T, uint8_t* rec, uint64_t* cond
 // string of each request.
 void amp_mfma_plan(const std::vector<AmpRequestPlan>& reqs, std::vector<AmpItem>& items, uint32_t* n_split,
                    std::vector<uint32_t>& tiles_per_range, std::vector<uint32_t>& rows);
+// The partial sums alone, and with their reduction.
+hipError_t launch_amp_mfma_sums(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items,
+                                uint32_t n_split, uint32_t max_steps, bool fp32c, hipStream_t st);
 hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, uint32_t n_items, uint32_t n_split,
                            uint32_t max_steps, bool fp32c, const uint64_t* prefix_d, uint32_t n_inst,
                            uint64_t total_x, hipStream_t st);

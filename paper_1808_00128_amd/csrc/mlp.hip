@@ -744,13 +744,18 @@ static hipError_t fused_forward(MLPDev& d, const uint64_t* x, uint32_t B, float*
 
 // One thread per term, loop over chains: Q_y = Q_x prod_{j in m} P_j (the
 // factors commute), <y|phi_alpha> from (u', mu'), tile sums per chain.
-__global__ __launch_bounds__(256) void k_learned_accept(MetroView Mv, LearnedView Lv, uint32_t step) {
+// sums: n_sums partial sums of a chain's proposal, `pitch` apart; `collect`: the
+// accepted masks of the call are collected (their products commute and are their
+// own inverses) for the one pass that brings the caches up to date at its end.
+__global__ __launch_bounds__(256) void k_learned_accept(MetroView Mv, LearnedView Lv, uint32_t step,
+                                                        const double2* __restrict__ sums, uint32_t n_sums,
+                                                        uint64_t chain_pitch, uint64_t pitch, bool collect) {
   __shared__ double part_r[256], part_i[256];
   const uint32_t ch = blockIdx.x;
   const uint32_t n = Lv.n;
   double ar = 0.0, ai = 0.0;
-  for (uint32_t t = threadIdx.x; t < Mv.n_tiles; t += 256u) {
-    const double2 v = Mv.partial[(uint64_t)ch * Mv.n_tiles + t];
+  for (uint32_t t = threadIdx.x; t < n_sums; t += 256u) {
+    const double2 v = sums[ch * chain_pitch + t * pitch];
     ar += v.x;
     ai += v.y;
   }
@@ -803,7 +808,8 @@ __global__ __launch_bounds__(256) void k_learned_accept(MetroView Mv, LearnedVie
       }
       // The chain's cache is brought up to date with an accepted mask by the
       // next proposal step (or the final pass of the call).
-      Mv.pmask[ch] = (acc && m != 0ull) ? m : 0ull;
+      const uint64_t before = collect && step > 0u ? Mv.pmask[ch] : 0ull;
+      Mv.pmask[ch] = before ^ (acc ? m : 0ull);
       acc_s = acc && (m != 0ull);
       if (Mv.trace) Mv.trace[idx] = Mv.x[ch];
       if (Mv.accepted) Mv.accepted[idx] = (uint8_t)acc;
@@ -816,7 +822,7 @@ __global__ __launch_bounds__(256) void k_learned_accept(MetroView Mv, LearnedVie
       Lv.logit_x[(uint64_t)ch * n + j] = Lv.logit_y[(uint64_t)ch * n + j];
 }
 
-hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& Lv, MLPDev& d,
+hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& Lv, MLPDev& d, const LearnedAmps* amps,
                                 uint32_t n_steps, hipStream_t st) {
   hipError_t e;
   const bool fused = fused_ok(d);
@@ -831,13 +837,22 @@ hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& 
       if ((e = hipGetLastError()) != hipSuccess) return e;
       if ((e = mlp_forward(d, Lv.y, Lv.n_chain, Lv.logit_y, st)) != hipSuccess) return e;
     }
-    const uint32_t mode = kProposeMasks | (t > 0 ? kProposeApplyPending : 0u);
-    if ((e = launch_propose(T, Mv, Lv.mask, mode, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_learned_accept, dim3(Mv.n_chain), dim3(256), 0, st, Mv, Lv, t);
+    if (amps) {
+      if ((e = launch_amp_mfma_sums(amps->inst, amps->items, amps->n_items, amps->n_split, amps->steps, false, st)) !=
+          hipSuccess)
+        return e;
+      hipLaunchKernelGGL(k_learned_accept, dim3(Mv.n_chain), dim3(256), 0, st, Mv, Lv, t, amps->sums, amps->rows,
+                         (uint64_t)1, (uint64_t)Mv.n_chain, true);
+    } else {
+      const uint32_t mode = kProposeMasks | (t > 0 ? kProposeApplyPending : 0u);
+      if ((e = launch_propose(T, Mv, Lv.mask, mode, st)) != hipSuccess) return e;
+      hipLaunchKernelGGL(k_learned_accept, dim3(Mv.n_chain), dim3(256), 0, st, Mv, Lv, t, (const double2*)Mv.partial,
+                         Mv.n_tiles, (uint64_t)Mv.n_tiles, (uint64_t)1, false);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // The last step's accepted masks, so that the caches are up to date when the
-  // call returns.
+  // The last step's (or the call's) accepted masks, so that the caches are up to
+  // date when the call returns.
   return n_steps ? launch_propose(T, Mv, Lv.mask, kProposeApplyPending, st) : hipSuccess;
 }
 

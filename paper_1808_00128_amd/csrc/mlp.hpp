@@ -75,7 +75,16 @@ hipError_t mlp_forward(MLPDev& d, const uint64_t* x, uint32_t B, float* logits, 
 // Loss sum (added to *loss_acc, cleared first with clear_loss) and gradients; with adam also the Adam step.
 hipError_t mlp_loss_grad(MLPDev& d, const uint64_t* x, const uint64_t* t, uint32_t B,
                          double* loss_acc, bool clear_loss, bool adam, float lr, hipStream_t st);
-hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& Lv, MLPDev& d,
+// Amplitudes of the proposals on the matrix cores: the plan of one request (x =
+// the proposals) and its partial sums [rows][n_chain].
+struct LearnedAmps {
+  const AmpMfmaInst* inst;
+  const AmpItem* items;
+  uint32_t n_items, n_split, steps, rows;
+  const double2* sums;
+};
+// amps null: amplitudes from the chains' caches (k_propose).
+hipError_t launch_learned_steps(const TermsView& T, MetroView& Mv, LearnedView& Lv, MLPDev& d, const LearnedAmps* amps,
                                 uint32_t n_steps, hipStream_t st);
 
 }  // namespace chsim
