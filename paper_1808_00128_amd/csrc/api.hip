@@ -1600,10 +1600,8 @@ chsim_status chsim_inner_products_ch(chsim_ctx* ctx, uint32_t inst, uint32_t bra
   if ((st = ensure_materialised(Bt, s))) return st;
   const uint32_t n = K.n, L = (uint32_t)Bt.chi;
   const InnerChPlan ip = inner_ch_plan(n, K.chi, L);
-  if (ip.pairs || bra_inst == inst) {
-    HIP_TRY(ctx->chrec_k.ensure(inner_ch_record_words(n, K.chi)));
-    HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
-  }
+  if (ip.pairs || bra_inst == inst) HIP_TRY(ctx->chrec_k.ensure(inner_ch_record_words(n, K.chi)));
+  if (bra_inst == inst) HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
   const uint64_t* rec_b = ctx->chrec_k.p;
   if (bra_inst != inst) {
     HIP_TRY(ctx->chrec_b.ensure(inner_ch_record_words(n, Bt.chi)));

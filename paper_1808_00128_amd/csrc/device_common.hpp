@@ -29,6 +29,16 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // Mask of lanes where pred holds (64-bit wave).
 __device__ __forceinline__ uint64_t ballot64(bool pred) { return (uint64_t)__ballot(pred); }
 
+// Maximum over 64 copies of a count, 16 words apart, read one per lane.
+__device__ __forceinline__ uint32_t quad_stat_max(const uint32_t* stat, uint32_t k, uint32_t lane) {
+  uint32_t x = stat[lane * 16u + k];
+  for (int m = 32; m >= 1; m >>= 1) {
+    const uint32_t o = (uint32_t)__shfl_xor((int)x, m);
+    x = o > x ? o : x;
+  }
+  return uniform32(x);
+}
+
 // All-ones if bit i of x is set, else 0.
 __device__ __forceinline__ uint64_t bitmask64(uint64_t x, uint32_t i) {
   return (uint64_t)0 - ((x >> i) & 1ull);

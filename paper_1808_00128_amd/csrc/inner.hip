@@ -470,10 +470,10 @@ __global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, const uint6
 }
 
 // overlap_l = the sum of the groups' partials in FP64, in a fixed order: a
-// 256-thread block takes 8 states and 32 slices of the groups, and the slice
+// 256-thread block takes 4 states and 64 slices of the groups, and the slice
 // sums are added in slice order (one thread per state walking 512 groups took
 // 122 us for 100 states, a serial chain of loads; this takes 5 us).
-constexpr uint32_t kRedX = 8, kRedSlices = 32;
+constexpr uint32_t kRedX = 4, kRedSlices = 64;
 __global__ __launch_bounds__(256) void k_inner_reduce(const double2* __restrict__ partial,
                                                       uint32_t n_blocks, uint32_t L, uint32_t n,
                                                       double2* __restrict__ overlap,

@@ -52,12 +52,22 @@ constexpr uint32_t kSlicedSlots = 32;  // constraints held per bra; more go to t
 
 __host__ __device__ constexpr uint32_t chrec_words(uint32_t n) { return 6u * n + 6u; }
 
+// 1 + the constraints of the bras (a large number if they are more than the slots),
+// or zero when every ket's form fits the bit-sliced kernels.
+__device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat, uint32_t slots, uint32_t lane) {
+  uint32_t w = quad_stat_max(stat, 2u, lane);
+  if (w > slots) w = 1u << 20;
+  return quad_stat_max(stat, 0u, lane) + w <= kQuadMaxVars ? 0u : w + 1u;
+}
+
 // Record of one term: colG [0, n), rows of G [n, 2n), colF [2n, 3n), rows of
 // Bs [3n, 4n), Bs colG_i [4n, 5n), Bu colG_i [5n, 6n) (Bu: the strictly
 // upper part of Bs, row q below bit q), then diag(B), glo, x1 = s G^T, s, v,
 // omega.
-__global__ __launch_bounds__(64 * kCHWaves) void k_chrec(TermsView T, uint64_t* __restrict__ rec) {
+__global__ __launch_bounds__(64 * kCHWaves) void k_chrec(TermsView T, uint64_t* __restrict__ rec,
+                                                         const uint32_t* __restrict__ stat, uint32_t slots) {
   const uint32_t lane = threadIdx.x & 63u;
+  if (stat && pairs_left(stat, slots, lane) == 0u) return;
   const uint64_t term = (uint64_t)blockIdx.x * kCHWaves + uniform32(threadIdx.x >> 6);
   if (term >= T.chi) return;  // whole waves
   const uint32_t n = T.n;
@@ -235,8 +245,8 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   const uint32_t l = bblock * kCHWaves + uniform32(threadIdx.x >> 6);
   if (l >= L) return;  // whole waves
   // Kets whose form fits the bit-sliced kernels are theirs.
-  const uint32_t nw = !stat || stat[2] > slots ? 1u << 20 : stat[2];
-  if (stat && stat[0] + nw <= kQuadMaxVars) {
+  const uint32_t nw = stat ? pairs_left(stat, slots, lane) : 1u << 20;
+  if (nw == 0u) {
     if (lane == 0u) partial[(uint64_t)group * L + l] = make_double2(0.0, 0.0);
     return;
   }
@@ -290,7 +300,7 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   uint32_t bad = 0;
   for (uint64_t a = group; a < chi_k; a += groups) {
     const uint64_t* rk = rec_k + a * R;
-    if (stat && (uint32_t)__popcll(uniform64(rk[6u * n + 4u])) + nw <= kQuadMaxVars) continue;
+    if (stat && (uint32_t)__popcll(uniform64(rk[6u * n + 4u])) + (nw - 1u) <= kQuadMaxVars) continue;
     const uint64_t colGk = act ? rk[lane] : 0ull;
     const uint64_t Growk = act ? rk[n + lane] : 0ull;
     const uint64_t Bsk = act ? rk[3u * n + lane] : 0ull;
@@ -447,10 +457,10 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   if (lane == 0u) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
 }
 
-// overlap_l = the sum of the groups' partials in FP64, in a fixed order: 8
-// states and 32 slices of the groups per block, the slice sums added in slice
+// overlap_l = the sum of the groups' partials in FP64, in a fixed order: 4
+// states and 64 slices of the groups per block, the slice sums added in slice
 // order (one thread per state walking 512 groups took 123 us).
-constexpr uint32_t kRedX = 8, kRedSlices = 32;
+constexpr uint32_t kRedX = 4, kRedSlices = 64;
 __global__ __launch_bounds__(256) void k_inner_ch_reduce(const double2* __restrict__ partial, uint32_t groups,
                                                          uint32_t L, double2* __restrict__ overlap) {
   __shared__ double2 part[kRedSlices][kRedX];
@@ -506,12 +516,17 @@ __global__ __launch_bounds__(256) void k_inner_ch_total(const double2* __restric
 
 size_t inner_ch_record_words(uint32_t n, uint64_t chi) { return (size_t)chi * chrec_words(n); }
 
-hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_t st) {
+static hipError_t launch_records(const TermsView& T, uint64_t* rec, const uint32_t* stat, uint32_t slots,
+                                 hipStream_t st) {
   const uint64_t blocks = (T.chi + kCHWaves - 1) / kCHWaves;
   if (blocks == 0) return hipSuccess;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_chrec, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, T, rec);
+  hipLaunchKernelGGL(k_chrec, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, T, rec, stat, slots);
   return hipGetLastError();
+}
+
+hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_t st) {
+  return launch_records(T, rec, nullptr, 0u, st);
 }
 
 static uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
@@ -532,7 +547,7 @@ InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L) {
   return P;
 }
 
-hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, const uint64_t* rec_k,
+hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, uint64_t* rec_k,
                            const uint64_t* rec_b, uint64_t* work, double2* partial, double2* overlap, double2* total,
                            uint32_t* err, hipStream_t st) {
   const uint32_t n = K.n, L = (uint32_t)Tb.chi;
@@ -547,8 +562,10 @@ hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerC
     const uint64_t blocks = (uint64_t)bra_blocks * P.groups;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const uint32_t* const stat = P.sliced ? quad_stat(P.quad, work) : nullptr;
+    if (rec_k != rec_b && (e = launch_records(K, rec_k, stat, P.quad.slots, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_inner_ch_pairs, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, rec_k, K.b, K.chi, rec_b, L,
-                       n, P.groups, bra_blocks, P.sliced ? quad_stat(P.quad, work) : nullptr, P.quad.slots,
+                       n, P.groups, bra_blocks, stat, P.quad.slots,
                        partial + (size_t)P.quad.rows * L, err);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

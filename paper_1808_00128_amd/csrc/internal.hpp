@@ -296,9 +296,14 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
 constexpr uint32_t kQuadMaxVars = 59;
 struct QuadPlan {
   uint32_t n_batches, slots, ne1, rows;
+  bool many;  // more than one launch by size: the counts are kept
   size_t rec_words, slice_words, words;
 };
 QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots);
+// The counts: 64 copies, 64 bytes apart, that workgroups take turns in (one address
+// for every wave of a prologue serialised it: 3001 terms in 37 µs, 14 now).
+constexpr uint32_t kQuadStatWords = 64u * 16u;
+__host__ __device__ constexpr uint32_t quad_stat_slot(uint32_t block) { return (block % 64u) * 16u; }
 uint32_t* quad_stat(const QuadPlan& P, uint64_t* work);
 hipError_t launch_quad_prep(const TermsView& T, const QuadPlan& P, uint64_t* work, hipStream_t st);
 hipError_t launch_quad_equatorial(const uint64_t* Aoff, const uint8_t* Adiag, uint32_t n, uint32_t L,
@@ -336,8 +341,9 @@ struct InnerChPlan {
   size_t partial_elems;
 };
 InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L);
-// rec_k is read by the pair kernel only (plan.pairs).
-hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, const uint64_t* rec_k,
+// rec_b: the bras' records; rec_k: room for the kets' (plan.pairs), written here
+// where the pair kernel has kets to take, or rec_b if the sets are the same.
+hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, uint64_t* rec_k,
                            const uint64_t* rec_b, uint64_t* work, double2* partial, double2* overlap, double2* total,
                            uint32_t* err, hipStream_t st);
 

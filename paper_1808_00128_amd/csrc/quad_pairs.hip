@@ -103,8 +103,8 @@ __device__ __forceinline__ uint64_t gather_bits(uint64_t x, uint64_t m) {
 
 constexpr uint32_t kPrepWaves = 4;
 
-// One wave per term, lane = row, then lane = column.  stat[0] = max |v|,
-// stat[1] = max (64 - |v|).
+// One wave per term, lane = row, then lane = column.  Counts 0, 1: max |v|, max
+// (64 - |v|), unless stat is null (one launch takes every term).
 __global__ __launch_bounds__(64 * kPrepWaves) void k_quad_prep(TermsView T, uint64_t* __restrict__ rec,
                                                                uint32_t* __restrict__ stat) {
   __shared__ uint64_t cols[kPrepWaves][64];
@@ -210,9 +210,11 @@ __global__ __launch_bounds__(64 * kPrepWaves) void k_quad_prep(TermsView T, uint
     r[0] = (uint64_t)nv | ((uint64_t)m << 8) | ((uint64_t)T.omega[term] << 16);
     r[1] = kdlo;
     r[2] = kdhi;
-    // One address for all waves: write only what raises it.
-    if (nv > __hip_atomic_load(stat, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(stat, nv);
-    if (64u - nv > __hip_atomic_load(stat + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(stat + 1, 64u - nv);
+    if (stat) {
+      uint32_t* const sl = stat + quad_stat_slot(blockIdx.x);
+      atomicMax(sl, nv);
+      atomicMax(sl + 1, 64u - nv);
+    }
   }
 }
 
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(64) void k_slice_equatorial(const uint64_t* __restr
 // The same for bra states (terms of Tb with Bs and the planes in their records):
 // conj(<x|theta>) = 2^{-|v|/2} e^{-i pi omega/4} i^{-glo x - 2 x B x} on the
 // solutions of (x F)_j = s_j, j outside v (in increasing order: slots 0, 1, ...).
-// stat[2] = max number of constraints.
+// Count 2: max number of constraints.
 __global__ __launch_bounds__(64) void k_slice_bras(TermsView Tb, const uint64_t* __restrict__ rec, uint32_t rec_words,
                                                    uint32_t L, uint32_t ne1, uint32_t slots,
                                                    uint32_t* __restrict__ sl, uint32_t* __restrict__ info,
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(64) void k_slice_bras(TermsView Tb, const uint64_t*
   }
   if (i == 0u) {
     info[l] = l < L ? (Tb.omega[l] & 7u) | ((uint32_t)__popcll(Tb.v[l]) << 8) : 0u;
-    if (l < L) atomicMax(stat + 2, (uint32_t)__popcll(nvm));
+    if (l < L) atomicMax(stat + quad_stat_slot(blockIdx.x) + 2u, (uint32_t)__popcll(nvm));
   }
   uint32_t* out = sl + (size_t)(blockIdx.x >> 1) * slice_entries(n, ne1) * 4u + (size_t)i * ne1 * 4u;
   store_row(x, w, n, ne1, lane, blockIdx.x & 1u, out);
@@ -306,6 +308,7 @@ struct QuadArgs {
   double2* partial;  // this launch's rows
   uint32_t n, ne1, slots, L, n_waves, n_batches;
   uint32_t nc_lo, nc_hi;  // the variables (without the extra one) this launch takes
+  bool many;              // there are other launches: the counts tell whether this one has any terms
 };
 
 // Columns Q per lane, at most RM rows (variables and the extra one); the
@@ -319,10 +322,12 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   const uint32_t wgs = A.n_waves / NW;  // workgroups per batch
   const uint32_t batch = blockIdx.x / wgs, row0 = (blockIdx.x % wgs) * NW + wave;
   const uint32_t l0 = batch * 128u + g * 32u + 2u * j;
-  uint32_t w = A.slots ? A.stat[2] : 0u;
+  uint32_t w = 0u;
+  bool any_term = true;  // uniform over the grid
+  if (A.slots) w = quad_stat_max(A.stat, 2u, lane);
   if (w > A.slots) w = 1u << 20;  // more constraints than columns: not for these kernels
+  if (A.many) any_term = quad_stat_max(A.stat, 0u, lane) + w >= A.nc_lo && 64u - quad_stat_max(A.stat, 1u, lane) + w <= A.nc_hi;
   double ar[2] = {0.0, 0.0}, ai[2] = {0.0, 0.0};
-  const bool any_term = A.stat[0] + w >= A.nc_lo && 64u - A.stat[1] + w <= A.nc_hi;  // uniform over the grid
   if (any_term) {
     const uint4* src = reinterpret_cast<const uint4*>(A.sl) + (size_t)batch * slice_entries(n, ne1);
     for (uint32_t e = threadIdx.x; e < slice_entries(n, ne1); e += 64u * NW) reinterpret_cast<uint4*>(lds)[e] = src[e];
@@ -622,7 +627,8 @@ QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots) {
     if (c.nc_lo <= n + slots) P.rows += class_waves(c, chi, P.n_batches);
   P.rec_words = ((size_t)chi * rec_layout(n).words + 1u) & ~(size_t)1;  // the slices are read 16 bytes at a time
   P.slice_words = (size_t)P.n_batches * slice_entries(n, P.ne1) * 2u;
-  P.words = P.rec_words + P.slice_words + (size_t)P.n_batches * 64u + 2u;
+  P.many = n + slots > kClasses[0].nc_hi;
+  P.words = P.rec_words + P.slice_words + (size_t)P.n_batches * 64u + kQuadStatWords / 2u;
   return P;
 }
 
@@ -631,11 +637,15 @@ uint32_t* quad_stat(const QuadPlan& P, uint64_t* work) {
 }
 
 hipError_t launch_quad_prep(const TermsView& T, const QuadPlan& P, uint64_t* work, hipStream_t st) {
-  hipError_t e = hipMemsetAsync(quad_stat(P, work), 0, 16, st);
-  if (e != hipSuccess) return e;
+  const bool counts = P.many || P.slots;
+  if (counts) {
+    const hipError_t e = hipMemsetAsync(quad_stat(P, work), 0, kQuadStatWords * sizeof(uint32_t), st);
+    if (e != hipSuccess) return e;
+  }
   const uint64_t blocks = (T.chi + kPrepWaves - 1) / kPrepWaves;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)blocks), dim3(64 * kPrepWaves), 0, st, T, work, quad_stat(P, work));
+  hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)blocks), dim3(64 * kPrepWaves), 0, st, T, work,
+                     counts ? quad_stat(P, work) : nullptr);
   return hipGetLastError();
 }
 
@@ -671,6 +681,7 @@ hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, 
   A.slots = P.slots;
   A.L = L;
   A.n_batches = P.n_batches;
+  A.many = P.many;
   A.partial = partial;
   const uint32_t sm = slice_entries(T.n, P.ne1) * 16u;
   for (int k = 0; k < 3; ++k) {
