@@ -23,17 +23,19 @@
 // the 16 lanes by DPP.  Each step takes the next variable a in order and, state by
 // state, the first b with S_ab = 1: b's row is the sum of the rows under the
 // first-set masks; states in which a has no partner left take part with zeros (an
-// eliminated variable's row and column come out zero by themselves).  Every two
-// rows a step leaves, registers move down and lanes shift, so that the next
-// variable is again register 0, lane 0.  One bit operation serves 2048 pairs'
+// eliminated variable's row and column come out zero by themselves).  Forms of up to
+// 27 variables have every step as code of its own; above, after every Q steps the
+// registers move down and the lanes shift, so that the next variable is again
+// register 0, lane 0.  One bit operation serves 2048 pairs'
 // entries of a wave where the lane-per-state form (one 32-bit row of one state per
 // lane) serves 64 rows; selection and pivoting cost nothing for divergence.
 //
 // VALU issue bounds it.  Against one state per lane with its form's rows in LDS
 // (equatorial) and one wave per pair (bras), whole calls: n = 40, |v| = 20..22,
-// chi = 2^18, 1024 states 73.6 -> 38.9 ms; n = 45, |v| = 41..43, chi = 60000, 500
+// chi = 2^18, 1024 states 73.6 -> 37.0 ms (the pair kernel 67.2 -> 27.3 where the
+// clock holds; with loops as for larger forms 30.3); n = 45, |v| = 41..43, chi = 60000, 500
 // states 45.7 -> 8.7; n = 50, |v| = 46..49, 1000 states 117 -> 43.6; 256 bras
-// n = 40, chi = 2^16 34.1 -> 5.3, n = 50, chi = 60000, 200 bras 50.2 -> 14.0.
+// n = 40, chi = 2^16 34.1 -> 5.1, n = 50, chi = 60000, 200 bras 50.2 -> 14.0.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -313,9 +315,16 @@ struct QuadArgs {
 
 // Columns Q per lane, at most RM rows (variables and the extra one); the
 // elimination's loops are unrolled for RM, RM - GR, ... rows.
+// GR = 0: straight-line code instead, with column and row c at place RM - 1 - c, so
+// that the steps of a smaller form are the last ones, nothing moves and no row is
+// visited in vain (RM = 28; for more rows the code would leave the instruction
+// cache).
 template <int Q, int RM, int GR, int NW, int OCC>
 __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   extern __shared__ __align__(16) uint32_t lds[];
+  constexpr bool kStraight = GR == 0;
+  constexpr auto at = [](int c) { return kStraight ? RM - 1 - c : c; };  // place of column or row c
+  constexpr int kQ0 = at(0) % Q, kJ0 = at(0) / Q;                        // column 0's
   const uint32_t lane = threadIdx.x & 63u, wave = uniform32(threadIdx.x >> 6);
   const uint32_t g = lane >> 4, j = lane & 15u;
   const uint32_t n = A.n, ne1 = A.ne1;
@@ -337,7 +346,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
     const uint32_t dhi0 = (n + 1u) * stride;
     const uint32_t inf0 = A.info[l0], inf1 = A.info[l0 + 1u];
     const RecLayout RL = rec_layout(n);
-    const uint32_t nl0 = j == 0u ? 0u : ~0u;
+    const uint32_t nl0 = j == (uint32_t)kJ0 ? 0u : ~0u;
     for (uint64_t term = row0; term < A.chi; term += A.n_waves) {
       const uint64_t* __restrict__ r = A.rec + term * RL.words;
       const uint64_t hdr = r[0];
@@ -353,7 +362,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       uint32_t Hl[Q], Hh[Q], Kl[Q], Kh[Q], B1[Q], B2[Q], D0[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t dcol = (uint32_t)Q * j + (uint32_t)q;
+        const uint32_t dcol = kStraight ? (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q) : (uint32_t)Q * j + (uint32_t)q;
         const uint64_t* rc = r + RL.cols + 3u * (dcol <= nv ? dcol : 0u);
         const bool on = dcol <= nv, xt = on && dcol != 0u;
         const uint64_t h = on ? rc[0] : 0ull, k = xt ? rc[1] : 0ull;
@@ -372,17 +381,17 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       sfor<RM>([&](auto ic) {
         constexpr int c = ic;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) S[c][q] = 0u;
+        for (int q = 0; q < Q; ++q) S[at(c)][q] = 0u;
         if constexpr (c > 0) {
           if ((uint32_t)c <= nv) {
             const uint32_t base = rp[c] * stride;
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-              S[c][q] = ld(base + B1[q]) ^ bit_mask(c < 32 ? Kl[q] : Kh[q], (uint32_t)c & 31u);
+              S[at(c)][q] = ld(base + B1[q]) ^ bit_mask(c < 32 ? Kl[q] : Kh[q], (uint32_t)c & 31u);
           } else if ((uint32_t)c <= nc) {
             const uint32_t base = (n + (uint32_t)c - nv - 1u) * 16u;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) S[c][q] = ld(base + B2[q]);
+            for (int q = 0; q < Q; ++q) S[at(c)][q] = ld(base + B2[q]);
           }
         }
       });
@@ -392,7 +401,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       // Rows i of N, two at a time (a zero row after the last of an odd count).
       for (uint32_t i = 0; i < m; i += 2u) {
         const uint32_t n0 = rn[i], n1 = rn[i + 1u];
-        const uint32_t r0 = n0 * stride, r1 = n1 * stride;
+        const uint32_t r0 = n0 * stride, r1 = n1 * stride, r0g = r0 + g4, r1g = r1 + g4;
         uint32_t a0[Q], a1[Q], y0[Q], y1[Q], h0[Q], h1[Q], c0[Q], c1[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -406,8 +415,8 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
         auto span = [&](uint32_t jb, uint32_t je, const uint32_t (&Hw)[Q]) {
 #pragma unroll 4
           for (uint32_t jj = jb; jj < je; ++jj) {
-            const uint32_t o = rn[jj] * 16u + g4;
-            const uint32_t w0 = ld(r0 + o), w1 = ld(r1 + o);
+            const uint32_t o = rn[jj] * 16u;
+            const uint32_t w0 = ld(r0g + o), w1 = ld(r1g + o);
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
               const uint32_t hm = bit_mask(Hw[q], jj & 31u);
@@ -450,13 +459,13 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
           if ((uint32_t)(c & ~3) <= nc) {
             const uint32_t m0 = (uint32_t)((int32_t)((c < 32 ? (uint32_t)hr0 : (uint32_t)(hr0 >> 32)) << (31 - (c & 31))) >> 31);
             const uint32_t m1 = (uint32_t)((int32_t)((c < 32 ? (uint32_t)hr1 : (uint32_t)(hr1 >> 32)) << (31 - (c & 31))) >> 31);
-            const uint32_t b0 = row_bcast<c / Q>(a0[c % Q]), b1 = row_bcast<c / Q>(a1[c % Q]);
+            const uint32_t b0 = row_bcast<at(c) / Q>(a0[at(c) % Q]), b1 = row_bcast<at(c) / Q>(a1[at(c) % Q]);
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-              S[c][q] = and_xor(m0, y0[q], S[c][q]);
-              S[c][q] = and_xor(m1, y1[q], S[c][q]);
-              S[c][q] = and_xor(b0, h0[q], S[c][q]);
-              S[c][q] = and_xor(b1, h1[q], S[c][q]);
+              S[at(c)][q] = and_xor(m0, y0[q], S[at(c)][q]);
+              S[at(c)][q] = and_xor(m1, y1[q], S[at(c)][q]);
+              S[at(c)][q] = and_xor(b0, h0[q], S[at(c)][q]);
+              S[at(c)][q] = and_xor(b1, h1[q], S[at(c)][q]);
             }
           }
         });
@@ -465,108 +474,125 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       // with x1 (row 0), the term's part.  Column 0's is the constant.
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t dcol = (uint32_t)Q * j + (uint32_t)q;
+        const uint32_t dcol = kStraight ? (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q) : (uint32_t)Q * j + (uint32_t)q;
         const uint32_t plo = ld(D0[q]), phi = ld(dhi0 + B1[q]);
         hi[q] = and_xor(lo[q], plo, hi[q] ^ phi);
         lo[q] ^= plo;
-        hi[q] ^= q == 0 ? S[0][0] & nl0 : S[0][q];
+        hi[q] ^= q == kQ0 ? S[at(0)][q] & nl0 : S[at(0)][q];
         const uint32_t kl = 0u - ((uint32_t)(kdlo >> (dcol & 63u)) & 1u), kh = 0u - ((uint32_t)(kdhi >> (dcol & 63u)) & 1u);
         hi[q] = and_xor(lo[q], kl, hi[q] ^ kh);
         lo[q] ^= kl;
       }
-      const uint32_t cst0 = row_bcast<0>(lo[0]), cst1 = row_bcast<0>(hi[0]);
+      const uint32_t cst0 = row_bcast<kJ0>(lo[kQ0]), cst1 = row_bcast<kJ0>(hi[kQ0]);
       // Lift: column 0 becomes the extra variable.
       uint32_t lr[Q], li[Q], kx[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        lr[q] = q == 0 ? hi[0] & nl0 : hi[q];
-        li[q] = q == 0 ? lr[0] | ~nl0 : lr[q];
-        kx[q] = q == 0 ? lo[0] | ~nl0 : lo[q];
-        S[0][q] = q == 0 ? lo[0] & nl0 : lo[q];
+        lr[q] = q == kQ0 ? hi[q] & nl0 : hi[q];
+        li[q] = q == kQ0 ? lr[q] | ~nl0 : lr[q];
+        kx[q] = q == kQ0 ? lo[q] | ~nl0 : lo[q];
+        S[at(0)][q] = q == kQ0 ? lo[q] & nl0 : lo[q];
       }
       sfor<RM>([&](auto ic) {
         constexpr int c = ic;
         if constexpr (c > 0) {
-          const uint32_t kf = row_bcast<c / Q>(lo[c % Q]);
-          S[c][0] &= nl0;
+          constexpr int pc = at(c);
+          const uint32_t kf = row_bcast<pc / Q>(lo[pc % Q]);
+          S[pc][kQ0] &= nl0;
 #pragma unroll
-          for (int q = 0; q < Q; ++q) S[c][q] = and_xor(kf, kx[q], S[c][q]);
-          S[c][c % Q] = j == (uint32_t)(c / Q) ? 0u : S[c][c % Q];
+          for (int q = 0; q < Q; ++q) S[pc][q] = and_xor(kf, kx[q], S[pc][q]);
+          S[pc][pc % Q] = j == (uint32_t)(pc / Q) ? 0u : S[pc][pc % Q];
         }
       });
       // Pair elimination.
       uint32_t sr = 0, si = 0, nzr = 0, nzi = 0, cn[6];
 #pragma unroll
       for (int k = 0; k < 6; ++k) cn[k] = 0u;
-      int rem = (int)nc + 1;
-      sfor<(RM + GR - 1) / GR>([&](auto ib) {
-        constexpr int RB = RM - GR * (int)ib;  // rows of this loop
-        while (rem > RB - GR && rem > 0) {
-          sfor<(Q < RB ? Q : RB)>([&](auto ik) {
-            constexpr int k = ik;
-            uint32_t fo = 0u, Sb[Q], sv[Q], Sa[Q];  // fo: states with a partner
+      // Variable at place kV of register k and lane kL (in the loops it has moved to
+      // the first lane), against the rows of places k + 1 .. R - 1.
+      auto pivot = [&](auto kk, auto kl, auto rr) {
+        constexpr int k = kk, kL = kl, R = rr, q0 = k % Q;
+        uint32_t fo = 0u, Sb[Q], sv[Q], Sa[Q];  // fo: states with a partner
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              Sb[q] = sv[q] = 0u;
-              Sa[q] = S[k][q];
-            }
-            sfor<RB - k - 1>([&](auto ic) {
-              constexpr int c = k + 1 + (int)ic;
-              const uint32_t s1 = row_bcast<0>(S[c][k]), sel = bop3<kAndNot>(s1, fo, 0u);
-              fo = bop3<kOr>(s1, fo, 0u);
+        for (int q = 0; q < Q; ++q) {
+          Sb[q] = sv[q] = 0u;
+          Sa[q] = S[k][q];
+        }
+        sfor<R - k - 1>([&](auto ic) {
+          constexpr int c = k + 1 + (int)ic;
+          const uint32_t s1 = row_bcast<kL>(S[c][q0]), sel = bop3<kAndNot>(s1, fo, 0u);
+          fo = bop3<kOr>(s1, fo, 0u);
 #pragma unroll
-              for (int q = 0; q < Q; ++q) Sb[q] = and_xor(sel, S[c][q], Sb[q]);
-              sv[c % Q] = j == (uint32_t)(c / Q) ? sel : sv[c % Q];
-            });
-            const uint32_t la = row_bcast<0>(lr[k]), ma = row_bcast<0>(li[k]);
-            uint32_t xb = 0, yb = 0;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              xb = and_xor(sv[q], lr[q], xb);
-              yb = and_xor(sv[q], li[q], yb);
-            }
-            const uint32_t lb = row_xor(xb), mb = row_xor(yb);
-            nzr = bop3<kAndNotOr>(la, fo, nzr);
-            nzi = bop3<kAndNotOr>(ma, fo, nzi);
-            sr = and_xor(la, lb, sr);
-            si = and_xor(ma, mb, si);
-            uint32_t carry = fo;
-#pragma unroll
-            for (int p = 0; p < 6; ++p) {
-              const uint32_t x = cn[p] & carry;
-              cn[p] ^= carry;
-              carry = x;
-            }
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              const uint32_t ab = Sa[q] & Sb[q];
-              lr[q] = and_xor(lb, Sa[q], and_xor(la, Sb[q], lr[q] ^ ab));
-              li[q] = and_xor(mb, Sa[q], and_xor(ma, Sb[q], li[q] ^ ab));
-            }
-            sfor<RB - k - 1>([&](auto ic) {
-              constexpr int c = k + 1 + (int)ic;
-              const uint32_t s1 = row_bcast<0>(S[c][k]), s2 = row_bcast<c / Q>(Sb[c % Q]);
-#pragma unroll
-              for (int q = 0; q < Q; ++q) S[c][q] = and_xor(s2, Sa[q], and_xor(s1, Sb[q], S[c][q]));
-            });
-          });
-          // The next variable to register 0, lane 0.
-          sfor<RB>([&](auto ic) {
-            constexpr int c = ic;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              if constexpr (c + Q < RB) S[c][q] = row_next(S[c + Q][q]);
-              else S[c][q] = 0u;
-            }
-          });
+          for (int q = 0; q < Q; ++q) Sb[q] = and_xor(sel, S[c][q], Sb[q]);
+          sv[c % Q] = j == (uint32_t)(c / Q) ? sel : sv[c % Q];
+        });
+        const uint32_t la = row_bcast<kL>(lr[q0]), ma = row_bcast<kL>(li[q0]);
+        nzr = bop3<kAndNotOr>(la, fo, nzr);
+        nzi = bop3<kAndNotOr>(ma, fo, nzi);
+        if constexpr (R - k - 1 > 0) {
+          uint32_t xb = 0, yb = 0;
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
-            lr[q] = row_next(lr[q]);
-            li[q] = row_next(li[q]);
+            xb = and_xor(sv[q], lr[q], xb);
+            yb = and_xor(sv[q], li[q], yb);
           }
-          rem -= Q;
+          const uint32_t lb = row_xor(xb), mb = row_xor(yb);
+          sr = and_xor(la, lb, sr);
+          si = and_xor(ma, mb, si);
+          uint32_t carry = fo;
+#pragma unroll
+          for (int p = 0; p < 6; ++p) {
+            const uint32_t x = cn[p] & carry;
+            cn[p] ^= carry;
+            carry = x;
+          }
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            const uint32_t ab = Sa[q] & Sb[q];
+            lr[q] = and_xor(lb, Sa[q], and_xor(la, Sb[q], lr[q] ^ ab));
+            li[q] = and_xor(mb, Sa[q], and_xor(ma, Sb[q], li[q] ^ ab));
+          }
+          sfor<R - k - 1>([&](auto ic) {
+            constexpr int c = k + 1 + (int)ic;
+            const uint32_t s1 = row_bcast<kL>(S[c][q0]), s2 = row_bcast<c / Q>(Sb[c % Q]);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) S[c][q] = and_xor(s2, Sa[q], and_xor(s1, Sb[q], S[c][q]));
+          });
         }
-      });
+      };
+      if constexpr (kStraight) {
+        sfor<RM>([&](auto ip) {
+          constexpr int p = ip;
+          if ((uint32_t)(RM - 1 - p) <= nc)
+            pivot(std::integral_constant<int, p>{}, std::integral_constant<int, p / Q>{}, std::integral_constant<int, RM>{});
+        });
+      } else {
+        int rem = (int)nc + 1;
+        constexpr int kG = kStraight ? 1 : GR;
+        sfor<(RM + kG - 1) / kG>([&](auto ib) {
+          constexpr int RB = RM - kG * (int)ib;  // rows of this loop
+          while (rem > RB - kG && rem > 0) {
+            sfor<(Q < RB ? Q : RB)>([&](auto ik) {
+              pivot(std::integral_constant<int, (int)ik>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, RB>{});
+            });
+            // The next variable to register 0, lane 0.
+            sfor<RB>([&](auto ic) {
+              constexpr int c = ic;
+#pragma unroll
+              for (int q = 0; q < Q; ++q) {
+                if constexpr (c + Q < RB) S[c][q] = row_next(S[c + Q][q]);
+                else S[c][q] = 0u;
+              }
+            });
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+              lr[q] = row_next(lr[q]);
+              li[q] = row_next(li[q]);
+            }
+            rem -= Q;
+          }
+        });
+      }
       // The lane's two states.
       const double2 b = A.b[term];
 #pragma unroll
@@ -691,7 +717,7 @@ hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, 
     A.nc_hi = c.nc_hi;
     A.n_waves = class_waves(c, T.chi, P.n_batches);
     const dim3 grid(P.n_batches * (A.n_waves / c.nw)), block(64u * c.nw);
-    void (*const fn)(QuadArgs) = k == 0   ? k_quad_pairs<2, 28, 4, 8, 4>
+    void (*const fn)(QuadArgs) = k == 0   ? k_quad_pairs<2, 28, 0, 8, 4>
                                  : k == 1 ? k_quad_pairs<3, 45, 9, 8, 2>
                                           : k_quad_pairs<4, 60, 20, 4, 1>;
     if (sm > 64u * 1024u) {
