@@ -59,6 +59,8 @@ def table_ops_evolve(stats, n):
 
 # MI355X LDS: 256 CUs x 128 B/clk x 2.4 GHz.
 LDS_PEAK_BPS = 256 * 128 * 2.4e9
+# FP4 matrix cores: 1024 SIMDs, a 32x32x64 product (2^17 operations) per 32 clocks at 2.4 GHz.
+FP4_PEAK_OPS = 1024 * 2.0**17 / 32 * 2.4e9
 
 # Peaks measured in this run by chsim_measure_peaks (int32 VALU in TOP/s, HBM
 # copy in GB/s, LDS reads in TB/s); filled in main() before any section.
@@ -78,7 +80,7 @@ def roof(bound, achieved, peak, unit, measured=None, **extra):
 
 
 def amp_lds_bytes_per_pair(n, v_words):
-    """LDS bytes the amplitude kernel reads per (term, x): 8-byte table
+    """LDS bytes the table kernel (n > 60) reads per (term, x): 8-byte table
     lookups, ceil(n / 4) for a term whose zero test is packed into its
     quadratic-form rows (n - |v| <= 64 - n), twice that otherwise, plus one
     lookup of the term's value; returned with the packed fraction of the
@@ -88,6 +90,13 @@ def amp_lds_bytes_per_pair(n, v_words):
     nch = (n + 3) // 4
     per = np.where(packed, nch, 2 * nch) + 1
     return 8.0 * float(np.mean(per)), float(np.mean(packed))
+
+
+def amp_fp4_ops_per_pair(n):
+    """FP4 operations (multiply and add counted apart) of the matrix-core
+    amplitude kernel per (term, x): 64 features per step, n (n + 1) / 2 + 1
+    features."""
+    return 128.0 * ((n * (n + 1) // 2 + 1 + 63) // 64)
 
 
 def algorithmic_ops_amp(xs):
@@ -138,6 +147,7 @@ KERNEL_SOURCES = {
                  "api.hip"],
     "k_evolve_cols": ["evolve_cols.hpp", "bitops.hpp", "evolve_w64.hip", "evolve.hip", "prefix.hip",
                      "device_common.hpp", "internal.hpp", "api.hip"],
+    "k_amp_mfma<float>": ["amplitude_mfma.hip", "device_common.hpp", "internal.hpp", "api.hip"],
     "k_amp<float>": ["amplitude.hip", "device_common.hpp", "internal.hpp", "api.hip"],
     "k_quad_pairs": ["quad_pairs.hip", "inner.hip", "bitops.hpp", "device_common.hpp", "internal.hpp", "api.hip"],
     "k_quad_pairs(ch)": ["quad_pairs.hip", "inner_ch.hip", "bitops.hpp", "device_common.hpp", "internal.hpp", "api.hip"],
@@ -442,14 +452,14 @@ def bench_learned(torch, B, W, stats, steps=1000, n_chain=64, chi=1 << 20, eps=0
     learned = chain_report(stats, ltr, lac, lms, burn, lcost, lfl)
     lbytes = chain_step_bytes(chi, n, n_chain)
     lach = lbytes * steps / (lms / 1e3) / 1e9
-    lown = float(chi * (17 * n + 8 * n_chain * (1 + learned["acceptance"]) + 33))
+    lown = float(chi * 32 * ((n * (n + 1) // 2 + 1 + 63) // 64 + 4))
     learned["roofline"] = roof("hbm", lach, HBM_PEAK_BPS / 1e9, "GB/s", MEASURED.get("hbm"),
-                               kernel="k_propose (flip masks) + k_mlp_fused (masks and network) + k_learned_accept",
+                               kernel="k_mlp_fused (masks and network) + k_amp_mfma<double> (proposals) + k_learned_accept",
                                traffic=None, bytes_per_step=lbytes,
                                count="chi (17 n + 16 chains + 33) B per step (every row staged for the masks)",
                                bytes_per_step_own=lown,
-                               own_count="chi (17 n + 8 chains (1 + acceptance) + 33) B per step (a chain's "
-                                         "cache word is written only after an accepted move)",
+                               own_count="the amplitude records: (n (n + 1) / 2 + 1) / 64 + 4 KB per 32 terms and "
+                                         "step (the caches are brought up to date once per call)",
                                frac_own_count=round(lown * steps / (lms / 1e3) / HBM_PEAK_BPS, 4))
     net.close()
     progress("metropolis: learned chains with the untrained network")
@@ -570,10 +580,7 @@ def bench_uneven(torch, B, W, steps=2, warmup=1):
             t_batch.append(ev[1].elapsed_time(ev[2]))
             t_single.append(ev[2].elapsed_time(ev[3]))
     evals = float(sum(sp["chi"] * sp["x"].size for sp in insts))
-    lds = 0.0
-    for k, sp in enumerate(insts):
-        per, _ = amp_lds_bytes_per_pair(sp["circuit"].n, ctx.get_terms(0, min(sp["chi"], 512), inst=k)["v"])
-        lds += per * sp["chi"] * sp["x"].size
+    fp4 = sum(amp_fp4_ops_per_pair(sp["circuit"].n) * sp["chi"] * sp["x"].size for sp in insts)
     ms_b = float(np.mean(t_batch))
     ms_s = float(np.mean(t_single))
     ms_e = float(np.mean(t_ev))
@@ -587,8 +594,7 @@ def bench_uneven(torch, B, W, steps=2, warmup=1):
             "evals_per_s_batched": evals / (ms_b / 1e3), "evals_per_s_per_instance": evals / (ms_s / 1e3),
             "evals_per_s_step": evals / ((ms_e + ms_b) / 1e3),
             "amplitude_strings_per_item": amp_strings,
-            "amplitude_roofline": roof("lds", lds / (ms_b / 1e3) / 1e12, LDS_PEAK_BPS / 1e12,
-                                       "TB/s (LDS table reads)", MEASURED.get("lds")),
+            "amplitude_roofline": roof("mfma", fp4 / (ms_b / 1e3) / 1e12, FP4_PEAK_OPS / 1e12, "TFLOP/s (FP4)"),
             "finite": ok}
 
 
@@ -801,7 +807,6 @@ def main():
     fp32c_vs_fp64 = float(np.max(np.abs(c32 - c64)) / rms) if rms > 0 else 0.0
 
     ev_stats = ctx.evolution_stats()
-    lds_pair, packed_frac = amp_lds_bytes_per_pair(n, ctx.get_terms(0, min(chi, 4096))["v"])
     ops_ev = algorithmic_ops_evolve(ev_stats, n)
     ops_sv = table_ops_evolve(ev_stats, n)
     ops_amp = algorithmic_ops_amp(xs) * chi * n_x
@@ -823,9 +828,9 @@ def main():
                         own_count="per rule as implemented: H 28 n + 40, CX 12, CZ 4, S-type 3, general 12",
                         frac_own_count=round(ops_ev / (ms_ev / 1e3) / INT32_PEAK_OPS, 4))
     else:
-        dom = f"k_amp<float, {amp_strings // 256}> + k_reduce_ranges (amplitudes, FP32C)"
+        dom = "k_amp_mfma<float> + k_amp_mfma_reduce (amplitudes, FP32C)"
         roofline = roof("alu", ops_amp / (ms_amp / 1e3) / 1e12, INT32_PEAK_OPS / 1e12, "TOP/s (int32)",
-                        MEASURED.get("valu"), kernel=dom, traffic=counter_traffic("k_amp<float>"),
+                        MEASURED.get("valu"), kernel=dom, traffic=counter_traffic("k_amp_mfma<float>"),
                         ops_per_launch=ops_amp, ms_per_launch=round(ms_amp, 4),
                         count="8 |x| + 35 int32 ops per (term, x)")
 
@@ -864,12 +869,12 @@ def main():
         "peaks_measured": dict(MEASURED),
         "fp32c_vs_fp64_normwise": fp32c_vs_fp64,
         "roofline": roofline,
-        "amplitude_roofline": roof("lds", lds_pair * chi * n_x / (ms_amp / 1e3) / 1e12, LDS_PEAK_BPS / 1e12,
-                                   "TB/s (LDS table reads)", MEASURED.get("lds"),
-                                   kernel=f"k_amp<float, {amp_strings // 256}> (with k_amp_prep, k_reduce_ranges)",
-                                   lds_bytes_per_pair=lds_pair, packed_fraction=packed_frac,
-                                   count="8-byte table reads per (term, x): ceil(n/4) + 1 packed, "
-                                         "2 ceil(n/4) + 1 otherwise (lookup-table algorithm)",
+        "amplitude_roofline": roof("mfma", amp_fp4_ops_per_pair(n) * chi * n_x / (ms_amp / 1e3) / 1e12,
+                                   FP4_PEAK_OPS / 1e12, "TFLOP/s (FP4)",
+                                   kernel="k_amp_mfma<float> (with k_amp_mfma_prep, k_amp_mfma_reduce)",
+                                   fp4_ops_per_pair=amp_fp4_ops_per_pair(n),
+                                   count="128 FP4 operations per step of 64 features, n (n + 1) / 2 + 1 features "
+                                         "per (term, x); the support test's groups are not counted",
                                    paper_ops_per_s=round(ops_amp / (ms_amp / 1e3) / 1e12, 3),
                                    paper_count="8 |x| + 35 int32 ops per (term, x) (set-bit loop; this "
                                                "kernel does less work per pair)"),
