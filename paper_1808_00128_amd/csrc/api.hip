@@ -2218,18 +2218,7 @@ chsim_status chsim_terms_copy(chsim_ctx* ctx, uint32_t src_inst, uint32_t dst_in
   st = ensure_materialised(A, s);
   if (st) return st;
   D.drop_chains();
-  const TermsView a = A.view(), d = D.view();
-  const size_t rows = (size_t)A.n * A.chi;
-  HIP_TRY(hipMemcpyAsync(d.F, a.F, rows * 8, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.G, a.G, rows * 8, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.M, a.M, rows * 8, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.gamma, a.gamma, rows, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.v, a.v, A.chi * 8, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.s, a.s, A.chi * 8, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.omega, a.omega, A.chi, hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d.b, a.b, A.chi * sizeof(double2), hipMemcpyDeviceToDevice, s));
-  if (A.n_slot == D.n_slot && A.n_slot)
-    HIP_TRY(hipMemcpyAsync(d.branch, a.branch, (size_t)A.n_slot * A.chi, hipMemcpyDeviceToDevice, s));
+  HIP_TRY(launch_terms_copy(A.view(), D.view(), A.n_slot == D.n_slot, s));
   D.at_zero = false;
   D.amp_ready = D.mfma_ready = false;
   return CHSIM_OK;

@@ -164,6 +164,8 @@ constexpr int evolve_cols_waves(int lanes, int cols) {
 hipError_t launch_evolve(const TermsView& T, const DGate* gates, uint32_t n_gates,
                          const uint32_t* slot_seq, uint32_t n_occ, bool from_zero, uint32_t* err,
                          EvolveShape shape, hipStream_t st);
+// The term store of `a` into `d` (same n and chi), with the branches if asked for.
+hipError_t launch_terms_copy(const TermsView& a, const TermsView& d, bool branches, hipStream_t st);
 hipError_t launch_set_zero(const TermsView& T, hipStream_t st);
 
 // One checkpoint level of shared-prefix evolution.  For every term a < chi:
