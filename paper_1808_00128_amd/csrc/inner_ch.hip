@@ -26,7 +26,7 @@
 //
 // Mapping.  From a few bras on, and for forms of at most kQuadMaxVars variables, the
 // bit-sliced kernels take the pairs, a bra's equations as further variables (n = 40,
-// chi = 2^16, 256 bras: 4.4 ms, one wave per pair 26.6).  Below and beyond: a
+// chi = 2^16, 256 bras: 3.9 ms, one wave per pair 26.6).  Below and beyond: a
 // prologue writes a record per term (one wave per term, lane =
 // row): the columns and rows of G, the columns of F, the rows of Bs and a few
 // words.  The pair kernel runs one wave per (bra state, group of ket terms),
@@ -43,10 +43,9 @@ namespace {
 
 constexpr int kCHWaves = 4;
 // Bra states from which the bit-sliced kernels take over: their cost is that of 128
-// states, 2.0 (n = 20), 4.5 (40) and 8 (46) times as much for forms of up to 27, 44
-// and 59 variables, where a wave per pair costs its share per bra (16 bras: n = 20,
-// chi = 3000: 909 µs and 215; n = 40, chi = 20000: 1808 and 991; n = 46, chi = 30000:
-// 3153 and 3479, with 24 bras 4106 and 3506).
+// states and grows with the form's size, where a wave per pair costs its share per bra
+// (16 bras: n = 20, chi = 3000: 909 µs and 215; n = 40, chi = 20000: 1808 and 991;
+// n = 46, chi = 30000: 3153 and about 3050, with 24 bras 4136 and 3056).
 constexpr uint32_t sliced_min_bras(uint32_t n) { return n <= 28u ? 8u : n <= 44u ? 12u : 20u; }
 constexpr uint32_t kSlicedSlots = 32;  // constraints held per bra; more go to the pair kernel
 

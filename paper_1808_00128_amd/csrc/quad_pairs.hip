@@ -23,19 +23,21 @@
 // the 16 lanes by DPP.  Each step takes the next variable a in order and, state by
 // state, the first b with S_ab = 1: b's row is the sum of the rows under the
 // first-set masks; states in which a has no partner left take part with zeros (an
-// eliminated variable's row and column come out zero by themselves).  Forms of up to
-// 27 variables have every step as code of its own; above, after every Q steps the
-// registers move down and the lanes shift, so that the next variable is again
-// register 0, lane 0.  One bit operation serves 2048 pairs'
+// eliminated variable's row and column come out zero by themselves).  Every step is
+// code of its own (33, 125 and 240 KB for Q = 2, 3, 4: the waves of a compute unit
+// run through it about together, so that it need not fit the instruction cache).
+// One bit operation serves 2048 pairs'
 // entries of a wave where the lane-per-state form (one 32-bit row of one state per
 // lane) serves 64 rows; selection and pivoting cost nothing for divergence.
 //
 // VALU issue bounds it.  Against one state per lane with its form's rows in LDS
 // (equatorial) and one wave per pair (bras), whole calls: n = 40, |v| = 20..22,
 // chi = 2^18, 1024 states 73.6 -> 37.0 ms (the pair kernel 67.2 -> 27.3 where the
-// clock holds; with loops as for larger forms 30.3); n = 45, |v| = 41..43, chi = 60000, 500
-// states 45.7 -> 8.7; n = 50, |v| = 46..49, 1000 states 117 -> 43.6; 256 bras
-// n = 40, chi = 2^16 34.1 -> 5.1, n = 50, chi = 60000, 200 bras 50.2 -> 14.0.
+// clock holds); n = 45, |v| = 41..43, chi = 60000, 500 states 47.0 -> 7.4; n = 50,
+// |v| = 46..49, 1000 states 117 -> 38.2; 256 bras n = 40, chi = 2^16 34.1 -> 4.4,
+// n = 50, chi = 60000, 200 bras 49.8 -> 12.0.  Loops that moved the rows down and the
+// lanes along after every Q steps instead: 30.3 ms (27.3), and 3.17 against 2.82 for
+// the 44-variable kernel of the 256 bras.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -62,10 +64,6 @@ __device__ __forceinline__ void sfor(F&& f) {
 template <int kLane>
 __device__ __forceinline__ uint32_t row_bcast(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + kLane, 0xF, 0xF, true);
-}
-// Lane i takes lane i + 1 of its row, lane 15 zero.
-__device__ __forceinline__ uint32_t row_next(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x101, 0xF, 0xF, true);
 }
 // XOR over the 16 lanes of a row, in all of them.
 __device__ __forceinline__ uint32_t row_xor(uint32_t x) {
@@ -313,18 +311,14 @@ struct QuadArgs {
   bool many;              // there are other launches: the counts tell whether this one has any terms
 };
 
-// Columns Q per lane, at most RM rows (variables and the extra one); the
-// elimination's loops are unrolled for RM, RM - GR, ... rows.
-// GR = 0: straight-line code instead, with column and row c at place RM - 1 - c, so
-// that the steps of a smaller form are the last ones, nothing moves and no row is
-// visited in vain (RM = 28; for more rows the code would leave the instruction
-// cache).
-template <int Q, int RM, int GR, int NW, int OCC>
+// Columns Q per lane, at most RM rows (variables and the extra one).  Column and
+// row c are at place RM - 1 - c (columns Q j + q on lane j), so that the elimination
+// is straight-line code of RM steps of which a smaller form takes the last ones.
+template <int Q, int RM, int NW, int OCC>
 __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   extern __shared__ __align__(16) uint32_t lds[];
-  constexpr bool kStraight = GR == 0;
-  constexpr auto at = [](int c) { return kStraight ? RM - 1 - c : c; };  // place of column or row c
-  constexpr int kQ0 = at(0) % Q, kJ0 = at(0) / Q;                        // column 0's
+  constexpr auto at = [](int c) { return RM - 1 - c; };  // place of column or row c
+  constexpr int kQ0 = at(0) % Q, kJ0 = at(0) / Q;        // column 0's
   const uint32_t lane = threadIdx.x & 63u, wave = uniform32(threadIdx.x >> 6);
   const uint32_t g = lane >> 4, j = lane & 15u;
   const uint32_t n = A.n, ne1 = A.ne1;
@@ -362,7 +356,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       uint32_t Hl[Q], Hh[Q], Kl[Q], Kh[Q], B1[Q], B2[Q], D0[Q];
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t dcol = kStraight ? (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q) : (uint32_t)Q * j + (uint32_t)q;
+        const uint32_t dcol = (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q);
         const uint64_t* rc = r + RL.cols + 3u * (dcol <= nv ? dcol : 0u);
         const bool on = dcol <= nv, xt = on && dcol != 0u;
         const uint64_t h = on ? rc[0] : 0ull, k = xt ? rc[1] : 0ull;
@@ -474,7 +468,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       // with x1 (row 0), the term's part.  Column 0's is the constant.
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const uint32_t dcol = kStraight ? (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q) : (uint32_t)Q * j + (uint32_t)q;
+        const uint32_t dcol = (uint32_t)RM - 1u - ((uint32_t)Q * j + (uint32_t)q);
         const uint32_t plo = ld(D0[q]), phi = ld(dhi0 + B1[q]);
         hi[q] = and_xor(lo[q], plo, hi[q] ^ phi);
         lo[q] ^= plo;
@@ -508,17 +502,16 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       uint32_t sr = 0, si = 0, nzr = 0, nzi = 0, cn[6];
 #pragma unroll
       for (int k = 0; k < 6; ++k) cn[k] = 0u;
-      // Variable at place kV of register k and lane kL (in the loops it has moved to
-      // the first lane), against the rows of places k + 1 .. R - 1.
-      auto pivot = [&](auto kk, auto kl, auto rr) {
-        constexpr int k = kk, kL = kl, R = rr, q0 = k % Q;
+      // Place k against the places after it.
+      auto pivot = [&](auto kk) {
+        constexpr int k = kk, kL = k / Q, q0 = k % Q;
         uint32_t fo = 0u, Sb[Q], sv[Q], Sa[Q];  // fo: states with a partner
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
           Sb[q] = sv[q] = 0u;
           Sa[q] = S[k][q];
         }
-        sfor<R - k - 1>([&](auto ic) {
+        sfor<RM - k - 1>([&](auto ic) {
           constexpr int c = k + 1 + (int)ic;
           const uint32_t s1 = row_bcast<kL>(S[c][q0]), sel = bop3<kAndNot>(s1, fo, 0u);
           fo = bop3<kOr>(s1, fo, 0u);
@@ -529,7 +522,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
         const uint32_t la = row_bcast<kL>(lr[q0]), ma = row_bcast<kL>(li[q0]);
         nzr = bop3<kAndNotOr>(la, fo, nzr);
         nzi = bop3<kAndNotOr>(ma, fo, nzi);
-        if constexpr (R - k - 1 > 0) {
+        if constexpr (k + 1 < RM) {
           uint32_t xb = 0, yb = 0;
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
@@ -552,7 +545,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
             lr[q] = and_xor(lb, Sa[q], and_xor(la, Sb[q], lr[q] ^ ab));
             li[q] = and_xor(mb, Sa[q], and_xor(ma, Sb[q], li[q] ^ ab));
           }
-          sfor<R - k - 1>([&](auto ic) {
+          sfor<RM - k - 1>([&](auto ic) {
             constexpr int c = k + 1 + (int)ic;
             const uint32_t s1 = row_bcast<kL>(S[c][q0]), s2 = row_bcast<c / Q>(Sb[c % Q]);
 #pragma unroll
@@ -560,39 +553,9 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
           });
         }
       };
-      if constexpr (kStraight) {
-        sfor<RM>([&](auto ip) {
-          constexpr int p = ip;
-          if ((uint32_t)(RM - 1 - p) <= nc)
-            pivot(std::integral_constant<int, p>{}, std::integral_constant<int, p / Q>{}, std::integral_constant<int, RM>{});
-        });
-      } else {
-        int rem = (int)nc + 1;
-        constexpr int kG = kStraight ? 1 : GR;
-        sfor<(RM + kG - 1) / kG>([&](auto ib) {
-          constexpr int RB = RM - kG * (int)ib;  // rows of this loop
-          while (rem > RB - kG && rem > 0) {
-            sfor<(Q < RB ? Q : RB)>([&](auto ik) {
-              pivot(std::integral_constant<int, (int)ik>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, RB>{});
-            });
-            // The next variable to register 0, lane 0.
-            sfor<RB>([&](auto ic) {
-              constexpr int c = ic;
-#pragma unroll
-              for (int q = 0; q < Q; ++q) {
-                if constexpr (c + Q < RB) S[c][q] = row_next(S[c + Q][q]);
-                else S[c][q] = 0u;
-              }
-            });
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              lr[q] = row_next(lr[q]);
-              li[q] = row_next(li[q]);
-            }
-            rem -= Q;
-          }
-        });
-      }
+      sfor<RM>([&](auto ip) {
+        if ((uint32_t)(RM - 1 - (int)ip) <= nc) pivot(ip);
+      });
       // The lane's two states.
       const double2 b = A.b[term];
 #pragma unroll
@@ -634,7 +597,7 @@ namespace {
 struct QuadClass {
   uint32_t nc_lo, nc_hi, nw, waves;  // variables taken, waves per workgroup, waves that fill the chip
 };
-constexpr QuadClass kClasses[3] = {{0, 27, 8, 4096}, {28, 44, 8, 2048}, {45, kQuadMaxVars, 4, 1024}};
+constexpr QuadClass kClasses[3] = {{0, 27, 8, 4096}, {28, 47, 8, 2048}, {48, kQuadMaxVars, 4, 1024}};
 
 uint32_t class_waves(const QuadClass& c, uint64_t chi, uint32_t n_batches) {
   const uint64_t want = std::max<uint32_t>(c.waves / n_batches, 1u);
@@ -717,9 +680,9 @@ hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, 
     A.nc_hi = c.nc_hi;
     A.n_waves = class_waves(c, T.chi, P.n_batches);
     const dim3 grid(P.n_batches * (A.n_waves / c.nw)), block(64u * c.nw);
-    void (*const fn)(QuadArgs) = k == 0   ? k_quad_pairs<2, 28, 0, 8, 4>
-                                 : k == 1 ? k_quad_pairs<3, 45, 9, 8, 2>
-                                          : k_quad_pairs<4, 60, 20, 4, 1>;
+    void (*const fn)(QuadArgs) = k == 0   ? k_quad_pairs<2, 28, 8, 4>
+                                 : k == 1 ? k_quad_pairs<3, 48, 8, 2>
+                                          : k_quad_pairs<4, 60, 4, 1>;
     if (sm > 64u * 1024u) {
       const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
       if (e != hipSuccess) return e;

@@ -1,6 +1,6 @@
 """Inner products by bit-sliced elimination against the CPU oracle at the edges of
 the kernels' ranges: the number of variables at which the next kernel takes over
-(27 | 28, 44 | 45, 59 | 60, with none and one at the bottom), rows outside the
+(27 | 28, 47 | 48, 59 | 60, with none and one at the bottom), rows outside the
 echelon form past 32, odd and even counts of them, states that fill a word of 32,
 a batch of 128 and one more, and for two CH forms the same numbers reached with
 constraints of the bra (more of them than there are slots for among them), and
@@ -34,7 +34,7 @@ def _spread(n, k, rng, slots, mix):
 
 @pytest.mark.parametrize("n,k,chi,L", [
     (1, 0, 1, 1), (1, 1, 2, 33), (28, 0, 9, 31), (28, 27, 40, 32), (28, 28, 70, 129), (45, 44, 33, 128),
-    (45, 45, 17, 5), (59, 59, 12, 64), (60, 60, 12, 130), (61, 3, 50, 40), (62, 27, 31, 95), (63, 44, 20, 20),
+    (45, 45, 17, 5), (48, 47, 19, 33), (50, 48, 18, 100), (59, 59, 12, 64), (60, 60, 12, 130), (61, 3, 50, 40), (62, 27, 31, 95), (63, 44, 20, 20),
     (64, 59, 9, 65), (64, 60, 9, 65), (64, 33, 16, 257)])
 def test_equatorial_edges(B, n, k, chi, L):  # noqa: F811
     rng = np.random.default_rng(8100 + 64 * n + k)
@@ -53,7 +53,7 @@ def test_equatorial_edges(B, n, k, chi, L):  # noqa: F811
 @pytest.mark.parametrize("n,kk,kb,chi,bras", [
     (1, 1, 0, 3, 16), (20, 12, 5, 40, 16), (20, 12, 4, 40, 7), (20, 12, 4, 40, 8), (33, 20, 25, 40, 33), (33, 20, 24, 40, 128),
     (50, 40, 46, 30, 129), (50, 40, 45, 30, 40), (50, 10, 18, 20, 40), (50, 10, 17, 20, 40), (61, 45, 47, 12, 20),
-    (61, 45, 46, 12, 20), (64, 64, 64, 1, 1), (64, 62, 63, 8, 17)])
+    (61, 45, 46, 12, 20), (50, 40, 43, 30, 40), (50, 40, 42, 30, 40), (64, 64, 64, 1, 1), (64, 62, 63, 8, 17)])
 def test_ch_edges(B, n, kk, kb, chi, bras):  # noqa: F811
     rng = np.random.default_rng(8200 + 64 * n + kk + kb)
     ck, cb = _spread(n, kk, rng, 4, True), _spread(n, kb, rng, 4, True)
