@@ -29,6 +29,16 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // Mask of lanes where pred holds (64-bit wave).
 __device__ __forceinline__ uint64_t ballot64(bool pred) { return (uint64_t)__ballot(pred); }
 
+// Words that lanes of one wave exchange through LDS: every lane's writes before
+// are visible to every lane's reads after (and reads before precede writes after).
+// The hardware takes a wave's LDS instructions in order; the fences keep the
+// compiler from moving them and cost no instruction.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Maximum over 64 copies of a count, 16 words apart, read one per lane.
 __device__ __forceinline__ uint32_t quad_stat_max(const uint32_t* stat, uint32_t k, uint32_t lane) {
   uint32_t x = stat[lane * 16u + k];

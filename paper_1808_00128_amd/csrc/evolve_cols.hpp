@@ -53,6 +53,11 @@ namespace {
 
 constexpr uint32_t kColWaves = 4;  // waves per workgroup
 
+// The rows in LDS are written and read as 64-bit words and transposed as 32-bit
+// halves: both views may alias.
+typedef uint32_t __attribute__((may_alias)) lds_u32;
+typedef uint64_t __attribute__((may_alias)) lds_u64;
+
 template <int kCtrl>
 __device__ __forceinline__ uint32_t dpp32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xF, 0xF, true);
@@ -100,21 +105,22 @@ __device__ __forceinline__ void transpose32(uint32_t (&a)[32]) {
 }
 
 // Bit transpose of a term's matrix in LDS (Rt[0 .. 32 KW), bits 0 .. 32 KW):
-// lane li < KW^2 of the term takes one 32 x 32 block.  Every read of the wave
-// precedes its first write (one instruction stream, LDS in order).
+// lane li < KW^2 of the term takes one 32 x 32 block and writes it where another
+// lane's was, after every lane's reads.
 template <int KW>
-__device__ __forceinline__ void transpose_lds(uint64_t* Rt, uint32_t li) {
+__device__ __forceinline__ void transpose_lds(lds_u64* Rt, uint32_t li) {
   if (li < (uint32_t)(KW * KW)) {
     const uint32_t rh = li % KW, ch = li / KW;
-    uint32_t* const w = reinterpret_cast<uint32_t*>(Rt);
+    lds_u32* const w = reinterpret_cast<lds_u32*>(Rt);
     uint32_t a[32];
 #pragma unroll
     for (int k = 0; k < 32; ++k) a[k] = w[(32u * rh + (uint32_t)k) * 2u + ch];
     transpose32(a);
+    wave_sync();
 #pragma unroll
     for (int k = 0; k < 32; ++k) w[(32u * ch + (uint32_t)k) * 2u + rh] = a[k];
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
 }
 
 // Words of LDS per term: its rows and one of padding, so that the terms of a
@@ -128,31 +134,31 @@ template <int LPT, int C, int KW>
 struct Cols {
   uint32_t w[KW][C];  // half, column
 
-  __device__ __forceinline__ void load(uint64_t* Rt, uint32_t li, uint32_t n, const uint64_t* src, uint64_t rs) {
+  __device__ __forceinline__ void load(lds_u64* Rt, uint32_t li, uint32_t n, const uint64_t* src, uint64_t rs) {
     for (uint32_t p = li; p < 32u * KW; p += LPT) Rt[p] = p < n ? src[(uint64_t)p * rs] : 0ull;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     transpose_lds<KW>(Rt, li);
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-      const uint32_t* const x = reinterpret_cast<const uint32_t*>(Rt + li * C + j);
+      const lds_u32* const x = reinterpret_cast<const lds_u32*>(Rt + li * C + j);
 #pragma unroll
       for (int k = 0; k < KW; ++k) w[k][j] = x[k];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
-  __device__ __forceinline__ void store(uint64_t* Rt, uint32_t li, uint32_t n, uint64_t* dst, uint64_t rs, bool live) {
+  __device__ __forceinline__ void store(lds_u64* Rt, uint32_t li, uint32_t n, uint64_t* dst, uint64_t rs, bool live) {
     for (uint32_t p = LPT * C + li; p < 32u * KW; p += LPT) Rt[p] = 0ull;
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-      uint32_t* const x = reinterpret_cast<uint32_t*>(Rt + li * C + j);
+      lds_u32* const x = reinterpret_cast<lds_u32*>(Rt + li * C + j);
       x[0] = w[0][j];
       x[1] = KW == 2 ? w[KW - 1][j] : 0u;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     transpose_lds<KW>(Rt, li);
     if (live)
       for (uint32_t p = li; p < n; p += LPT) dst[(uint64_t)p * rs] = Rt[p];
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
   }
 };
 
@@ -185,7 +191,7 @@ __global__ __launch_bounds__(256, (col_waves<LPT, C>())) void k_evolve_cols(Evol
   __shared__ uint64_t lds_rows[kColWaves * T * pitch];
   const uint32_t n = J.dst.n;
   const uint32_t tw = lane / LPT, li = lane % LPT;
-  uint64_t* const Rt = lds_rows + (wave * T + tw) * pitch;
+  lds_u64* const Rt = lds_rows + (wave * T + tw) * pitch;
   const uint64_t item = wave0 + tw;
   const bool live = item < count;
   // Groups past the last term evolve a copy of item 0 and store nothing.

@@ -250,7 +250,7 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
     }
     if (lane < 16u) gtab[k * 16u + lane] = t;
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
   // The rows of only 32 lanes fit the LDS region at once: the two halves of the
   // wave take the term one after the other.
   constexpr uint32_t stride = 32u;
@@ -386,7 +386,7 @@ __device__ __forceinline__ void pair_term(const uint64_t* __restrict__ r, uint32
         ++nel;
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     const int rr = __popcll(iso);
     const bool re_nz = (lr & iso) == 0, im_nz = (li & iso) == 0;
     // Re Z = (-1)^sr 2^{nel + r - 1}, Im Z likewise; both non-zero only with equal exponents.

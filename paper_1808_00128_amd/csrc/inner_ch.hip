@@ -410,11 +410,11 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
         cw[c] = wv;
         ce[c] = ef;
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       const bool fc = lane < nf;
       const uint64_t dc = fc ? cd[lane] : 0ull, wc = fc ? cw[lane] : 0ull;
       const uint32_t ec = fc ? ce[lane] : 0u;
-      __builtin_amdgcn_wave_barrier();
+      wave_sync();
       uint32_t S = 0;
       for (uint32_t c2 = 0; c2 < nf; ++c2) S |= par64(dc & rl64(wc, c2)) << c2;
       const uint32_t lb32 = lane < 32u ? (1u << lane) : 0u;

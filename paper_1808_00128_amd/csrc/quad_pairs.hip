@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * kPrepWaves) void k_quad_prep(TermsView T, uint
     cols[wave][0] = x1;
     pivs[wave][0] = 0u;
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_sync();
   const bool ic = lane <= nv;
   const uint64_t dc = ic ? cols[wave][lane] : 0ull;
   const uint32_t pc = ic ? pivs[wave][lane] : 0u;
