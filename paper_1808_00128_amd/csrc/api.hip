@@ -45,6 +45,14 @@ chsim_status fail(chsim_status st, const char* fmt, ...) {
   return st;
 }
 
+// CHSIM_ENOMEM where a caller has something to give up for the memory.
+#define GROW_TRY(expr)                                                                                      \
+  do {                                                                                                      \
+    hipError_t e_ = (expr);                                                                                 \
+    if (e_ != hipSuccess)                                                                                   \
+      return fail(e_ == hipErrorOutOfMemory ? CHSIM_ENOMEM : CHSIM_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
+  } while (0)
+
 #define HIP_TRY(expr)                                                                   \
   do {                                                                                  \
     hipError_t e_ = (expr);                                                             \
@@ -62,6 +70,7 @@ struct DevBuf {
     n = 0;
     hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
     if (e == hipSuccess) n = count;
+    else (void)hipGetLastError();  // reported here, not by a later launch
     return e;
   }
   void release() {
@@ -93,7 +102,8 @@ struct Instance {
   bool at_zero = true;  // every term is |0^n> and the store holds nothing yet
   bool amp_ready = false;  // the amplitude prologue output matches the terms
   bool mfma_ready = false;  // the matrix-core prologue output matches the terms
-  bool mfma_off = false;    // its buffers did not fit: the table kernel serves this instance
+  bool mfma_off = false;    // its buffers did not fit beside these terms: the table kernel takes them
+  uint64_t mfma_call = 0;   // the call that last used it (chsim_ctx::call)
   EvolveShape shape;    // evolution mapping (0 = default for n)
   bool autotune = false;  // time every shape at the next from-|0^n> evolution
   float tuned_ms[kTuneShapes] = {};     // per tuned shape, kTuneLanes order (0 = not timed)
@@ -187,6 +197,8 @@ struct Instance {
     n_chain = 0;
     drop_graph();
   }
+  // What was computed from the terms is void.
+  void terms_changed() { amp_ready = mfma_ready = mfma_off = false; }
   void release() {
     drop_graph();
     if (metro_done) hipEventDestroy(metro_done);
@@ -234,6 +246,7 @@ struct chsim_ctx {
   std::vector<AmpItem> mitems_h;
   std::vector<uint32_t> mtpr, mrows;
   uint32_t m_split = 0;
+  uint64_t call = 0;  // counts the calls that use matrix-core records
   uint32_t amp_n_items = 0;
   hipStream_t cap_stream = nullptr;  // stream the Metropolis graphs are recorded on
   // The last gate list as given (instance, raw gates) and as converted; a call
@@ -270,6 +283,42 @@ chsim_status check_ctx(chsim_ctx* ctx, uint32_t inst) {
   if (!ctx) return fail(CHSIM_EINVAL, "null context");
   if (inst >= ctx->inst.size()) return fail(CHSIM_EINVAL, "instance %u out of range", inst);
   return CHSIM_OK;
+}
+
+// Give back the matrix-core amplitude records, the one large store that is
+// computed again from the terms when it is needed (n = 50: 1168 bytes per term
+// beside 1284 of the terms), except those the current call uses.  Returns whether
+// any memory was freed.
+bool release_records(chsim_ctx* ctx, bool current) {
+  bool freed = false;
+  for (auto& I : ctx->inst) {
+    if ((!I.mrec.p && !I.mcond.p) || (!current && I.mfma_call == ctx->call)) continue;
+    I.mrec.release();
+    I.mcond.release();
+    I.mfma_ready = false;
+    freed = true;
+  }
+  return freed;
+}
+
+// The span of a call that uses records.
+struct RecordUse {
+  explicit RecordUse(chsim_ctx* c) : ctx(c) { ++ctx->call; }
+  ~RecordUse() { ++ctx->call; }
+  chsim_ctx* ctx;
+};
+
+// A buffer of at least `count` elements; short of memory, the records of other
+// calls and the inner products' workspace go first (calls that use that grow it
+// last).
+template <typename T>
+hipError_t grow(chsim_ctx* ctx, DevBuf<T>& buf, size_t count) {
+  hipError_t e = buf.ensure(count);
+  if (e != hipErrorOutOfMemory) return e;
+  const bool work = ctx->inner_work.p != nullptr;
+  ctx->inner_work.release();
+  if (!release_records(ctx, false) && !work) return e;
+  return buf.ensure(count);
 }
 
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -415,13 +464,13 @@ chsim_status build_slots(Instance& I, const chsim_instance& in) {
 
 // Upload a host or device input array into a device buffer; returns the device pointer.
 template <typename T>
-chsim_status stage_in(DevBuf<T>& buf, const T* src, size_t count, bool device_ptrs, hipStream_t st,
+chsim_status stage_in(chsim_ctx* ctx, DevBuf<T>& buf, const T* src, size_t count, bool device_ptrs, hipStream_t st,
                       const T** out) {
   if (device_ptrs) {
     *out = src;
     return CHSIM_OK;
   }
-  HIP_TRY(buf.ensure(count));
+  HIP_TRY(grow(ctx, buf, count));
   HIP_TRY(hipMemcpyAsync(buf.p, src, count * sizeof(T), hipMemcpyHostToDevice, st));
   *out = buf.p;
   return CHSIM_OK;
@@ -431,7 +480,7 @@ chsim_status ensure_materialised(Instance& I, hipStream_t st) {
   if (!I.at_zero) return CHSIM_OK;
   HIP_TRY(launch_set_zero(I.view(), st));
   I.at_zero = false;
-  I.amp_ready = I.mfma_ready = false;
+  I.terms_changed();
   return CHSIM_OK;
 }
 
@@ -542,7 +591,7 @@ chsim_status chsim_terms_reset(chsim_ctx* ctx, uint32_t inst, uint64_t seed, voi
   const double scale = I.l1 / (double)I.chi;
   HIP_TRY(launch_choose(I.view(), I.slots.p, I.mode, I.seed, scale, as_stream(stream)));
   I.at_zero = true;
-  I.amp_ready = I.mfma_ready = false;
+  I.terms_changed();
   I.drop_chains();
   return CHSIM_OK;
 }
@@ -877,8 +926,8 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
     I.plan_key = key;
     I.plan_valid = true;
     if (!I.plan_cut.empty()) {
-      HIP_TRY(I.plan_slot.ensure(I.plan_slot_h.size()));
-      HIP_TRY(I.plan_width.ensure(I.plan_width_h.size()));
+      HIP_TRY(grow(ctx, I.plan_slot, I.plan_slot_h.size()));
+      HIP_TRY(grow(ctx, I.plan_width, I.plan_width_h.size()));
       HIP_TRY(hipMemcpy(I.plan_slot.p, I.plan_slot_h.data(), I.plan_slot_h.size() * sizeof(uint16_t),
                         hipMemcpyHostToDevice));
       HIP_TRY(hipMemcpy(I.plan_width.p, I.plan_width_h.data(), I.plan_width_h.size(), hipMemcpyHostToDevice));
@@ -894,21 +943,21 @@ chsim_status evolve_all(chsim_ctx* ctx, Instance& I, const std::vector<DGate>& d
   const uint64_t chi = I.chi, n = I.n;
   uint64_t ts = 1;
   while (ts < 2 * chi) ts <<= 1;
-  HIP_TRY(ctx->pf_table.ensure(ts));
-  HIP_TRY(ctx->pf_ids.ensure(ts));
-  HIP_TRY(ctx->pf_slotof.ensure(chi));
-  HIP_TRY(ctx->pf_rep.ensure(chi));
-  HIP_TRY(ctx->pf_parent.ensure(chi));
-  HIP_TRY(I.plan_count.ensure(K));
+  HIP_TRY(grow(ctx, ctx->pf_table, ts));
+  HIP_TRY(grow(ctx, ctx->pf_ids, ts));
+  HIP_TRY(grow(ctx, ctx->pf_slotof, chi));
+  HIP_TRY(grow(ctx, ctx->pf_rep, chi));
+  HIP_TRY(grow(ctx, ctx->pf_parent, chi));
+  HIP_TRY(grow(ctx, I.plan_count, K));
   for (int k = 0; k < 2; ++k) {
-    HIP_TRY(ctx->pf_id[k].ensure(chi));
-    HIP_TRY(ctx->ck_F[k].ensure(n * chi));
-    HIP_TRY(ctx->ck_G[k].ensure(n * chi));
-    HIP_TRY(ctx->ck_M[k].ensure(n * chi));
-    HIP_TRY(ctx->ck_gamma[k].ensure(n * chi));
-    HIP_TRY(ctx->ck_v[k].ensure(chi));
-    HIP_TRY(ctx->ck_s[k].ensure(chi));
-    HIP_TRY(ctx->ck_omega[k].ensure(chi));
+    HIP_TRY(grow(ctx, ctx->pf_id[k], chi));
+    HIP_TRY(grow(ctx, ctx->ck_F[k], n * chi));
+    HIP_TRY(grow(ctx, ctx->ck_G[k], n * chi));
+    HIP_TRY(grow(ctx, ctx->ck_M[k], n * chi));
+    HIP_TRY(grow(ctx, ctx->ck_gamma[k], n * chi));
+    HIP_TRY(grow(ctx, ctx->ck_v[k], chi));
+    HIP_TRY(grow(ctx, ctx->ck_s[k], chi));
+    HIP_TRY(grow(ctx, ctx->ck_omega[k], chi));
   }
   const uint32_t* prev_id = nullptr;
   uint32_t g0 = 0;
@@ -1036,7 +1085,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
     // One padding entry past the last gate: the column kernels read the gate
     // after the current one without a bound check.
     static const DGate kPadGate = {OP_S, 0, 0, 0, 0, 0, 0};
-    HIP_TRY(ctx->gates.ensure(dg.size() + 1));
+    HIP_TRY(grow(ctx, ctx->gates, dg.size() + 1));
     HIP_TRY(hipMemcpyAsync(ctx->gates.p, dg.data(), dg.size() * sizeof(DGate), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(ctx->gates.p + dg.size(), &kPadGate, sizeof(DGate), hipMemcpyHostToDevice, s));
     ctx->occ_start.clear();
@@ -1046,7 +1095,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
         ctx->occ_start.push_back((uint32_t)i);
         ctx->slotseq_h.push_back(dg[i].slot);
       }
-    HIP_TRY(ctx->slotseq.ensure(ctx->slotseq_h.size()));
+    HIP_TRY(grow(ctx, ctx->slotseq, ctx->slotseq_h.size()));
     if (!ctx->slotseq_h.empty())
       HIP_TRY(hipMemcpyAsync(ctx->slotseq.p, ctx->slotseq_h.data(), ctx->slotseq_h.size() * sizeof(uint32_t),
                              hipMemcpyHostToDevice, s));
@@ -1093,7 +1142,7 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
     if (st) return st;
   }
   I.at_zero = false;
-  I.amp_ready = I.mfma_ready = false;
+  I.terms_changed();
   return check_err_flag(ctx, s, "apply_clifford");
 }
 
@@ -1109,31 +1158,55 @@ struct AmpReq {
 };
 
 // Run the amplitude prologue of an instance if its terms changed since.
-chsim_status ensure_amp_prep(Instance& I, hipStream_t s) {
+chsim_status ensure_amp_prep(chsim_ctx* ctx, Instance& I, hipStream_t s) {
   if (I.amp_ready) return CHSIM_OK;
-  HIP_TRY(I.acrow.ensure((size_t)I.n * I.chi));
-  HIP_TRY(I.acst.ensure(I.chi));
+  GROW_TRY(grow(ctx, I.acrow, (size_t)I.n * I.chi));
+  GROW_TRY(grow(ctx, I.acst, I.chi));
   HIP_TRY(launch_amp_prep(I.view(), I.acrow.p, I.acst.p, s));
   I.amp_ready = true;
   return CHSIM_OK;
 }
 
+// The context's records stay beside whatever else the program puts on the GPU, so
+// past kRecordFloor bytes new ones have to leave 1 / kRecordReserve of the device
+// memory free.  (Below it the question alone, 10 to 35 µs, would cost a small
+// instance's first call more than it is worth.)
+constexpr size_t kRecordFloor = (size_t)1 << 30, kRecordReserve = 8;
+
 // The matrix-core prologue, if the terms changed since.  An instance whose
-// records do not fit beside its term store stays with the table kernel, whose
-// prologue output is smaller.
-chsim_status ensure_mfma_prep(Instance& I, hipStream_t s) {
+// records do not fit beside its term store takes the table kernel, whose
+// prologue output is smaller, until its terms change.
+chsim_status ensure_mfma_prep(chsim_ctx* ctx, Instance& I, hipStream_t s) {
+  I.mfma_call = ctx->call;
   if (I.mfma_ready || I.mfma_off) return CHSIM_OK;
   const size_t tiles = (I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile;
-  hipError_t e = I.mrec.ensure(tiles * amp_mfma_tile_bytes(I.n));
-  if (e == hipSuccess) e = I.mcond.ensure(tiles * I.n * kAmpMfmaTile);
+  const size_t rec = tiles * amp_mfma_tile_bytes(I.n), cond = tiles * I.n * kAmpMfmaTile;
+  hipError_t e = hipSuccess;
+  if (I.mrec.n < rec || I.mcond.n < cond) {
+    I.mrec.release();
+    I.mcond.release();
+    auto fits = [&]() {
+      size_t held = rec + cond * sizeof(uint64_t);
+      for (const auto& o : ctx->inst) held += o.mrec.n + o.mcond.n * sizeof(uint64_t);
+      if (held <= kRecordFloor) return true;
+      size_t avail = 0, total = 0;
+      if (hipMemGetInfo(&avail, &total) != hipSuccess) return false;
+      return avail >= rec + cond * sizeof(uint64_t) + total / kRecordReserve;
+    };
+    e = fits() || (release_records(ctx, false) && fits()) ? hipSuccess : hipErrorOutOfMemory;
+    if (e == hipSuccess) e = I.mrec.ensure(rec);
+    if (e == hipSuccess) e = I.mcond.ensure(cond);
+  }
   if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
     I.mrec.release();
     I.mcond.release();
     I.mfma_off = true;
     return CHSIM_OK;
   }
   HIP_TRY(e);
+  I.acrow.release();  // the table kernel's, from a time without records
+  I.acst.release();
+  I.amp_ready = false;
   HIP_TRY(launch_amp_mfma_prep(I.view(), I.mrec.p, I.mcond.p, s));
   I.mfma_ready = true;
   return CHSIM_OK;
@@ -1167,7 +1240,7 @@ chsim_status run_amplitudes_mfma(chsim_ctx* ctx, const std::vector<AmpReq>& reqs
     total_x += reqs[q].n_x;
     max_steps = std::max(max_steps, amp_mfma_steps(ctx->inst[reqs[q].inst].n));
   }
-  HIP_TRY(ctx->partial.ensure(part));
+  GROW_TRY(grow(ctx, ctx->partial, part));
   std::vector<AmpMfmaInst> insts(R);
   size_t off = 0;
   for (size_t q = 0; q < R; ++q) {
@@ -1199,7 +1272,7 @@ chsim_status run_amplitudes_mfma(chsim_ctx* ctx, const std::vector<AmpReq>& reqs
     const size_t at = (w_inst + R + 2) & ~(size_t)1;  // items are 16 bytes
     std::memcpy(words.data() + at, ctx->mitems_h.data(), w_items * 8);
     ctx->mplan_key.clear();
-    HIP_TRY(ctx->mplan.ensure(words.size()));
+    GROW_TRY(grow(ctx, ctx->mplan, words.size()));
     HIP_TRY(hipMemcpyAsync(ctx->mplan.p, words.data(), words.size() * 8, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));  // the host vector dies with this call
     ctx->mplan_key = insts;
@@ -1220,28 +1293,33 @@ chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& req
 // table kernel the others.
 chsim_status run_amplitudes_xpl(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, uint32_t xpl,
                                 hipStream_t s) {
+  RecordUse use(ctx);
   std::vector<AmpReq> mf, tb;
   for (const auto& r : reqs) {
     Instance& I = ctx->inst[r.inst];
     const bool fits = I.n <= kAmpMfmaMaxN && (I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile <= 0x7FFFFFFFull;
     if (fits) {
-      chsim_status st = ensure_mfma_prep(I, s);
+      chsim_status st = ensure_mfma_prep(ctx, I, s);
       if (st) return st;
     }
-    (fits && !I.mfma_off ? mf : tb).push_back(r);
+    (fits && I.mfma_ready ? mf : tb).push_back(r);
   }
-  if (!mf.empty()) {
-    chsim_status st = run_amplitudes_mfma(ctx, mf, fp32c, s);
-    if (st) return st;
+  chsim_status st = mf.empty() ? CHSIM_OK : run_amplitudes_mfma(ctx, mf, fp32c, s);
+  if (!st && !tb.empty()) st = run_amplitudes_table(ctx, tb, fp32c, xpl, s);
+  // Out of memory beside the records of this call: without them.
+  if (st == CHSIM_ENOMEM && release_records(ctx, true)) {
+    g_err.clear();
+    for (const auto& r : reqs) ctx->inst[r.inst].mfma_off = true;
+    st = run_amplitudes_table(ctx, reqs, fp32c, xpl, s);
   }
-  return tb.empty() ? CHSIM_OK : run_amplitudes_table(ctx, tb, fp32c, xpl, s);
+  return st == CHSIM_ENOMEM ? CHSIM_EDEVICE : st;
 }
 
 // The table kernel's plan, uploaded if it differs from the last one, and launch.
 chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, uint32_t xpl,
                                 hipStream_t s) {
   for (const auto& r : reqs) {
-    chsim_status st = ensure_amp_prep(ctx->inst[r.inst], s);
+    chsim_status st = ensure_amp_prep(ctx, ctx->inst[r.inst], s);
     if (st) return st;
   }
   std::vector<AmpRequestPlan> plan;
@@ -1269,7 +1347,7 @@ chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& req
   const std::vector<uint32_t>& nr = ctx->amp_nr;
   size_t part = 0;
   for (size_t q = 0; q < reqs.size(); ++q) part += (size_t)nr[q] * reqs[q].n_x;
-  HIP_TRY(ctx->partial.ensure(part));
+  GROW_TRY(grow(ctx, ctx->partial, part));
   std::vector<AmpInst> insts(reqs.size());
   std::vector<uint64_t> prefix(reqs.size() + 1, 0);
   size_t off = 0;
@@ -1293,10 +1371,11 @@ chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& req
   const bool same = insts.size() == ctx->amp_key.size() && ctx->amp_key_xpl == xpl &&
                     std::memcmp(insts.data(), ctx->amp_key.data(), insts.size() * sizeof(AmpInst)) == 0;
   if (!same) {
-    HIP_TRY(ctx->amp_insts.ensure(insts.size()));
-    HIP_TRY(ctx->amp_items.ensure(items.size()));
-    HIP_TRY(ctx->amp_prefix.ensure(prefix.size()));
-    HIP_TRY(ctx->amp_counter.ensure(1));
+    ctx->amp_key.clear();  // invalid until the plan is whole
+    GROW_TRY(grow(ctx, ctx->amp_insts, insts.size()));
+    GROW_TRY(grow(ctx, ctx->amp_items, items.size()));
+    GROW_TRY(grow(ctx, ctx->amp_prefix, prefix.size()));
+    GROW_TRY(grow(ctx, ctx->amp_counter, 1));
     HIP_TRY(hipMemcpyAsync(ctx->amp_insts.p, insts.data(), insts.size() * sizeof(AmpInst),
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(ctx->amp_items.p, items.data(), items.size() * sizeof(AmpItem),
@@ -1372,12 +1451,12 @@ chsim_status chsim_amplitudes(chsim_ctx* ctx, uint32_t inst, const uint64_t* x, 
   st = ensure_materialised(I, s);
   if (st) return st;
   const uint64_t* xd;
-  st = stage_in(ctx->xbuf, x, n_x, dev, s, &xd);
+  st = stage_in(ctx, ctx->xbuf, x, n_x, dev, s, &xd);
   if (st) return st;
   double2* outd;
   if (dev) outd = reinterpret_cast<double2*>(out);
   else {
-    HIP_TRY(ctx->out.ensure(n_x));
+    HIP_TRY(grow(ctx, ctx->out, n_x));
     outd = ctx->out.p;
   }
   st = run_amplitudes(ctx, {AmpReq{inst, xd, (uint32_t)n_x, outd}}, (flags & CHSIM_FP32C) != 0, s);
@@ -1419,8 +1498,8 @@ chsim_status chsim_amplitudes_batch(chsim_ctx* ctx, const chsim_amp_request* req
     for (size_t q = 0; q < n_req; ++q)
       rq[q] = AmpReq{reqs[q].inst, reqs[q].x, (uint32_t)reqs[q].n_x, reinterpret_cast<double2*>(reqs[q].out)};
   } else {
-    HIP_TRY(ctx->xbuf.ensure(total));
-    HIP_TRY(ctx->out.ensure(total));
+    HIP_TRY(grow(ctx, ctx->xbuf, total));
+    HIP_TRY(grow(ctx, ctx->out, total));
     size_t off = 0;
     for (size_t q = 0; q < n_req; ++q) {
       HIP_TRY(hipMemcpyAsync(ctx->xbuf.p + off, reqs[q].x, reqs[q].n_x * sizeof(uint64_t),
@@ -1498,6 +1577,9 @@ chsim_status chsim_amplitudes_noalloc(chsim_ctx* ctx, uint32_t inst, const uint6
   return CHSIM_OK;
 }
 
+// Fewest terms of a pass over them.
+constexpr uint64_t kInnerMinPass = 4096;
+
 chsim_status chsim_inner_products(chsim_ctx* ctx, uint32_t inst, const uint64_t* A_off,
                                   const uint8_t* A_diag, size_t L, double* overlap, double* eta,
                                   double* eta_mean, uint32_t flags, void* stream) {
@@ -1525,7 +1607,7 @@ chsim_status chsim_inner_products(chsim_ctx* ctx, uint32_t inst, const uint64_t*
   st = ensure_materialised(I, s);
   if (st) return st;
   HIP_TRY(hipMemsetAsync(ctx->err.p, 0, sizeof(uint32_t), s));
-  HIP_TRY(ctx->eta_sum.ensure(1));
+  HIP_TRY(grow(ctx, ctx->eta_sum, 1));
   double total = 0.0;
   // Chunks of equatorial states bound the LDS accumulator of the kernel.
   const size_t kChunk = 2048;
@@ -1538,30 +1620,39 @@ chsim_status chsim_inner_products(chsim_ctx* ctx, uint32_t inst, const uint64_t*
       ao = A_off + l0 * n;
       ad = A_diag + l0 * n;
     } else {
-      HIP_TRY(ctx->aoff.ensure((size_t)Lc * n));
-      HIP_TRY(ctx->adiag.ensure((size_t)Lc * n));
+      HIP_TRY(grow(ctx, ctx->aoff, (size_t)Lc * n));
+      HIP_TRY(grow(ctx, ctx->adiag, (size_t)Lc * n));
       HIP_TRY(hipMemcpyAsync(ctx->aoff.p, A_off + l0 * n, (size_t)Lc * n * 8, hipMemcpyHostToDevice, s));
       HIP_TRY(hipMemcpyAsync(ctx->adiag.p, A_diag + l0 * n, (size_t)Lc * n, hipMemcpyHostToDevice, s));
       ao = ctx->aoff.p;
       ad = ctx->adiag.p;
     }
-    const InnerPlan ip = inner_plan(I.view(), Lc);
-    HIP_TRY(ctx->partial.ensure(ip.partial_elems));
-    HIP_TRY(ctx->inner_work.ensure(ip.work_words));
     double2* ovd;
     double* etad;
     if (dev) {
       ovd = reinterpret_cast<double2*>(overlap) + l0;
       if (eta) etad = eta + l0;
       else {
-        HIP_TRY(ctx->eta.ensure(Lc));
+        HIP_TRY(grow(ctx, ctx->eta, Lc));
         etad = ctx->eta.p;
       }
     } else {
-      HIP_TRY(ctx->out.ensure(Lc));
-      HIP_TRY(ctx->eta.ensure(Lc));
+      HIP_TRY(grow(ctx, ctx->out, Lc));
+      HIP_TRY(grow(ctx, ctx->eta, Lc));
       ovd = ctx->out.p;
       etad = ctx->eta.p;
+    }
+    // The records of all terms at once, or of a part of them in turn where they
+    // do not fit (n = 50: 2080 bytes per term).
+    uint64_t pass = I.chi;
+    InnerPlan ip;
+    for (;;) {
+      ip = inner_plan(I.view(), Lc, pass);
+      hipError_t e = grow(ctx, ctx->partial, ip.partial_elems);
+      if (e == hipSuccess) e = grow(ctx, ctx->inner_work, ip.work_words);
+      if (e == hipSuccess) break;
+      if (e != hipErrorOutOfMemory || pass <= kInnerMinPass) HIP_TRY(e);
+      pass = (pass + 1) / 2;
     }
     HIP_TRY(launch_inner(I.view(), ao, ad, Lc, ip, ctx->partial.p, ctx->inner_work.p, ovd, etad, ctx->eta_sum.p,
                          ctx->err.p, s));
@@ -1599,30 +1690,41 @@ chsim_status chsim_inner_products_ch(chsim_ctx* ctx, uint32_t inst, uint32_t bra
   if ((st = ensure_materialised(K, s))) return st;
   if ((st = ensure_materialised(Bt, s))) return st;
   const uint32_t n = K.n, L = (uint32_t)Bt.chi;
-  const InnerChPlan ip = inner_ch_plan(n, K.chi, L);
-  if (ip.pairs || bra_inst == inst) HIP_TRY(ctx->chrec_k.ensure(inner_ch_record_words(n, K.chi)));
-  if (bra_inst == inst) HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
-  const uint64_t* rec_b = ctx->chrec_k.p;
-  if (bra_inst != inst) {
-    HIP_TRY(ctx->chrec_b.ensure(inner_ch_record_words(n, Bt.chi)));
-    HIP_TRY(launch_inner_ch_records(Bt.view(), ctx->chrec_b.p, s));
-    rec_b = ctx->chrec_b.p;
-  }
-  HIP_TRY(ctx->partial.ensure(ip.partial_elems));
-  HIP_TRY(ctx->inner_work.ensure(ip.quad.words));
   double2* ovd;
   if (dev) ovd = reinterpret_cast<double2*>(overlap);
   else {
-    HIP_TRY(ctx->out.ensure(L));
+    HIP_TRY(grow(ctx, ctx->out, L));
     ovd = ctx->out.p;
   }
   double2* totd = nullptr;
   if (total) {
     if (dev) totd = reinterpret_cast<double2*>(total);
     else {
-      HIP_TRY(ctx->chtotal.ensure(1));
+      HIP_TRY(grow(ctx, ctx->chtotal, 1));
       totd = ctx->chtotal.p;
     }
+  }
+  // Without memory for the bit-sliced kernels' records the pair kernel takes all.
+  InnerChPlan ip = inner_ch_plan(n, K.chi, L, true);
+  auto buffers = [&]() {
+    hipError_t e = hipSuccess;
+    if (ip.pairs || bra_inst == inst) e = grow(ctx, ctx->chrec_k, inner_ch_record_words(n, K.chi));
+    if (e == hipSuccess && bra_inst != inst) e = grow(ctx, ctx->chrec_b, inner_ch_record_words(n, Bt.chi));
+    if (e == hipSuccess) e = grow(ctx, ctx->partial, ip.partial_elems);
+    if (e == hipSuccess && ip.sliced) e = grow(ctx, ctx->inner_work, ip.quad.words);
+    return e;
+  };
+  hipError_t e = buffers();
+  if (e == hipErrorOutOfMemory && ip.sliced) {
+    ip = inner_ch_plan(n, K.chi, L, false);
+    e = buffers();
+  }
+  HIP_TRY(e);
+  if (bra_inst == inst) HIP_TRY(launch_inner_ch_records(K.view(), ctx->chrec_k.p, s));
+  const uint64_t* rec_b = ctx->chrec_k.p;
+  if (bra_inst != inst) {
+    HIP_TRY(launch_inner_ch_records(Bt.view(), ctx->chrec_b.p, s));
+    rec_b = ctx->chrec_b.p;
   }
   HIP_TRY(hipMemsetAsync(ctx->err.p, 0, sizeof(uint32_t), s));
   HIP_TRY(launch_inner_ch(K.view(), Bt.view(), ip, ctx->chrec_k.p, rec_b, ctx->inner_work.p, ctx->partial.p, ovd, totd,
@@ -1675,19 +1777,20 @@ chsim_status chsim_metropolis_init(chsim_ctx* ctx, uint32_t inst, uint32_t n_cha
   hipStream_t s = as_stream(stream);
   st = ensure_materialised(I, s);
   if (st) return st;
-  I.n_chain = n_chain;
+  I.n_chain = 0;  // no chains until every buffer is there
   const size_t cells = (size_t)n_chain * I.chi;
   const uint32_t tiles = (uint32_t)((I.chi + kMetroTile - 1) / kMetroTile);
-  if (I.mstate0.ensure(cells) != hipSuccess)
+  if (grow(ctx, I.mstate0, cells) != hipSuccess)
     return fail(CHSIM_ENOMEM, "chain state (%zu words) does not fit", cells);
-  HIP_TRY(I.mpend.ensure(n_chain));
-  HIP_TRY(I.mpmask.ensure(n_chain));
+  HIP_TRY(grow(ctx, I.mpend, n_chain));
+  HIP_TRY(grow(ctx, I.mpmask, n_chain));
   HIP_TRY(hipMemsetAsync(I.mpend.p, 0, n_chain * sizeof(uint32_t), s));
   HIP_TRY(hipMemsetAsync(I.mpmask.p, 0, n_chain * sizeof(uint64_t), s));
-  HIP_TRY(I.mx.ensure(n_chain));
-  HIP_TRY(I.mamp.ensure(n_chain));
-  HIP_TRY(I.mpartial.ensure((size_t)3 * n_chain * tiles));  // three sums per pair of steps
+  HIP_TRY(grow(ctx, I.mx, n_chain));
+  HIP_TRY(grow(ctx, I.mamp, n_chain));
+  HIP_TRY(grow(ctx, I.mpartial, (size_t)3 * n_chain * tiles));  // three sums per pair of steps
   HIP_TRY(hipMemcpyAsync(I.mx.p, x0, n_chain * 8, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
+  I.n_chain = n_chain;
   MetroView mv = metro_view(I);
   HIP_TRY(launch_metro_init(I.view(), mv, s));
   std::vector<double2> a(n_chain);
@@ -1727,23 +1830,23 @@ chsim_status chsim_metropolis_step(chsim_ctx* ctx, uint32_t inst, uint32_t n_ste
   mv.n_steps = n_steps;
   const uint32_t* jd;
   const double* ud;
-  st = stage_in(I.mj, j_stream, cnt, dev, s, &jd);
+  st = stage_in(ctx, I.mj, j_stream, cnt, dev, s, &jd);
   if (st) return st;
-  st = stage_in(I.mu, u_stream, cnt, dev, s, &ud);
+  st = stage_in(ctx, I.mu, u_stream, cnt, dev, s, &ud);
   if (st) return st;
   mv.jstream = jd;
   mv.ustream = ud;
   if (x_trace) {
     if (dev) mv.trace = x_trace;
     else {
-      HIP_TRY(I.mtrace.ensure(cnt));
+      HIP_TRY(grow(ctx, I.mtrace, cnt));
       mv.trace = I.mtrace.p;
     }
   }
   if (accepted) {
     if (dev) mv.accepted = accepted;
     else {
-      HIP_TRY(I.macc.ensure(cnt));
+      HIP_TRY(grow(ctx, I.macc, cnt));
       mv.accepted = I.macc.p;
     }
   }
@@ -1799,7 +1902,7 @@ chsim_status chsim_sample_terms(chsim_ctx* ctx, uint32_t inst, size_t count, con
   st = ensure_materialised(I, nullptr);
   if (st) return st;
   DevBuf<uint64_t> buf;
-  HIP_TRY(buf.ensure(3 * count));
+  HIP_TRY(grow(ctx, buf, 3 * count));
   HIP_TRY(hipMemcpy(buf.p, alpha, count * 8, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(buf.p + count, flips, count * 8, hipMemcpyHostToDevice));
   hipError_t e = launch_sample(I.view(), buf.p, buf.p + count, buf.p + 2 * count, (uint32_t)count, nullptr);
@@ -1906,7 +2009,7 @@ chsim_status chsim_set_terms(chsim_ctx* ctx, uint32_t inst, uint64_t first, uint
   HIP_TRY(hipMemcpy(I.s.p + first, s, count * 8, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(I.omega.p + first, omega, count, hipMemcpyHostToDevice));
   HIP_TRY(hipMemcpy(I.b.p + first, b, count * 16, hipMemcpyHostToDevice));
-  I.amp_ready = I.mfma_ready = false;
+  I.terms_changed();
   return CHSIM_OK;
 }
 
@@ -1920,7 +2023,7 @@ chsim_status chsim_validate(chsim_ctx* ctx, uint32_t inst, uint64_t first, uint6
   HIP_TRY(hipSetDevice(ctx->device));
   st = ensure_materialised(I, nullptr);
   if (st) return st;
-  HIP_TRY(ctx->vcheck.ensure(3));
+  HIP_TRY(grow(ctx, ctx->vcheck, 3));
   HIP_TRY(launch_validate(I.view(), first, count, ctx->vcheck.p, nullptr));
   unsigned long long h[3] = {0ull, ~0ull, 0ull};
   HIP_TRY(hipMemcpy(h, ctx->vcheck.p, sizeof h, hipMemcpyDeviceToHost));
@@ -2149,7 +2252,7 @@ chsim_status run_projection(chsim_ctx* ctx, uint32_t inst, const ProjGates& P, v
   I.drop_chains();
   HIP_TRY(hipMemsetAsync(ctx->err.p, 0, sizeof(uint32_t), s));
   HIP_TRY(launch_project(I.view(), P, ctx->err.p, s));
-  I.amp_ready = I.mfma_ready = false;
+  I.terms_changed();
   return check_err_flag(ctx, s, "projection");
 }
 
@@ -2220,7 +2323,7 @@ chsim_status chsim_terms_copy(chsim_ctx* ctx, uint32_t src_inst, uint32_t dst_in
   D.drop_chains();
   HIP_TRY(launch_terms_copy(A.view(), D.view(), A.n_slot == D.n_slot, s));
   D.at_zero = false;
-  D.amp_ready = D.mfma_ready = false;
+  D.terms_changed();
   return CHSIM_OK;
 }
 
@@ -2351,6 +2454,9 @@ namespace {
 template <typename T>
 hipError_t mlp_alloc(chsim_mlp* m, T** p, size_t count) {
   hipError_t e = hipMalloc((void**)p, std::max<size_t>(count, 1) * sizeof(T));
+  if (e == hipErrorOutOfMemory && release_records(m->ctx, false))
+    e = hipMalloc((void**)p, std::max<size_t>(count, 1) * sizeof(T));
+  (void)hipGetLastError();
   if (e == hipSuccess) m->owned.push_back((void*)*p);
   return e;
 }
@@ -2364,20 +2470,19 @@ hipError_t mlp_alloc(chsim_mlp* m, T** p, size_t count) {
 // from the caches and 48; n = 12, chi = 4000: 31 and 29).
 constexpr uint32_t kLearnedPrepSteps = 8, kLearnedChains = 16, kLearnedSmallN = 24;
 
-chsim_status plan_learned_amps(Instance& I, uint32_t n_steps, hipStream_t s, LearnedAmps* out, bool* use) {
+chsim_status plan_learned_amps(chsim_ctx* ctx, Instance& I, uint32_t n_steps, hipStream_t s, LearnedAmps* out, bool* use) {
   *use = false;
   if (I.n > kAmpMfmaMaxN || I.mfma_off || !(I.mfma_ready || n_steps >= kLearnedPrepSteps)) return CHSIM_OK;
   if (I.n_chain < kLearnedChains && I.n > kLearnedSmallN) return CHSIM_OK;
-  chsim_status st = ensure_mfma_prep(I, s);
+  chsim_status st = ensure_mfma_prep(ctx, I, s);
   if (st || I.mfma_off) return st;
   std::vector<AmpItem> items;
   std::vector<uint32_t> tpr, rows;
   uint32_t n_split = 0;
   amp_mfma_plan({AmpRequestPlan{I.n, I.n_chain, I.chi}}, items, &n_split, tpr, rows);
-  if (I.lsums.ensure((size_t)rows[0] * I.n_chain) == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    return CHSIM_OK;
-  }
+  hipError_t e = grow(ctx, I.lsums, (size_t)rows[0] * I.n_chain);
+  if (e == hipErrorOutOfMemory) return CHSIM_OK;
+  HIP_TRY(e);
   AmpMfmaInst a;
   std::memset(&a, 0, sizeof a);
   a.rec = I.mrec.p;
@@ -2396,7 +2501,9 @@ chsim_status plan_learned_amps(Instance& I, uint32_t n_steps, hipStream_t s, Lea
   std::memcpy(words.data() + w_inst, items.data(), w_items * 8);
   if (words != I.lplan_h) {
     I.lplan_h.clear();
-    HIP_TRY(I.lplan.ensure(words.size()));
+    e = grow(ctx, I.lplan, words.size());
+    if (e == hipErrorOutOfMemory) return CHSIM_OK;
+    HIP_TRY(e);
     HIP_TRY(hipMemcpyAsync(I.lplan.p, words.data(), words.size() * 8, hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
     I.lplan_h = std::move(words);
@@ -2445,7 +2552,7 @@ chsim_status chsim_mlp_create(chsim_ctx* ctx, uint32_t n, uint32_t hidden, uint3
             mlp_alloc(m, &d.gf, B * n) == hipSuccess && mlp_alloc(m, &d.dz1, B * H) == hipSuccess &&
             mlp_alloc(m, &d.dz2, B * H) == hipSuccess && mlp_alloc(m, &d.gb, B * n) == hipSuccess &&
             mlp_alloc(m, &d.gz1, B * H) == hipSuccess && mlp_alloc(m, &d.gz2, B * H) == hipSuccess &&
-            m->loss.ensure(1) == hipSuccess;
+            grow(ctx, m->loss, 1) == hipSuccess;
   if (!ok) {
     delete m;
     return fail(CHSIM_ENOMEM, "network buffers do not fit");
@@ -2502,7 +2609,7 @@ chsim_status chsim_mlp_forward(chsim_mlp* mlp, const uint64_t* x, uint32_t batch
   HIP_TRY(hipSetDevice(mlp->ctx->device));
   hipStream_t s = as_stream(stream);
   const uint64_t* xd;
-  chsim_status st = stage_in(mlp->xin, x, batch, dev, s, &xd);
+  chsim_status st = stage_in(mlp->ctx, mlp->xin, x, batch, dev, s, &xd);
   if (st) return st;
   float* out = dev ? logits : d.logits;
   HIP_TRY(mlp_forward(d, xd, batch, out, s));
@@ -2524,9 +2631,9 @@ chsim_status chsim_mlp_loss_grad(chsim_mlp* mlp, const uint64_t* x, const uint64
   HIP_TRY(hipSetDevice(mlp->ctx->device));
   hipStream_t s = as_stream(stream);
   const uint64_t *xd, *td;
-  chsim_status st = stage_in(mlp->xin, x, batch, false, s, &xd);
+  chsim_status st = stage_in(mlp->ctx, mlp->xin, x, batch, false, s, &xd);
   if (st) return st;
-  st = stage_in(mlp->tin, target, batch, false, s, &td);
+  st = stage_in(mlp->ctx, mlp->tin, target, batch, false, s, &td);
   if (st) return st;
   HIP_TRY(mlp_loss_grad(d, xd, td, batch, mlp->loss.p, true, false, 0.f, s));
   double lsum = 0.0;
@@ -2548,9 +2655,9 @@ chsim_status chsim_mlp_train(chsim_mlp* mlp, const uint64_t* x, const uint64_t* 
   HIP_TRY(hipSetDevice(mlp->ctx->device));
   hipStream_t s = as_stream(stream);
   const uint64_t *xd, *td;
-  chsim_status st = stage_in(mlp->xin, x, count, dev, s, &xd);
+  chsim_status st = stage_in(mlp->ctx, mlp->xin, x, count, dev, s, &xd);
   if (st) return st;
-  st = stage_in(mlp->tin, target, count, dev, s, &td);
+  st = stage_in(mlp->ctx, mlp->tin, target, count, dev, s, &td);
   if (st) return st;
   for (uint32_t e = 0; e < epochs; ++e) {
     for (uint64_t b0 = 0; b0 < count; b0 += batch) {
@@ -2605,18 +2712,18 @@ chsim_status chsim_metropolis_step_learned(chsim_ctx* ctx, uint32_t inst, chsim_
   lv.pi_max = args->pi_max;
   const double *umd, *ubd, *ud;
   const uint32_t* jd;
-  if ((st = stage_in(I.lumix, args->u_mix, cnt, dev, s, &umd))) return st;
-  if ((st = stage_in(I.lj, args->j, cnt, dev, s, &jd))) return st;
-  if ((st = stage_in(I.lubits, args->u_bits, cnt * I.n, dev, s, &ubd))) return st;
-  if ((st = stage_in(I.mu, args->u, cnt, dev, s, &ud))) return st;
+  if ((st = stage_in(ctx, I.lumix, args->u_mix, cnt, dev, s, &umd))) return st;
+  if ((st = stage_in(ctx, I.lj, args->j, cnt, dev, s, &jd))) return st;
+  if ((st = stage_in(ctx, I.lubits, args->u_bits, cnt * I.n, dev, s, &ubd))) return st;
+  if ((st = stage_in(ctx, I.mu, args->u, cnt, dev, s, &ud))) return st;
   lv.u_mix = umd;
   lv.j = jd;
   lv.u_bits = ubd;
   lv.u = ud;
-  HIP_TRY(I.ly.ensure(C));
-  HIP_TRY(I.lmask.ensure(C));
-  HIP_TRY(I.logit_x.ensure(C * I.n));
-  HIP_TRY(I.logit_y.ensure(C * I.n));
+  HIP_TRY(grow(ctx, I.ly, C));
+  HIP_TRY(grow(ctx, I.lmask, C));
+  HIP_TRY(grow(ctx, I.logit_x, C * I.n));
+  HIP_TRY(grow(ctx, I.logit_y, C * I.n));
   lv.x = I.mx.p;
   lv.y = I.ly.p;
   lv.mask = I.lmask.p;
@@ -2626,27 +2733,28 @@ chsim_status chsim_metropolis_step_learned(chsim_ctx* ctx, uint32_t inst, chsim_
   if (x_trace) {
     if (dev) mv.trace = x_trace;
     else {
-      HIP_TRY(I.mtrace.ensure(cnt));
+      HIP_TRY(grow(ctx, I.mtrace, cnt));
       mv.trace = I.mtrace.p;
     }
   }
   if (accepted) {
     if (dev) mv.accepted = accepted;
     else {
-      HIP_TRY(I.macc.ensure(cnt));
+      HIP_TRY(grow(ctx, I.macc, cnt));
       mv.accepted = I.macc.p;
     }
   }
   if (n_flips) {
     if (dev) lv.n_flips = n_flips;
     else {
-      HIP_TRY(I.lflips.ensure(cnt));
+      HIP_TRY(grow(ctx, I.lflips, cnt));
       lv.n_flips = I.lflips.p;
     }
   }
   LearnedAmps amps;
+  RecordUse use(ctx);
   bool on_mfma = false;
-  if ((st = plan_learned_amps(I, n_steps, s, &amps, &on_mfma))) return st;
+  if ((st = plan_learned_amps(ctx, I, n_steps, s, &amps, &on_mfma))) return st;
   // The network's output at the current states.
   HIP_TRY(mlp_forward(mlp->d, I.mx.p, I.n_chain, I.logit_x.p, s));
   HIP_TRY(launch_learned_steps(I.view(), mv, lv, mlp->d, on_mfma ? &amps : nullptr, n_steps, s));

@@ -122,12 +122,12 @@ __device__ __forceinline__ uint64_t gather_bits(uint64_t x, uint64_t m) {
   return out;
 }
 
-__global__ __launch_bounds__(256) void k_inner_prep(TermsView Tv, uint64_t* __restrict__ rec) {
+__global__ __launch_bounds__(256) void k_inner_prep(TermsView Tv, uint64_t count, uint64_t* __restrict__ rec) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u;
   const uint32_t n = Tv.n;
   const bool act = lane < n;
   const uint64_t term = (uint64_t)blockIdx.x * kWaves + uniform32(tid >> 6);
-  if (term >= Tv.chi) return;  // whole wave
+  if (term >= count) return;  // whole wave
   const uint64_t chi = Tv.chi;
   const uint64_t off = (uint64_t)lane * chi + term;
   const uint64_t F = act ? Tv.F[off] : 0ull;
@@ -425,7 +425,8 @@ __host__ __device__ constexpr uint32_t inner_srow_bytes(uint32_t n) { return (n 
 // index maps XCD-aware: workgroups are dealt to the 8 XCDs in turn, and the
 // batches of one term group are consecutive on one XCD, so a term's record
 // is read from HBM once per XCD-resident group rather than once per batch.
-__global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, const uint64_t* __restrict__ rec,
+__global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, uint64_t count, bool add,
+                                                    const uint64_t* __restrict__ rec,
                                                     const uint64_t* __restrict__ at,
                                                     const uint64_t* __restrict__ planes, uint32_t L,
                                                     uint32_t Lp, uint32_t n_groups, uint32_t n_batches,
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, const uint6
   void* const srow = reinterpret_cast<unsigned char*>(lds_w) + inner_gtab_bytes();
   double accr = 0.0, acci = 0.0;
   uint32_t bad = 0;
-  for (uint64_t term = group; term < Tv.chi; term += n_groups) {
+  for (uint64_t term = group; term < count; term += n_groups) {
     const uint64_t* r = rec + term * R;
     const uint64_t v = uniform64(Tv.v[term]);
     const uint32_t omega = uniform32(Tv.omega[term]);
@@ -466,7 +467,11 @@ __global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, const uint6
                       accr, acci);
   }
   if (bad && lane == 0u) atomicOr(err, 1u);
-  if (l < L) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
+  if (l < L) {
+    double2* const p = partial + ((uint64_t)group * L + l);
+    const double2 before = add ? *p : make_double2(0.0, 0.0);
+    *p = make_double2(before.x + accr, before.y + acci);
+  }
 }
 
 // overlap_l = the sum of the groups' partials in FP64, in a fixed order: a
@@ -530,34 +535,36 @@ uint32_t term_groups(uint64_t chi, uint32_t n_batches) {
   return g >= 8u ? g & ~7u : g;
 }
 
-InnerPlan inner_plan(const TermsView& T, uint32_t L) {
+InnerPlan inner_plan(const TermsView& T, uint32_t L, uint64_t pass) {
   InnerPlan P;
-  P.quad = quad_plan(T.n, T.chi, L, 0);
+  P.pass = pass;
+  P.quad = quad_plan(T.n, pass, L, 0);
   P.wide = T.n > kQuadMaxVars;
   P.Lp = (L + 63u) / 64u * 64u;
   P.n_batches = P.Lp / 64u;
-  P.n_groups = term_groups(T.chi, P.n_batches);
+  P.n_groups = term_groups(pass, P.n_batches);
   P.partial_elems = (size_t)(P.quad.rows + (P.wide ? P.n_groups : 0u)) * L;
   P.work_words = P.quad.words;
-  if (P.wide) P.work_words += (size_t)T.chi * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
+  if (P.wide) P.work_words += (size_t)pass * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
   return P;
 }
 
-// Terms with more than kQuadMaxVars variables (n > kQuadMaxVars).
-static hipError_t launch_wide(const TermsView& T, const uint64_t* Aoff, const uint8_t* Adiag, uint32_t L,
-                              const InnerPlan& P, double2* partial, uint64_t* work, uint32_t* err, hipStream_t st) {
+// Terms with more than kQuadMaxVars variables (n > kQuadMaxVars) among `count`.
+static hipError_t launch_wide(const TermsView& T, uint64_t count, bool add, const uint64_t* Aoff, const uint8_t* Adiag,
+                              uint32_t L, const InnerPlan& P, double2* partial, uint64_t* work, uint32_t* err,
+                              hipStream_t st) {
   const uint32_t n = T.n;
   uint64_t* rec = work;
-  uint64_t* at = rec + (size_t)T.chi * inner_rec_words(n);
+  uint64_t* at = rec + (size_t)P.pass * inner_rec_words(n);
   uint64_t* planes = at + (size_t)n * P.Lp;
-  hipLaunchKernelGGL(k_inner_prep, dim3((uint32_t)((T.chi + kWaves - 1) / kWaves)), dim3(64 * kWaves), 0, st,
-                     T, rec);
-  hipLaunchKernelGGL(k_inner_atrans, dim3((P.Lp + 255u) / 256u), dim3(256), 0, st, Aoff, Adiag, n, L, P.Lp,
-                     at, planes);
+  hipLaunchKernelGGL(k_inner_prep, dim3((uint32_t)((count + kWaves - 1) / kWaves)), dim3(64 * kWaves), 0, st, T, count,
+                     rec);
+  if (!add)
+    hipLaunchKernelGGL(k_inner_atrans, dim3((P.Lp + 255u) / 256u), dim3(256), 0, st, Aoff, Adiag, n, L, P.Lp, at, planes);
   const size_t sm = (size_t)inner_gtab_bytes() + inner_srow_bytes(n);
   const dim3 grid(P.n_groups * P.n_batches);
-  hipLaunchKernelGGL(k_inner_pairs, grid, dim3(64), sm, st, T, rec, at, planes, L, P.Lp, P.n_groups, P.n_batches, partial,
-                     err);
+  hipLaunchKernelGGL(k_inner_pairs, grid, dim3(64), sm, st, T, count, add, rec, at, planes, L, P.Lp, P.n_groups,
+                     P.n_batches, partial, err);
   return hipGetLastError();
 }
 
@@ -566,12 +573,24 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
                         double* eta, double* eta_sum, uint32_t* err, hipStream_t st) {
   const uint32_t n = T.n;
   hipError_t e;
-  if ((e = launch_quad_prep(T, P.quad, work, st)) != hipSuccess) return e;
   if ((e = launch_quad_equatorial(Aoff, Adiag, n, L, P.quad, work, st)) != hipSuccess) return e;
-  if ((e = launch_quad_pairs(T, L, P.quad, work, partial, st)) != hipSuccess) return e;
-  if (P.wide && (e = launch_wide(T, Aoff, Adiag, L, P, partial + (size_t)P.quad.rows * L, work + P.quad.words, err,
-                                 st)) != hipSuccess)
-    return e;
+  for (uint64_t first = 0; first < T.chi; first += P.pass) {
+    TermsView V = T;  // the pass's terms, in the store's strides
+    V.F += first;
+    V.G += first;
+    V.M += first;
+    V.gamma += first;
+    V.v += first;
+    V.s += first;
+    V.omega += first;
+    V.b += first;
+    const uint64_t count = std::min(P.pass, T.chi - first);
+    if ((e = launch_quad_prep(V, count, P.quad, work, st)) != hipSuccess) return e;
+    if ((e = launch_quad_pairs(V, count, L, P.quad, work, partial, first > 0, st)) != hipSuccess) return e;
+    if (P.wide && (e = launch_wide(V, count, first > 0, Aoff, Adiag, L, P, partial + (size_t)P.quad.rows * L,
+                                   work + P.quad.words, err, st)) != hipSuccess)
+      return e;
+  }
   const uint32_t rows = P.quad.rows + (P.wide ? P.n_groups : 0u);
   hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, rows, L, n, overlap, eta);
   e = hipGetLastError();

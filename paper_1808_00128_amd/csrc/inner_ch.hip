@@ -536,9 +536,9 @@ static uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
   return (uint32_t)(g >= 8 ? g & ~7ull : g);
 }
 
-InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L) {
+InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L, bool sliced) {
   InnerChPlan P{};
-  P.sliced = L >= sliced_min_bras(n);
+  P.sliced = sliced && L >= sliced_min_bras(n);
   if (P.sliced) P.quad = quad_plan(n, chi_k, L, std::min(n, kSlicedSlots));
   P.pairs = !P.sliced || 2u * n > kQuadMaxVars;
   P.groups = P.pairs ? inner_ch_groups(chi_k, L) : 0u;
@@ -552,9 +552,9 @@ hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerC
   const uint32_t n = K.n, L = (uint32_t)Tb.chi;
   hipError_t e;
   if (P.sliced) {
-    if ((e = launch_quad_prep(K, P.quad, work, st)) != hipSuccess) return e;
+    if ((e = launch_quad_prep(K, K.chi, P.quad, work, st)) != hipSuccess) return e;
     if ((e = launch_quad_bras(Tb, rec_b, chrec_words(n), L, P.quad, work, st)) != hipSuccess) return e;
-    if ((e = launch_quad_pairs(K, L, P.quad, work, partial, st)) != hipSuccess) return e;
+    if ((e = launch_quad_pairs(K, K.chi, L, P.quad, work, partial, false, st)) != hipSuccess) return e;
   }
   if (P.pairs) {
     const uint32_t bra_blocks = (L + kCHWaves - 1) / kCHWaves;

@@ -297,6 +297,7 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
 // and `rows` rows of L partial sums.
 constexpr uint32_t kQuadMaxVars = 59;
 struct QuadPlan {
+  uint64_t chi;  // terms of a pass: a set can be taken in several
   uint32_t n_batches, slots, ne1, rows;
   bool many;  // more than one launch by size: the counts are kept
   size_t rec_words, slice_words, words;
@@ -307,24 +308,28 @@ QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots);
 constexpr uint32_t kQuadStatWords = 64u * 16u;
 __host__ __device__ constexpr uint32_t quad_stat_slot(uint32_t block) { return (block % 64u) * 16u; }
 uint32_t* quad_stat(const QuadPlan& P, uint64_t* work);
-hipError_t launch_quad_prep(const TermsView& T, const QuadPlan& P, uint64_t* work, hipStream_t st);
+// The first `count` terms of T (whose arrays may start at a later term of the
+// store), count <= P.chi.
+hipError_t launch_quad_prep(const TermsView& T, uint64_t count, const QuadPlan& P, uint64_t* work, hipStream_t st);
 hipError_t launch_quad_equatorial(const uint64_t* Aoff, const uint8_t* Adiag, uint32_t n, uint32_t L,
                                   const QuadPlan& P, uint64_t* work, hipStream_t st);
 hipError_t launch_quad_bras(const TermsView& Tb, const uint64_t* chrec, uint32_t chrec_words, uint32_t L,
                             const QuadPlan& P, uint64_t* work, hipStream_t st);
-hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, uint64_t* work, double2* partial,
-                             hipStream_t st);
+// add: to the partial sums that are there.
+hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, const QuadPlan& P, uint64_t* work,
+                             double2* partial, bool add, hipStream_t st);
 
 // Inner products with equatorial states: L states in batches of 64 (Lp =
 // L rounded up), partial sums per term group, and a device workspace of
 // work_words 8-byte words (per-term records and A rearranged by state).
 struct InnerPlan {
+  uint64_t pass;  // terms taken at a time (their records share the workspace)
   QuadPlan quad;
   bool wide;  // terms with more variables than the bit-sliced kernels take are possible
   uint32_t Lp, n_batches, n_groups;
   size_t partial_elems, work_words;
 };
-InnerPlan inner_plan(const TermsView& T, uint32_t L);
+InnerPlan inner_plan(const TermsView& T, uint32_t L, uint64_t pass);
 hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t* Adiag, uint32_t L,
                         const InnerPlan& P, double2* partial, uint64_t* work, double2* overlap,
                         double* eta, double* eta_sum, uint32_t* err, hipStream_t st);
@@ -342,7 +347,9 @@ struct InnerChPlan {
   uint32_t groups;
   size_t partial_elems;
 };
-InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L);
+// sliced: the bit-sliced kernels where they are the faster ones (they need room for
+// their own records).
+InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L, bool sliced);
 // rec_b: the bras' records; rec_k: room for the kets' (plan.pairs), written here
 // where the pair kernel has kets to take, or rec_b if the sets are the same.
 hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerChPlan& P, uint64_t* rec_k,

@@ -105,13 +105,13 @@ constexpr uint32_t kPrepWaves = 4;
 
 // One wave per term, lane = row, then lane = column.  Counts 0, 1: max |v|, max
 // (64 - |v|), unless stat is null (one launch takes every term).
-__global__ __launch_bounds__(64 * kPrepWaves) void k_quad_prep(TermsView T, uint64_t* __restrict__ rec,
+__global__ __launch_bounds__(64 * kPrepWaves) void k_quad_prep(TermsView T, uint64_t count, uint64_t* __restrict__ rec,
                                                                uint32_t* __restrict__ stat) {
   __shared__ uint64_t cols[kPrepWaves][64];
   __shared__ uint32_t pivs[kPrepWaves][64];
   const uint32_t lane = threadIdx.x & 63u, wave = uniform32(threadIdx.x >> 6);
   const uint64_t term = (uint64_t)blockIdx.x * kPrepWaves + wave;
-  if (term >= T.chi) return;  // whole waves
+  if (term >= count) return;  // whole waves
   const uint32_t n = T.n;
   const bool act = lane < n;
   const uint64_t off = (uint64_t)lane * T.chi + term;
@@ -308,6 +308,7 @@ struct QuadArgs {
   double2* partial;  // this launch's rows
   uint32_t n, ne1, slots, L, n_waves, n_batches;
   uint32_t nc_lo, nc_hi;  // the variables (without the extra one) this launch takes
+  bool add;               // to the partial sums that are there
   bool many;              // there are other launches: the counts tell whether this one has any terms
 };
 
@@ -586,7 +587,11 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   }
 #pragma unroll
   for (uint32_t u = 0; u < 2u; ++u)
-    if (l0 + u < A.L) A.partial[(size_t)row0 * A.L + l0 + u] = make_double2(ar[u], ai[u]);
+    if (l0 + u < A.L) {
+      double2* const p = A.partial + ((size_t)row0 * A.L + l0 + u);
+      const double2 before = A.add ? *p : make_double2(0.0, 0.0);
+      *p = make_double2(before.x + ar[u], before.y + ai[u]);
+    }
 }
 
 }  // namespace
@@ -609,6 +614,7 @@ uint32_t class_waves(const QuadClass& c, uint64_t chi, uint32_t n_batches) {
 
 QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots) {
   QuadPlan P{};
+  P.chi = chi;
   P.n_batches = (L + 127u) / 128u;
   P.slots = slots;
   P.ne1 = n + slots + 1u;
@@ -625,15 +631,15 @@ uint32_t* quad_stat(const QuadPlan& P, uint64_t* work) {
   return reinterpret_cast<uint32_t*>(work + P.rec_words + P.slice_words + (size_t)P.n_batches * 64u);
 }
 
-hipError_t launch_quad_prep(const TermsView& T, const QuadPlan& P, uint64_t* work, hipStream_t st) {
+hipError_t launch_quad_prep(const TermsView& T, uint64_t count, const QuadPlan& P, uint64_t* work, hipStream_t st) {
   const bool counts = P.many || P.slots;
   if (counts) {
     const hipError_t e = hipMemsetAsync(quad_stat(P, work), 0, kQuadStatWords * sizeof(uint32_t), st);
     if (e != hipSuccess) return e;
   }
-  const uint64_t blocks = (T.chi + kPrepWaves - 1) / kPrepWaves;
+  const uint64_t blocks = (count + kPrepWaves - 1) / kPrepWaves;
   if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)blocks), dim3(64 * kPrepWaves), 0, st, T, work,
+  hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)blocks), dim3(64 * kPrepWaves), 0, st, T, count, work,
                      counts ? quad_stat(P, work) : nullptr);
   return hipGetLastError();
 }
@@ -656,12 +662,13 @@ hipError_t launch_quad_bras(const TermsView& Tb, const uint64_t* chrec, uint32_t
   return hipGetLastError();
 }
 
-hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, uint64_t* work, double2* partial,
-                             hipStream_t st) {
+hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, const QuadPlan& P, uint64_t* work,
+                             double2* partial, bool add, hipStream_t st) {
   QuadArgs A{};
   A.rec = work;
   A.b = T.b;
-  A.chi = T.chi;
+  A.chi = count;
+  A.add = add;
   A.sl = reinterpret_cast<const uint32_t*>(work + P.rec_words);
   A.info = reinterpret_cast<const uint32_t*>(work + P.rec_words + P.slice_words);
   A.stat = quad_stat(P, work);
@@ -678,7 +685,7 @@ hipError_t launch_quad_pairs(const TermsView& T, uint32_t L, const QuadPlan& P, 
     if (c.nc_lo > T.n + P.slots) break;
     A.nc_lo = c.nc_lo;
     A.nc_hi = c.nc_hi;
-    A.n_waves = class_waves(c, T.chi, P.n_batches);
+    A.n_waves = class_waves(c, P.chi, P.n_batches);
     const dim3 grid(P.n_batches * (A.n_waves / c.nw)), block(64u * c.nw);
     void (*const fn)(QuadArgs) = k == 0   ? k_quad_pairs<2, 28, 8, 4>
                                  : k == 1 ? k_quad_pairs<3, 48, 8, 2>
