@@ -602,44 +602,52 @@ __global__ __launch_bounds__(256, 2) void k_amp_mfma(const AmpMfmaInst* __restri
 }
 
 // out[i] = the sum of the partial rows of string i in row order (FP64): a
-// 256-thread block takes 8 strings (over all requests) and 32 slices of
+// 256-thread block takes 8 strings (over all requests) at a time and 32 slices of
 // their rows; the slice sums are added in slice order.
 constexpr uint32_t kRedX = 8, kRedSlices = 32;
+// Blocks of a launch.  A grid of 2^32 threads (2^27 strings) or more is cut short
+// without an error, so past 2^26 strings the blocks go round.
+constexpr uint32_t kRedBlocks = 1u << 23;
 __global__ __launch_bounds__(256) void k_amp_mfma_reduce(const AmpMfmaInst* __restrict__ insts,
                                                          const uint64_t* __restrict__ prefix, uint32_t n_inst) {
   __shared__ double2 part[kRedSlices][kRedX];
   const uint32_t xl = threadIdx.x % kRedX, sl = threadIdx.x / kRedX;
-  const uint64_t g = (uint64_t)blockIdx.x * kRedX + xl;
-  const bool on = g < prefix[n_inst];
-  uint32_t lo = 0;
-  uint64_t i = 0;
-  double re = 0.0, im = 0.0;
-  if (on) {
-    uint32_t hi = n_inst;
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) / 2;
-      if (prefix[mid] <= g) lo = mid;
-      else hi = mid;
+  const uint64_t total = prefix[n_inst];
+  for (uint64_t g0 = (uint64_t)blockIdx.x * kRedX; g0 < total; g0 += (uint64_t)gridDim.x * kRedX) {
+    const uint64_t g = g0 + xl;
+    const bool on = g < total;
+    uint32_t lo = 0;
+    uint64_t i = 0;
+    double re = 0.0, im = 0.0;
+    if (on) {
+      uint32_t hi = n_inst;
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (prefix[mid] <= g) lo = mid;
+        else hi = mid;
+      }
+      const AmpMfmaInst& I = insts[lo];
+      i = g - prefix[lo];
+      const uint32_t r0 = (uint32_t)((uint64_t)I.rows * sl / kRedSlices);
+      const uint32_t r1 = (uint32_t)((uint64_t)I.rows * (sl + 1) / kRedSlices);
+      for (uint32_t t = r0; t < r1; ++t) {
+        const double2 v = I.partial[(uint64_t)t * I.n_x + i];
+        re += v.x;
+        im += v.y;
+      }
     }
-    const AmpMfmaInst& I = insts[lo];
-    i = g - prefix[lo];
-    const uint32_t r0 = (uint32_t)((uint64_t)I.rows * sl / kRedSlices);
-    const uint32_t r1 = (uint32_t)((uint64_t)I.rows * (sl + 1) / kRedSlices);
-    for (uint32_t t = r0; t < r1; ++t) {
-      const double2 v = I.partial[(uint64_t)t * I.n_x + i];
-      re += v.x;
-      im += v.y;
+    part[sl][xl] = make_double2(re, im);
+    __syncthreads();
+    if (sl == 0 && on) {
+      double sr = 0.0, si = 0.0;
+      for (uint32_t k = 0; k < kRedSlices; ++k) {
+        sr += part[k][xl].x;
+        si += part[k][xl].y;
+      }
+      insts[lo].out[i] = make_double2(sr, si);
     }
+    __syncthreads();  // the slices are read before the next strings' are written
   }
-  part[sl][xl] = make_double2(re, im);
-  __syncthreads();
-  if (sl != 0 || !on) return;
-  double sr = 0.0, si = 0.0;
-  for (uint32_t k = 0; k < kRedSlices; ++k) {
-    sr += part[k][xl].x;
-    si += part[k][xl].y;
-  }
-  insts[lo].out[i] = make_double2(sr, si);
 }
 
 }  // namespace
@@ -689,7 +697,7 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
                            uint64_t total_x, hipStream_t st) {
   const hipError_t e = launch_amp_mfma_sums(insts_d, items_d, n_items, n_split, max_steps, fp32c, st);
   if (e != hipSuccess) return e;
-  const uint32_t blocks = (uint32_t)((total_x + kRedX - 1) / kRedX);
+  const uint32_t blocks = (uint32_t)std::min<uint64_t>((total_x + kRedX - 1) / kRedX, kRedBlocks);
   hipLaunchKernelGGL(k_amp_mfma_reduce, dim3(blocks), dim3(256), 0, st, insts_d, prefix_d, n_inst);
   return hipGetLastError();
 }

@@ -1644,7 +1644,7 @@ chsim_status chsim_inner_products(chsim_ctx* ctx, uint32_t inst, const uint64_t*
     }
     // The records of all terms at once, or of a part of them in turn where they
     // do not fit (n = 50: 2080 bytes per term).
-    uint64_t pass = I.chi;
+    uint64_t pass = std::min(I.chi, kWaveTerms);
     InnerPlan ip;
     for (;;) {
       ip = inner_plan(I.view(), Lc, pass);

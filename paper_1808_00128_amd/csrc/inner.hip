@@ -575,15 +575,7 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
   hipError_t e;
   if ((e = launch_quad_equatorial(Aoff, Adiag, n, L, P.quad, work, st)) != hipSuccess) return e;
   for (uint64_t first = 0; first < T.chi; first += P.pass) {
-    TermsView V = T;  // the pass's terms, in the store's strides
-    V.F += first;
-    V.G += first;
-    V.M += first;
-    V.gamma += first;
-    V.v += first;
-    V.s += first;
-    V.omega += first;
-    V.b += first;
+    const TermsView V = terms_from(T, first);
     const uint64_t count = std::min(P.pass, T.chi - first);
     if ((e = launch_quad_prep(V, count, P.quad, work, st)) != hipSuccess) return e;
     if ((e = launch_quad_pairs(V, count, L, P.quad, work, partial, first > 0, st)) != hipSuccess) return e;

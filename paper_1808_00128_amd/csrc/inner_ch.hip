@@ -63,12 +63,12 @@ __device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat
 // Bs [3n, 4n), Bs colG_i [4n, 5n), Bu colG_i [5n, 6n) (Bu: the strictly
 // upper part of Bs, row q below bit q), then diag(B), glo, x1 = s G^T, s, v,
 // omega.
-__global__ __launch_bounds__(64 * kCHWaves) void k_chrec(TermsView T, uint64_t* __restrict__ rec,
+__global__ __launch_bounds__(64 * kCHWaves) void k_chrec(TermsView T, uint64_t count, uint64_t* __restrict__ rec,
                                                          const uint32_t* __restrict__ stat, uint32_t slots) {
   const uint32_t lane = threadIdx.x & 63u;
   if (stat && pairs_left(stat, slots, lane) == 0u) return;
   const uint64_t term = (uint64_t)blockIdx.x * kCHWaves + uniform32(threadIdx.x >> 6);
-  if (term >= T.chi) return;  // whole waves
+  if (term >= count) return;  // whole waves
   const uint32_t n = T.n;
   const bool act = lane < n;
   const uint64_t off = (uint64_t)lane * T.chi + term;
@@ -517,11 +517,14 @@ size_t inner_ch_record_words(uint32_t n, uint64_t chi) { return (size_t)chi * ch
 
 static hipError_t launch_records(const TermsView& T, uint64_t* rec, const uint32_t* stat, uint32_t slots,
                                  hipStream_t st) {
-  const uint64_t blocks = (T.chi + kCHWaves - 1) / kCHWaves;
-  if (blocks == 0) return hipSuccess;
-  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_chrec, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, T, rec, stat, slots);
-  return hipGetLastError();
+  for (uint64_t first = 0; first < T.chi; first += kWaveTerms) {
+    const uint64_t count = std::min(kWaveTerms, T.chi - first);
+    hipLaunchKernelGGL(k_chrec, dim3((uint32_t)((count + kCHWaves - 1) / kCHWaves)), dim3(64 * kCHWaves), 0, st,
+                       terms_from(T, first), count, rec + first * chrec_words(T.n), stat, slots);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_t st) {

@@ -65,6 +65,24 @@ struct TermsView {
   uint8_t* branch;  // branch[p * chi + a]
 };
 
+// The terms from `first` on, in the store's strides (chi, the row pitch, stays).
+inline TermsView terms_from(TermsView T, uint64_t first) {
+  T.F += first;
+  T.G += first;
+  T.M += first;
+  T.gamma += first;
+  T.v += first;
+  T.s += first;
+  T.omega += first;
+  T.b += first;
+  T.branch += first;
+  return T;
+}
+
+// Terms per launch of the kernels with a wave per term: a grid of 2^32 threads or
+// more is cut short without an error.
+constexpr uint64_t kWaveTerms = 1ull << 25;
+
 // Metropolis chain state (one instance).
 struct MetroView {
   uint32_t n_chain;

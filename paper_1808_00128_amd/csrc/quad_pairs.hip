@@ -637,11 +637,15 @@ hipError_t launch_quad_prep(const TermsView& T, uint64_t count, const QuadPlan& 
     const hipError_t e = hipMemsetAsync(quad_stat(P, work), 0, kQuadStatWords * sizeof(uint32_t), st);
     if (e != hipSuccess) return e;
   }
-  const uint64_t blocks = (count + kPrepWaves - 1) / kPrepWaves;
-  if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)blocks), dim3(64 * kPrepWaves), 0, st, T, count, work,
-                     counts ? quad_stat(P, work) : nullptr);
-  return hipGetLastError();
+  for (uint64_t first = 0; first < count; first += kWaveTerms) {
+    const uint64_t c = std::min(kWaveTerms, count - first);
+    hipLaunchKernelGGL(k_quad_prep, dim3((uint32_t)((c + kPrepWaves - 1) / kPrepWaves)), dim3(64 * kPrepWaves), 0, st,
+                       terms_from(T, first), c, work + first * rec_layout(T.n).words,
+                       counts ? quad_stat(P, work) : nullptr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_quad_equatorial(const uint64_t* Aoff, const uint8_t* Adiag, uint32_t n, uint32_t L,
