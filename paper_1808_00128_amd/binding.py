@@ -305,8 +305,9 @@ class Context:
         _check(lib().chsim_set_tuning(self._h, inst, CHSIM_TUNE_PREFIX_SHARE, int(mode)))
 
     def set_amp_strings(self, value):
-        """Bitstrings per work item of the amplitude kernel (256 or 512; 0 =
-        default; -1 = autotune at the next amplitude call), for the context."""
+        """Bitstrings per work item of the table amplitude kernel (n > 60, and
+        amplitudes_noalloc; 256 or 512; 0 = default; -1 = autotune at the next
+        amplitude call), for the context."""
         _check(lib().chsim_set_tuning(self._h, 0, CHSIM_TUNE_AMP_STRINGS, int(value)))
 
     def amp_strings(self):

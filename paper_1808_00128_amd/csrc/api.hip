@@ -1392,38 +1392,50 @@ chsim_status run_amplitudes_table(chsim_ctx* ctx, const std::vector<AmpReq>& req
   return CHSIM_OK;
 }
 
-// With the autotuner armed, run the call twice per bitstrings-per-lane value
-// (the first run plans and uploads the work items; every run leaves correct
-// outputs), time the second with hipEvents, keep the faster.
+// With the autotuner armed, the table kernel runs the call twice per
+// bitstrings-per-lane value (the first run plans and uploads the work items), the
+// second timed with hipEvents, and the faster is kept; then the call itself, on the
+// kernel that takes it.  The value is the table kernel's alone, which serves n > 60,
+// instances without room for records and the no-allocation call, so that is what
+// is timed also where the matrix cores take the call.  Without memory for it the
+// value stays.
 chsim_status run_amplitudes(chsim_ctx* ctx, const std::vector<AmpReq>& reqs, bool fp32c, hipStream_t s) {
-  if (!ctx->amp_tune) return run_amplitudes_xpl(ctx, reqs, fp32c, ctx->amp_xpl, s);
-  hipEvent_t e0, e1;
-  HIP_TRY(hipEventCreate(&e0));
-  HIP_TRY(hipEventCreate(&e1));
-  uint32_t best = 2;
-  for (uint32_t xpl = 1; xpl <= 2; ++xpl) {
-    chsim_status st = run_amplitudes_xpl(ctx, reqs, fp32c, xpl, s);
+  if (ctx->amp_tune) {
+    ctx->amp_tune = false;
+    hipEvent_t e0, e1;
+    HIP_TRY(hipEventCreate(&e0));
+    HIP_TRY(hipEventCreate(&e1));
+    float ms[2] = {0.f, 0.f};
+    chsim_status st = CHSIM_OK;
+    hipError_t e = hipSuccess;
+    for (uint32_t xpl = 1; xpl <= 2 && !st && e == hipSuccess; ++xpl) {
+      st = run_amplitudes_table(ctx, reqs, fp32c, xpl, s);
+      if (!st && (e = hipEventRecord(e0, s)) == hipSuccess) st = run_amplitudes_table(ctx, reqs, fp32c, xpl, s);
+      if (!st && e == hipSuccess) e = hipEventRecord(e1, s);
+      if (!st && e == hipSuccess) e = hipEventSynchronize(e1);
+      if (!st && e == hipSuccess) e = hipEventElapsedTime(&ms[xpl - 1], e0, e1);
+    }
+    hipEventDestroy(e0);
+    hipEventDestroy(e1);
+    if (st && st != CHSIM_ENOMEM) return st;
+    HIP_TRY(e);
     if (!st) {
-      HIP_TRY(hipEventRecord(e0, s));
-      st = run_amplitudes_xpl(ctx, reqs, fp32c, xpl, s);
+      ctx->amp_tune_ms[0] = ms[0];
+      ctx->amp_tune_ms[1] = ms[1];
+      ctx->amp_xpl = ms[0] < ms[1] ? 1u : 2u;
     }
-    if (st) {
-      hipEventDestroy(e0);
-      hipEventDestroy(e1);
-      return st;
+    g_err.clear();
+    st = run_amplitudes_xpl(ctx, reqs, fp32c, ctx->amp_xpl, s);
+    for (const auto& r : reqs) {  // the table kernel's prologue, where it was only for this
+      Instance& I = ctx->inst[r.inst];
+      if (!I.mfma_ready) continue;
+      I.acrow.release();
+      I.acst.release();
+      I.amp_ready = false;
     }
-    HIP_TRY(hipEventRecord(e1, s));
-    HIP_TRY(hipEventSynchronize(e1));
-    float ms = 0.f;
-    HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-    ctx->amp_tune_ms[xpl - 1] = ms;
+    return st;
   }
-  hipEventDestroy(e0);
-  hipEventDestroy(e1);
-  best = ctx->amp_tune_ms[0] < ctx->amp_tune_ms[1] ? 1u : 2u;
-  ctx->amp_xpl = best;
-  ctx->amp_tune = false;
-  return CHSIM_OK;
+  return run_amplitudes_xpl(ctx, reqs, fp32c, ctx->amp_xpl, s);
 }
 
 chsim_status check_bits(const Instance& I, const uint64_t* x, size_t n_x, size_t req) {
