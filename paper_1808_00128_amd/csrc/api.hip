@@ -97,6 +97,7 @@ int value_of_shape(EvolveShape s) { return s.lanes | (s.cols ? CHSIM_EVOLVE_LDS 
 
 struct Instance {
   uint32_t n = 0, n_slot = 0, mode = 0;
+  uint32_t cus = 256;  // compute units of the device
   uint64_t chi = 0, seed = 0;
   double l1 = 1.0;
   bool at_zero = true;  // every term is |0^n> and the store holds nothing yet
@@ -542,6 +543,8 @@ chsim_status chsim_terms_init(chsim_ctx** out, int device, uint32_t n_inst,
     chsim_status sst = scratch_address(device, &sp);
     if (sst) return sst;
   }
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
   chsim_ctx* ctx = new chsim_ctx();
   ctx->device = device;
   ctx->inst.resize(n_inst);
@@ -558,6 +561,7 @@ chsim_status chsim_terms_init(chsim_ctx** out, int device, uint32_t n_inst,
     I.chi = in.chi;
     I.mode = in.mode;
     I.seed = in.seed;
+    I.cus = (uint32_t)cus;
     chsim_status st = build_slots(I, in);
     if (st != CHSIM_OK) return cleanup(st);
     const size_t rows = (size_t)in.n * in.chi;
@@ -632,9 +636,9 @@ int gate_kind(const DGate& g) {
 // `cap` items on the chip at once runs whole rounds of cap items at full
 // throughput and a last partial round, which is charged like a launch of that
 // many items alone (latency-bound when small).
-double span_us(EvolveShape s, const double cnt[4], double items, uint32_t n) {
+double span_us(const Instance& I, EvolveShape s, const double cnt[4], double items) {
   const GateCost& c = cost_of(s);
-  const double rows = (double)n / 50.0, cap = (double)evolve_capacity(s, n);
+  const double rows = (double)I.n / 50.0, cap = (double)evolve_capacity(s, I.n, I.cus);
   const double lat = s.cols ? 0.25 + 0.75 * rows : 1.0;
   double full = 0.0, rest = items;
   if (cap > 0 && items > cap) {
@@ -655,9 +659,9 @@ double span_us(EvolveShape s, const double cnt[4], double items, uint32_t n) {
 EvolveShape span_shape(const Instance& I, EvolveShape set, const double cnt[4], double items, double* us) {
   const EvolveShape wave = evolve_shape_for(I.n, 64);
   EvolveShape best = set.lanes ? set : evolve_default_shape(I.n);
-  double t = span_us(best, cnt, items, I.n);
+  double t = span_us(I, best, cnt, items);
   auto consider = [&](EvolveShape s) {
-    const double u = span_us(s, cnt, items, I.n);
+    const double u = span_us(I, s, cnt, items);
     if (u < t) {
       t = u;
       best = s;
@@ -782,7 +786,7 @@ void plan_prefix(Instance& I, const std::vector<DGate>& dg, EvolveShape shape) {
     if (j > m) {  // the last span: every term
       const EvolveShape s = last_shape(I, shape, cnt);
       if (lanes) *lanes = value_of_shape(s);
-      return span_us(s, cnt, items, I.n);
+      return span_us(I, s, cnt, items);
     }
     const EvolveShape s = span_shape(I, shape, cnt, items, &t);
     if (lanes) *lanes = value_of_shape(s);

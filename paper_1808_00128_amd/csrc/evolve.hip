@@ -84,11 +84,8 @@ EvolveShape evolve_default_shape(uint32_t n) {
   return s;
 }
 
-uint64_t evolve_capacity(EvolveShape s, uint32_t n) {
+uint64_t evolve_capacity(EvolveShape s, uint32_t n, uint32_t cus) {
   if (!s.cols) return 0u;
-  int dev = 0, cus = 0;
-  hipGetDevice(&dev);
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
   return (uint64_t)cus * 4u * (uint64_t)evolve_cols_waves(s.lanes, evolve_shape_for(n, s.lanes).rows) * 64u /
          (uint64_t)s.lanes;
 }

@@ -118,8 +118,8 @@ struct EvolveShape {
 };
 EvolveShape evolve_shape_for(uint32_t n, int lanes);
 EvolveShape evolve_default_shape(uint32_t n);
-// Items a mapping holds on the chip at once (0: not bounded by LDS).
-uint64_t evolve_capacity(EvolveShape s, uint32_t n);
+// Items a mapping holds on a chip of `cus` compute units at once (0: not bounded).
+uint64_t evolve_capacity(EvolveShape s, uint32_t n, uint32_t cus);
 bool evolve_shape_supported(EvolveShape s, uint32_t n);
 // One evolution launch: count work items (or *count_dev of them, count being
 // the grid's bound); item i starts from |0^n> (from_zero) or from state
