@@ -379,29 +379,50 @@ void merge_diagonal_branches(const Instance& I, const SlotTable& st, std::vector
 // of 50 qubits).  L[S_q] and L[CZ_qr] touch rows q, r of M and gamma through rows
 // q, r of G alone; the passed gates change neither those rows of G nor, since
 // F G^T = I, the phases they give, so the CH form is the same bit for bit.
+//
+// One pass from the end: a slot goes before the first gate after it that stops it
+// (before the slot which that gate belongs to), whose place is kept per qubit.
+// Slots before one gate stand in the order in which moves one at a time, from the
+// last slot on, would leave them.
 void defer_diagonal_slots(std::vector<DGate>& dg) {
-  for (size_t i = dg.size(); i-- > 0;) {
-    if (!(dg[i].cond & kSlotStart)) continue;
-    size_t end = i + 1;  // the slot's gates
-    while (end < dg.size() && (dg[end].cond & kCondApply) && !(dg[end].cond & kSlotStart)) ++end;
-    uint64_t qubits = 0;
-    bool diagonal = true;
-    for (size_t k = i; k < end; ++k) {
-      qubits |= 1ull << dg[k].q;
-      if (dg[k].op == OP_CZ) qubits |= 1ull << dg[k].r;
-      else if (dg[k].op != OP_SLOT_SPOW && dg[k].op != OP_SPOW) diagonal = false;
-    }
-    if (!diagonal) continue;
-    // A stop inside another slot's gates goes back to that slot's start.
-    size_t to = end, k = end;
-    for (; k < dg.size(); ++k) {
+  const uint32_t N = (uint32_t)dg.size(), kNone = UINT32_MAX;
+  std::array<uint32_t, 64> stop;  // per qubit
+  stop.fill(N);
+  std::vector<uint32_t> size(N, 0);  // gates of the slot that starts here (1 for a gate of its own)
+  std::vector<uint32_t> first(N + 1, kNone), last(N + 1, kNone), next(N, kNone);  // slots before a place
+  std::vector<bool> moved(N, false);
+  bool any = false;
+  for (uint32_t i = N, end = N; i-- > 0;) {
+    if ((dg[i].cond & kCondApply) && !(dg[i].cond & kSlotStart)) continue;  // inside a slot
+    size[i] = end - i;
+    bool diagonal = dg[i].cond & kSlotStart;
+    uint32_t to = N;
+    for (uint32_t k = i; k < end && diagonal; ++k) {
       const DGate& g = dg[k];
-      if (!(g.cond & kCondApply) || (g.cond & kSlotStart)) to = k;
-      if ((g.op == OP_H && (qubits >> g.q & 1u)) || (g.op == OP_CX && (qubits >> g.r & 1u))) break;
+      to = std::min(to, stop[g.q]);
+      if (g.op == OP_CZ) to = std::min(to, stop[g.r]);
+      else if (g.op != OP_SLOT_SPOW && g.op != OP_SPOW) diagonal = false;
     }
-    if (k == dg.size()) to = k;
-    if (to > end) std::rotate(dg.begin() + i, dg.begin() + end, dg.begin() + to);
+    if (diagonal) {
+      (first[to] == kNone ? first[to] : next[last[to]]) = i;
+      last[to] = i;
+      moved[i] = any = true;
+    } else {
+      for (uint32_t k = i; k < end; ++k) {
+        if (dg[k].op == OP_H) stop[dg[k].q] = i;
+        else if (dg[k].op == OP_CX) stop[dg[k].r] = i;
+      }
+    }
+    end = i;
   }
+  if (!any) return;
+  std::vector<DGate> out;
+  out.reserve(N);
+  for (uint32_t p = 0; p <= N; ++p) {
+    for (uint32_t k = first[p]; k != kNone; k = next[k]) out.insert(out.end(), dg.begin() + k, dg.begin() + k + size[k]);
+    if (p < N && size[p] && !moved[p]) out.insert(out.end(), dg.begin() + p, dg.begin() + p + size[p]);
+  }
+  dg.swap(out);
 }
 
 chsim_status build_slots(Instance& I, const chsim_instance& in) {
