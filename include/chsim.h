@@ -413,7 +413,7 @@ chsim_status chsim_decompose_ccz(uint32_t a, uint32_t b, uint32_t c, double coef
  * lanes | CHSIM_EVOLVE_LDS with lanes 4, 8 or 16 (lanes * 16 >= n): the columns
  * of every term's tableaux in registers, ceil(n / lanes) per lane.  The default
  * takes, span by span, the fastest of the column mappings and one term per
- * wave by estimate.  -1 =
+ * wave by estimate (n = 1: rows, 4 lanes).  -1 =
  * autotune: the next chsim_apply_clifford that starts from |0^n> times every
  * shape on the real gate list (hipEvents), keeps the fastest, and leaves the
  * same terms any shape would.  Results never depend on the knob.

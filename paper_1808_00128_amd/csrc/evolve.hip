@@ -77,10 +77,11 @@ EvolveShape evolve_shape_for(uint32_t n, int lanes) {
   return s;
 }
 
-// Default: columns in registers, 4 lanes per term.
+// Default: columns in registers, 4 lanes per term.  A single qubit has its row in a
+// register: there is nothing to transpose (65536 terms: 48 µs and 52 by columns).
 EvolveShape evolve_default_shape(uint32_t n) {
   EvolveShape s = evolve_shape_for(n, 4);
-  s.cols = true;
+  s.cols = n > 1u;
   return s;
 }
 
