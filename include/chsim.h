@@ -414,9 +414,9 @@ chsim_status chsim_decompose_ccz(uint32_t a, uint32_t b, uint32_t c, double coef
  * of every term's tableaux in registers, ceil(n / lanes) per lane.  The default
  * takes, span by span, the fastest of the column mappings and one term per
  * wave by estimate (n = 1: rows, 4 lanes).  -1 =
- * autotune: the next chsim_apply_clifford that starts from |0^n> times every
- * shape on the real gate list (hipEvents), keeps the fastest, and leaves the
- * same terms any shape would.  Results never depend on the knob.
+ * autotune: the next chsim_apply_clifford that starts from |0^n> times the
+ * default and every value on the real gate list (hipEvents, after a run of
+ * each), keeps the fastest, and leaves the same terms any would.  Results never depend on the knob.
  * EUNSUPPORTED: no compiled kernel for that value and n. */
 #define CHSIM_TUNE_EVOLVE_LANES 1u
 #define CHSIM_EVOLVE_LDS 0x100
@@ -443,7 +443,8 @@ chsim_status chsim_decompose_ccz(uint32_t a, uint32_t b, uint32_t c, double coef
 #define CHSIM_TUNE_AMP_STRINGS 3u
 chsim_status chsim_set_tuning(chsim_ctx* ctx, uint32_t inst, uint32_t knob, int32_t value);
 
-/* Current value of a knob.  For EVOLVE_LANES, timings_ms[8] receives the
+/* Current value of a knob.  For EVOLVE_LANES (the default reads as its mapping
+ * with 4 lanes, also where the autotuner kept it), timings_ms[8] receives the
  * autotuner's timings in ms for lanes 4, 8, 16, 32, 64 with rows in
  * registers and lanes 4, 8, 16 with columns in registers (0 where not timed); for
  * AMP_STRINGS, timings_ms[0..1] = the autotuner's timings of the table kernel for 256 and 512;
