@@ -506,21 +506,24 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, Metr
       }
     }
     const uint32_t i_end = min(n_mine - i0, 64u);
-    // Two chains per pass: all their cache words are requested before any is
-    // combined (an odd last chain is taken twice and stored once).
-    for (uint32_t k0 = 0; k0 < i_end; k0 += 2u) {
-      uint64_t st[2][kGSub];
+    // Chains k0 .. k0 + CP - 1: all their cache words are requested before any is
+    // combined.
+    auto pass = [&](auto cp, uint32_t k0) {
+      constexpr uint32_t CP = decltype(cp)::value;
+      uint64_t st[CP][kGSub];
 #pragma unroll
-      for (uint32_t h = 0; h < 2u; ++h) {
-        const uint32_t k = min(k0 + h, i_end - 1u);
+      for (uint32_t h = 0; h < CP; ++h) {
+        const uint32_t k = k0 + h;
         const uint64_t* sp = Mv.state + ((uint64_t)(w0 + n_waves * (i0 + k)) * chi + tile0);
 #pragma unroll
         for (uint32_t sb = 0; sb < kGSub; ++sb) st[h][sb] = sp[ao[sb]];
       }
       double sum[12];  // [chain][value][re, im]
 #pragma unroll
-      for (uint32_t h = 0; h < 2u; ++h) {
-        const uint32_t k = min(k0 + h, i_end - 1u);
+      for (uint32_t q = 6u * CP; q < 12u; ++q) sum[q] = 0.0;
+#pragma unroll
+      for (uint32_t h = 0; h < CP; ++h) {
+        const uint32_t k = k0 + h;
         Word u[kGSub];
         uint32_t mu[kGSub];
 #pragma unroll
@@ -532,7 +535,7 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, Metr
 #pragma unroll
         for (uint32_t q = 0; q < kMetroWin; ++q)
           if ((pm >> q) & 1u) flip(u, mu, q, (uint32_t)__builtin_amdgcn_readlane((int)m_js[q], (int)k));
-        if (write && k == k0 + h) {
+        if (write) {
           uint64_t* sp = Mv.state + ((uint64_t)(w0 + n_waves * (i0 + k)) * chi + tile0);
 #pragma unroll
           for (uint32_t sb = 0; sb < kGSub; ++sb) {
@@ -562,7 +565,7 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, Metr
           sm[2] = sm[3] = sm[4] = sm[5] = 0.0;
         }
       }
-      if (nprop == 0u) continue;
+      if (nprop == 0u) return;
       // 12 sums over 64 lanes: r[k] holds sums 4 k, 4 k + 2, 4 k + 1, 4 k + 3 in its rows.
       double r[3];
 #pragma unroll
@@ -572,12 +575,16 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, Metr
       const double x = kk == 0u ? r[0] : kk == 1u ? r[1] : r[2];
       const uint32_t f = 4u * kk + ((rr & 1u) << 1 | rr >> 1);  // [chain][value][re, im]
       const uint32_t h = f >= 6u ? 1u : 0u, g = f - 6u * h;
-      if (kk < 3u && k0 + h < i_end && (g < 2u || nprop == 2u)) {
+      if (kk < 3u && h < CP && (g < 2u || nprop == 2u)) {
         const uint32_t ch = w0 + n_waves * (i0 + k0 + h);
         double* const out = reinterpret_cast<double*>(Mv.partial + (g >> 1) * plane + (size_t)ch * Mv.n_tiles + blockIdx.x);
         out[g & 1u] = x;
       }
-    }
+    };
+    // Two chains per pass, an odd last one alone.
+    uint32_t k0 = 0;
+    for (; k0 + 1u < i_end; k0 += 2u) pass(std::integral_constant<uint32_t, 2>{}, k0);
+    if (k0 < i_end) pass(std::integral_constant<uint32_t, 1>{}, k0);
   }
 }
 
