@@ -161,8 +161,13 @@ struct Instance {
   DevBuf<uint8_t> macc;
   // learned chain
   DevBuf<uint64_t> ly, lmask;
-  DevBuf<uint64_t> lplan;           // plan of the proposals' amplitudes, and the same on the host
-  std::vector<uint64_t> lplan_h;
+  // Plan of the proposals' amplitudes: the request on the device and as uploaded,
+  // its items, and the number of chains it is for (0: none).
+  DevBuf<AmpMfmaInst> lplan;
+  DevBuf<AmpItem> litems;
+  AmpMfmaInst lreq;
+  LearnedAmps lamps;
+  uint32_t lplan_chains = 0;
   DevBuf<double2> lsums;
   DevBuf<float> logit_x, logit_y;
   DevBuf<double> lumix, lubits;
@@ -211,7 +216,7 @@ struct Instance {
     plan_slot.release(); plan_width.release(); plan_count.release();
     mstate0.release(); mpmask.release(); mx.release(); mtrace.release();
     mpend.release(); mj.release(); mamp.release(); mpartial.release(); mu.release(); macc.release();
-    lplan.release(); lplan_h.clear(); lsums.release();
+    lplan.release(); litems.release(); lplan_chains = 0; lsums.release();
     ly.release(); lmask.release(); logit_x.release(); logit_y.release(); lumix.release();
     lubits.release(); lj.release(); lflips.release();
   }
@@ -2515,57 +2520,69 @@ hipError_t mlp_alloc(chsim_mlp* m, T** p, size_t count) {
 
 // Learned steps take <y|psi> of the proposals from the matrix-core amplitude
 // kernel (n = 50, chi = 2^18, 64 chains: 45 µs per step; the chains' caches, with
-// every row read and each chain's cached words, 103) where its records are there,
-// or the call has steps enough to pay for them (8 x 58 µs against 250 µs).  The
-// kernel's cost is that of 64 strings and grows with n^2; with few chains the rows
-// are read sooner (n = 50, chi = 10^5, 8 chains, per step with the network 43 µs
-// from the caches and 48; n = 12, chi = 4000: 31 and 29).
+// every row read and each chain's cached words, 103) in calls with steps enough to
+// pay for its records (8 x 58 µs against 250 µs).  The kernel's cost is that of 64
+// strings (32 above 50 qubits) and grows with n^2; with few chains the rows are read
+// sooner (n = 50, chi = 10^5, 8 chains, per step with the network 43 µs from the
+// caches and 48; n = 12, chi = 4000: 31 and 29).  A shorter call takes it where the
+// records are there and the chains fill its strings, since the caches are read once
+// in any case, at the call's end (one step, n = 24, chi = 2^18, 33 chains 186 µs and
+// 217 from the caches; n = 20, chi = 2^16, 2 chains 154 and 139; n = 56, chi = 2^18, 33
+// chains 297 and 277, 64 chains 309 and 333).
 constexpr uint32_t kLearnedPrepSteps = 8, kLearnedChains = 16, kLearnedSmallN = 24;
 
-chsim_status plan_learned_amps(chsim_ctx* ctx, Instance& I, uint32_t n_steps, hipStream_t s, LearnedAmps* out, bool* use) {
+bool learned_on_mfma(const Instance& I, uint32_t n_steps) {
+  if (I.n > kAmpMfmaMaxN || I.mfma_off) return false;
+  if (n_steps < kLearnedPrepSteps) return I.mfma_ready && I.n_chain >= (I.n <= 50u ? 32u : 64u);
+  return I.n_chain >= kLearnedChains || I.n <= kLearnedSmallN;
+}
+
+chsim_status plan_learned_amps(chsim_ctx* ctx, Instance& I, uint32_t n_steps, hipStream_t s, LearnedAmps* out,
+                               bool* use) {
   *use = false;
-  if (I.n > kAmpMfmaMaxN || I.mfma_off || !(I.mfma_ready || n_steps >= kLearnedPrepSteps)) return CHSIM_OK;
-  if (I.n_chain < kLearnedChains && I.n > kLearnedSmallN) return CHSIM_OK;
+  if (!learned_on_mfma(I, n_steps)) return CHSIM_OK;
   chsim_status st = ensure_mfma_prep(ctx, I, s);
   if (st || I.mfma_off) return st;
-  std::vector<AmpItem> items;
-  std::vector<uint32_t> tpr, rows;
-  uint32_t n_split = 0;
-  amp_mfma_plan({AmpRequestPlan{I.n, I.n_chain, I.chi}}, items, &n_split, tpr, rows);
-  hipError_t e = grow(ctx, I.lsums, (size_t)rows[0] * I.n_chain);
-  if (e == hipErrorOutOfMemory) return CHSIM_OK;
-  HIP_TRY(e);
-  AmpMfmaInst a;
-  std::memset(&a, 0, sizeof a);
-  a.rec = I.mrec.p;
-  a.cond = I.mcond.p;
-  a.x = I.ly.p;
-  a.partial = I.lsums.p;
-  a.n = I.n;
-  a.steps = amp_mfma_steps(I.n);
-  a.tiles = (uint32_t)((I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile);
-  a.n_x = I.n_chain;
-  a.tiles_per_range = tpr[0];
-  a.rows = rows[0];
-  const size_t w_inst = (sizeof a / 8 + 1) & ~(size_t)1, w_items = items.size() * sizeof(AmpItem) / 8;  // items: 16 bytes
-  std::vector<uint64_t> words(w_inst + w_items, 0);
-  std::memcpy(words.data(), &a, sizeof a);
-  std::memcpy(words.data() + w_inst, items.data(), w_items * 8);
-  if (words != I.lplan_h) {
-    I.lplan_h.clear();
-    e = grow(ctx, I.lplan, words.size());
+  // The items depend on the number of chains alone (n and chi do not change).
+  if (I.lplan_chains != I.n_chain) {
+    I.lplan_chains = 0;  // invalid until the plan is whole
+    std::vector<AmpItem> items;
+    std::vector<uint32_t> tpr, rows;
+    LearnedAmps& A = I.lamps;
+    amp_mfma_plan({AmpRequestPlan{I.n, I.n_chain, I.chi}}, items, &A.n_split, tpr, rows);
+    AmpMfmaInst& q = I.lreq;
+    std::memset(&q, 0, sizeof q);
+    q.n = I.n;
+    q.steps = amp_mfma_steps(I.n);
+    q.tiles = (uint32_t)((I.chi + kAmpMfmaTile - 1) / kAmpMfmaTile);
+    q.n_x = I.n_chain;
+    q.tiles_per_range = tpr[0];
+    q.rows = rows[0];
+    hipError_t e = grow(ctx, I.lsums, (size_t)rows[0] * I.n_chain);
+    if (e == hipSuccess) e = grow(ctx, I.litems, items.size());
+    if (e == hipSuccess) e = grow(ctx, I.lplan, 1);
     if (e == hipErrorOutOfMemory) return CHSIM_OK;
     HIP_TRY(e);
-    HIP_TRY(hipMemcpyAsync(I.lplan.p, words.data(), words.size() * 8, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    I.lplan_h = std::move(words);
+    HIP_TRY(hipMemcpyAsync(I.litems.p, items.data(), items.size() * sizeof(AmpItem), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));  // the host vector dies with this call
+    A.n_items = (uint32_t)items.size();
+    A.steps = q.steps;
+    A.rows = q.rows;
+    I.lplan_chains = I.n_chain;
   }
-  out->inst = reinterpret_cast<const AmpMfmaInst*>(I.lplan.p);
-  out->items = reinterpret_cast<const AmpItem*>(I.lplan.p + w_inst);
-  out->n_items = (uint32_t)items.size();
-  out->n_split = n_split;
-  out->steps = a.steps;
-  out->rows = rows[0];
+  AmpMfmaInst q = I.lreq;
+  q.rec = I.mrec.p;
+  q.cond = I.mcond.p;
+  q.x = I.ly.p;
+  q.partial = I.lsums.p;
+  if (std::memcmp(&q, &I.lreq, sizeof q) != 0) {
+    HIP_TRY(hipMemcpyAsync(I.lplan.p, &q, sizeof q, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    I.lreq = q;
+  }
+  *out = I.lamps;
+  out->inst = I.lplan.p;
+  out->items = I.litems.p;
   out->sums = I.lsums.p;
   *use = true;
   return CHSIM_OK;
