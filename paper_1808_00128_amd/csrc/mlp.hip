@@ -52,8 +52,10 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 //   EPI_BIAS_RELU: z = acc + bias[j]; Cf = z; Cb = bf16(max(z, 0)).
 //   EPI_BIAS: Cf = acc + bias[j]  (no activation; logits).
 //   EPI_MASK: v = acc * (mask[i][j] > 0); Cf = v; Cb = bf16(v).
-//   EPI_BCE: l = acc + bias[j]; Cf = l, and the loss and its gradient (bce_value).
-// An operand can be the features s_j = 1 - 2 x_j of the bits of x (xa, xb).
+//   kTileBce: l = acc + bias[j]; Cf = l, and the loss and its gradient (bce_value).
+// An operand can be the features s_j = 1 - 2 x_j of the bits of x: a product of its
+// own per form (kTile*), since the plain ones would carry the registers of the others
+// along (56 against 80: 4000 x 512 x 512 in 33 and 44 µs).
 //
 // 32 x 32 output tile per 256-thread workgroup (2 x 2 waves, one 16 x 16
 // MFMA tile each), K staged 64 at a time through LDS (four MFMAs per wave per
@@ -64,7 +66,8 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 // sums in a fixed order before the epilogue, so results do not depend on
 // scheduling.
 // ---------------------------------------------------------------------------
-enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS = 2, EPI_MASK = 3, EPI_BCE = 4 };
+enum { kTilePlain = 0, kTileXA = 1, kTileXB = 2, kTileBce = 3 };
+enum { EPI_STORE = 0, EPI_BIAS_RELU = 1, EPI_BIAS = 2, EPI_MASK = 3 };
 
 // Small batches (inference in the chain, up to kFusedMaxBatch rows) take one
 // fused kernel for the whole network instead of features + three products.
@@ -87,14 +90,13 @@ struct GemmArgs {
   int ldc;
   int kc;             // K extent of one split (multiple of kGK)
   float* part;        // [splits][M][N] partial sums when split
-  const uint64_t* xa; // A(i, k) = feature k of x[i], if not null
-  const uint64_t* xb; // B(k, j) = feature j of x[k], if not null
-  // EPI_BCE
+  const uint64_t* x;  // kTileXA: A(i, k) = feature k of x[i]; kTileXB: B(k, j) = feature j of x[k]
+  // kTileBce
   const uint64_t* t;
   float* gf;
   uint16_t* gb;
   double* loss;
-  double* clear;      // set to zero, if not null (a loss that a later product adds to)
+  double* clear;      // kTileXA: set to zero, if not null (a loss that a later product adds to)
 };
 
 // s_j = 1 - 2 x_j as BF16.
@@ -150,17 +152,19 @@ __device__ __forceinline__ void stage_index(int q, bool k_fast, int& i, int& k) 
   }
 }
 
+// kX: no operand in memory but the features of x, by row (1) or by k (2).
+template <int kX>
 __device__ __forceinline__ void stage_load(const uint16_t* __restrict__ P, int64_t s_row, int64_t s_k,
                                            int rows, int r0, int k0, int kend, bool k_fast,
-                                           const uint64_t* __restrict__ x, bool x_by_k, uint16_t (&v)[8]) {
+                                           const uint64_t* __restrict__ x, uint16_t (&v)[8]) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     int i, k;
     stage_index(q, k_fast, i, k);
     const int gi = r0 + i, gk = k0 + k;
     const bool in = gi < rows && gk < kend;
-    if (x)
-      v[q] = in ? (x_by_k ? feature(x[gk], gi) : feature(x[gi], gk)) : (uint16_t)0;
+    if constexpr (kX != 0)
+      v[q] = in ? (kX == 2 ? feature(x[gk], gi) : feature(x[gi], gk)) : (uint16_t)0;
     else
       v[q] = in ? P[(int64_t)gi * s_row + (int64_t)gk * s_k] : (uint16_t)0;
   }
@@ -187,20 +191,27 @@ __device__ __forceinline__ void block_loss(double lv, double* loss) {
   if (threadIdx.x == 0) atomicAdd(loss, part[0]);
 }
 
+struct GemmLds {
+  alignas(16) uint16_t A[kGT][kGRow];  // [m][k]
+  alignas(16) uint16_t B[kGT][kGRow];  // [n][k]
+};
+
 // Tile (bx, by) of the product, K split bz of nz (nz > 1: to the partial sums).
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz, int nz) {
-  __shared__ __align__(16) uint16_t As[kGT][kGRow];  // [m][k]
-  __shared__ __align__(16) uint16_t Bs[kGT][kGRow];  // [n][k]
+template <int kTile>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, GemmLds& S, int bx, int by, int bz, int nz) {
+  constexpr int kXA = kTile == kTileXA ? 1 : 0, kXB = kTile == kTileXB ? 2 : 0;
+  auto& As = S.A;
+  auto& Bs = S.B;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int m0 = bx * kGT, n0 = by * kGT;
   const int kbeg = bz * g.kc;
   const int kend = min(g.K, kbeg + g.kc);
   const bool a_kf = g.sak == 1, b_kf = g.sbk == 1;
-  if (g.clear && bx + by + bz == 0 && tid == 0) *g.clear = 0.0;
+  if (kTile == kTileXA && g.clear && bx + by + bz == 0 && tid == 0) *g.clear = 0.0;
   uint16_t va[8], vb[8];
-  stage_load(g.A, g.sai, g.sak, g.M, m0, kbeg, kend, a_kf, g.xa, false, va);
-  stage_load(g.B, g.sbj, g.sbk, g.N, n0, kbeg, kend, b_kf, g.xb, true, vb);
+  stage_load<kXA>(g.A, g.sai, g.sak, g.M, m0, kbeg, kend, a_kf, g.x, va);
+  stage_load<kXB>(g.B, g.sbj, g.sbk, g.N, n0, kbeg, kend, b_kf, g.x, vb);
   // 16x16x32 operands: lane l holds A[l % 16][k] and B[k][l % 16] for the
   // eight k = 8 (l / 16) .. +7 of each 32-wide step (the same k for both, so
   // the contraction does not depend on their order inside the instruction);
@@ -213,8 +224,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
     stage_store(Bs, b_kf, vb);
     __syncthreads();
     if (k0 + kGK < kend) {
-      stage_load(g.A, g.sai, g.sak, g.M, m0, k0 + kGK, kend, a_kf, g.xa, false, va);
-      stage_load(g.B, g.sbj, g.sbk, g.N, n0, k0 + kGK, kend, b_kf, g.xb, true, vb);
+      stage_load<kXA>(g.A, g.sai, g.sak, g.M, m0, k0 + kGK, kend, a_kf, g.x, va);
+      stage_load<kXB>(g.B, g.sbj, g.sbk, g.N, n0, k0 + kGK, kend, b_kf, g.x, vb);
     }
 #pragma unroll
     for (int kk = 0; kk < kGK; kk += 32) {
@@ -224,7 +235,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
     }
   }
   const int col = n0 + wn * 16 + (lane & 15);
-  if (g.epi == EPI_BCE) {
+  if constexpr (kTile == kTileBce) {
     double lv = 0.0;
     for (int r = 0; r < 4; ++r) {
       const int row = m0 + wm * 16 + (lane >> 4) * 4 + r;
@@ -232,28 +243,29 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
       const int64_t o = (int64_t)row * g.ldc + col;
       const float l = acc[r] + g.bias[col];
       float gv;
-      lv += bce_value(l, (g.t[row] >> col) & 1ull, (uint32_t)(g.M * g.N), gv);
+      lv += bce_value(l, (g.t[row] >> col) & 1ull, (uint32_t)g.M * (uint32_t)g.N, gv);
       g.Cf[o] = l;
       g.gf[o] = gv;
       g.gb[o] = f2bf(gv);
     }
     block_loss(lv, g.loss);
-    return;
-  }
-  for (int r = 0; r < 4; ++r) {
-    const int row = m0 + wm * 16 + (lane >> 4) * 4 + r;
-    if (row >= g.M || col >= g.N) continue;
-    if (nz == 1)
-      gemm_epilogue(g, row, col, acc[r]);
-    else
-      g.part[((int64_t)bz * g.M + row) * g.N + col] = acc[r];
+  } else {
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm * 16 + (lane >> 4) * 4 + r;
+      if (row >= g.M || col >= g.N) continue;
+      if (nz == 1)
+        gemm_epilogue(g, row, col, acc[r]);
+      else
+        g.part[((int64_t)bz * g.M + row) * g.N + col] = acc[r];
+    }
   }
 }
 
+template <int kTile>
 __global__ __launch_bounds__(256) void k_gemm_bf16(GemmArgs g) {
-  gemm_tile(g, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
+  __shared__ GemmLds S;
+  gemm_tile<kTile>(g, S, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z);
 }
-
 
 // Sum of the K-split partials in split order, then the epilogue.
 __global__ __launch_bounds__(256) void k_gemm_splitk(GemmArgs g, int splits) {
@@ -280,11 +292,12 @@ static int gemm_splits(GemmArgs& g, const MLPDev& d) {
   return (n_kt + kt_per - 1) / kt_per;
 }
 
+template <int kTile = kTilePlain>
 static hipError_t gemm(GemmArgs g, const MLPDev& d, hipStream_t st) {
   const int bm = (g.M + kGT - 1) / kGT, bn = (g.N + kGT - 1) / kGT;
   const int splits = gemm_splits(g, d);
   g.part = d.part;
-  hipLaunchKernelGGL(k_gemm_bf16, dim3(bm, bn, splits), dim3(256), 0, st, g);
+  hipLaunchKernelGGL(k_gemm_bf16<kTile>, dim3(bm, bn, splits), dim3(256), 0, st, g);
   if (splits > 1) {
     const int64_t mn = (int64_t)g.M * g.N;
     hipLaunchKernelGGL(k_gemm_splitk, dim3((uint32_t)((mn + 255) / 256)), dim3(256), 0, st, g, splits);
@@ -343,6 +356,7 @@ __device__ __forceinline__ void colsum_tile(const float* __restrict__ d, uint32_
 }
 
 __global__ __launch_bounds__(256) void k_grad_parts(GradGroup G) {
+  __shared__ GemmLds S;
   uint32_t b = blockIdx.x;
   int k = 0;
   while (k < 5 && b >= G.first[k + 1]) ++k;
@@ -350,7 +364,9 @@ __global__ __launch_bounds__(256) void k_grad_parts(GradGroup G) {
   if (k < 3) {
     const GemmArgs& g = G.g[k];
     const uint32_t bm = (uint32_t)(g.M + kGT - 1) / kGT, bn = (uint32_t)(g.N + kGT - 1) / kGT;
-    gemm_tile(g, (int)(b % bm), (int)(b / bm % bn), (int)(b / (bm * bn)), G.splits[k]);
+    const int bx = (int)(b % bm), by = (int)(b / bm % bn), bz = (int)(b / (bm * bn));
+    if (k == 2) gemm_tile<kTileXB>(g, S, bx, by, bz, G.splits[k]);
+    else gemm_tile<kTilePlain>(g, S, bx, by, bz, G.splits[k]);
   } else {
     const uint32_t bx = (G.N[k - 3] + 63u) / 64u;
     colsum_tile(G.d[k - 3], G.B, G.N[k - 3], G.R, b % bx, b / bx, G.cpart[k - 3]);
@@ -422,15 +438,14 @@ static hipError_t forward_products(MLPDev& d, const uint64_t* x, uint32_t B, flo
   const int n = (int)L.n, H = (int)L.H;
   GemmArgs g{};
   // z1 = a0 W1^T + b1, a1 = bf16(relu(z1)), a0 the features
-  g.xa = x; g.sai = n; g.sak = 1;
+  g.x = x; g.sai = n; g.sak = 1;
   g.clear = clear;
   g.B = d.wb + L.wb_W1(); g.sbk = 1; g.sbj = n;
   g.M = (int)B; g.N = H; g.K = n; g.epi = EPI_BIAS_RELU; g.bias = d.p + L.off_b1();
   g.Cf = d.z1; g.Cb = d.a1; g.ldc = H;
-  hipError_t e = gemm(g, d, st);
+  hipError_t e = gemm<kTileXA>(g, d, st);
   if (e != hipSuccess) return e;
   // z2 = a1 W2^T + b2, a2 = bf16(relu(z2))
-  g.xa = nullptr;
   g.clear = nullptr;
   g.A = d.a1; g.sai = H; g.sak = 1;
   g.B = d.wb + L.wb_W2(); g.sbk = 1; g.sbj = H;
@@ -442,8 +457,9 @@ static hipError_t forward_products(MLPDev& d, const uint64_t* x, uint32_t B, flo
   g.N = n; g.K = H; g.epi = EPI_BIAS; g.bias = d.p + L.off_b3(); g.Cf = logits; g.Cb = nullptr;
   g.ldc = n;
   if (bce && gemm_splits(g, d) == 1) {
-    g.epi = EPI_BCE; g.t = bce->t; g.gf = bce->gf; g.gb = bce->gb; g.loss = bce->loss;
+    g.t = bce->t; g.gf = bce->gf; g.gb = bce->gb; g.loss = bce->loss;
     bce_done = true;
+    return gemm<kTileBce>(g, d, st);
   }
   return gemm(g, d, st);
 }
@@ -499,7 +515,7 @@ hipError_t mlp_loss_grad(MLPDev& d, const uint64_t* x, const uint64_t* t, uint32
   g.M = H; g.N = H; g.Cf = G + L.off_W2(); g.ldc = H;
   q.g[1] = g;
   // dW1[H][n] = gz1^T a0
-  g.A = d.gz1; g.sai = 1; g.sak = H; g.B = nullptr; g.xb = x; g.sbk = n; g.sbj = 1;
+  g.A = d.gz1; g.sai = 1; g.sak = H; g.x = x; g.sbk = n; g.sbj = 1;
   g.M = H; g.N = n; g.Cf = G + L.off_W1(); g.ldc = n;
   q.g[2] = g;
   q.d[0] = d.gf; q.d[1] = d.dz2; q.d[2] = d.dz1;
