@@ -707,6 +707,7 @@ void amp_mfma_plan(const std::vector<AmpRequestPlan>& reqs, std::vector<AmpItem>
   // A tile against one workgroup's strings costs its MFMA steps plus about
   // half as much as 14 steps for the sums; an item also builds its feature
   // operands, worth about 6 tiles.
+  constexpr uint64_t kSplitTiles = 128;
   const size_t R = reqs.size();
   std::vector<uint64_t> tiles(R), chunks(R);
   std::vector<uint32_t> per_wg(R);
@@ -720,7 +721,11 @@ void amp_mfma_plan(const std::vector<AmpRequestPlan>& reqs, std::vector<AmpItem>
     // workgroup that shares them would leave half of its waves idle (calls at
     // n = 50, chi = 2^18: 64 strings 45 µs split and 65 shared, 128 strings 57 and
     // 65; n = 20, chi = 10^5: 17 and 28, 19 and 28; n = 57: equal, bound by the records).
-    split[q] = reqs[q].n_x <= 2u * str;
+    // With few tiles a call is latency alone, and staged weights arrive sooner than
+    // those a wave reads for itself (33 strings, calls in µs, split and shared: chi = 300
+    // n = 24 41.7 and 40.6, n = 60 46.9 and 43.5; chi = 3000 42.9 and 41.5, 46.7 and 44.3; chi =
+    // 10000 43.2 and 44.5, 47.7 and 48.4).
+    split[q] = reqs[q].n_x <= 2u * str && tiles[q] >= kSplitTiles;
     per_wg[q] = split[q] ? str : str * kWaves;
     chunks[q] = (reqs[q].n_x + per_wg[q] - 1) / per_wg[q];
     tcost[q] = (amp_mfma_steps(reqs[q].n) + 8.0) * (str == 64u ? 2.0 : 1.0);
