@@ -25,8 +25,8 @@
 // The paper states the O(n^3) cost and defers this method to earlier work.
 //
 // Mapping.  From a few bras on, and for forms of at most kQuadMaxVars variables, the
-// bit-sliced kernels take the pairs, a bra's equations as further variables (n = 40,
-// chi = 2^16, 256 bras: 3.9 ms, one wave per pair 26.6).  Below and beyond: a
+// bit-sliced kernels take the pairs, a bra's equations as further variables (whole
+// calls in quad_pairs.hip, the rule at QuadRule).  Below and beyond: a
 // prologue writes a record per term (one wave per term, lane =
 // row): the columns and rows of G, the columns of F, the rows of Bs and a few
 // words.  The pair kernel runs one wave per (bra state, group of ket terms),
@@ -42,21 +42,23 @@ namespace chsim {
 namespace {
 
 constexpr int kCHWaves = 4;
-// Bra states from which the bit-sliced kernels take over: their cost is that of 128
-// states and grows with the form's size, where a wave per pair costs its share per bra
-// (16 bras: n = 20, chi = 3000: 909 µs and 215; n = 40, chi = 20000: 1808 and 991;
-// n = 46, chi = 30000: 3153 and about 3050, with 24 bras 4136 and 3056).
-constexpr uint32_t sliced_min_bras(uint32_t n) { return n <= 28u ? 8u : n <= 44u ? 12u : 20u; }
 constexpr uint32_t kSlicedSlots = 32;  // constraints held per bra; more go to the pair kernel
 
 __host__ __device__ constexpr uint32_t chrec_words(uint32_t n) { return 6u * n + 6u; }
 
 // 1 + the constraints of the bras (a large number if they are more than the slots),
-// or zero when every ket's form fits the bit-sliced kernels.
-__device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat, uint32_t slots, uint32_t lane) {
+// or zero when the bit-sliced kernels take every ket.
+__device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat, const QuadRule& rule, uint32_t slots,
+                                               uint32_t lane) {
   uint32_t w = quad_stat_max(stat, 2u, lane);
   if (w > slots) w = 1u << 20;
-  return quad_stat_max(stat, 0u, lane) + w <= kQuadMaxVars ? 0u : w + 1u;
+  const uint32_t most = quad_stat_max(stat, 0u, lane) + w, least = 64u - quad_stat_max(stat, 1u, lane) + w;
+  bool all = most <= kQuadMaxVars;
+  for (uint32_t k = 0; k < 3u; ++k) {  // a class's smallest form pays last
+    const uint32_t lo = k ? kQuadClassMax[k - 1u] + 1u : 0u, at = least > lo ? least : lo;
+    if (at <= kQuadClassMax[k] && at <= most) all = all && quad_takes(rule, at, w);
+  }
+  return all ? 0u : w + 1u;
 }
 
 // Record of one term: colG [0, n), rows of G [n, 2n), colF [2n, 3n), rows of
@@ -64,9 +66,10 @@ __device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat
 // upper part of Bs, row q below bit q), then diag(B), glo, x1 = s G^T, s, v,
 // omega.
 __global__ __launch_bounds__(64 * kCHWaves) void k_chrec(TermsView T, uint64_t count, uint64_t* __restrict__ rec,
-                                                         const uint32_t* __restrict__ stat, uint32_t slots) {
+                                                         const uint32_t* __restrict__ stat, QuadRule rule,
+                                                         uint32_t slots) {
   const uint32_t lane = threadIdx.x & 63u;
-  if (stat && pairs_left(stat, slots, lane) == 0u) return;
+  if (stat && pairs_left(stat, rule, slots, lane) == 0u) return;
   const uint64_t term = (uint64_t)blockIdx.x * kCHWaves + uniform32(threadIdx.x >> 6);
   if (term >= count) return;  // whole waves
   const uint32_t n = T.n;
@@ -230,7 +233,8 @@ __device__ __forceinline__ LiftOut lift_eliminate(Word S, Word kap, Word lam, Wo
 __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
     const uint64_t* __restrict__ rec_k, const double2* __restrict__ b_k, uint64_t chi_k,
     const uint64_t* __restrict__ rec_b, uint32_t L, uint32_t n, uint32_t groups, uint32_t bra_blocks,
-    const uint32_t* __restrict__ stat, uint32_t slots, double2* __restrict__ partial, uint32_t* __restrict__ err) {
+    const uint32_t* __restrict__ stat, QuadRule rule, uint32_t slots, double2* __restrict__ partial,
+    uint32_t* __restrict__ err) {
   const uint32_t lane = threadIdx.x & 63u;
   uint32_t group, bblock;
   if (groups % 8u == 0u) {
@@ -243,8 +247,8 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   }
   const uint32_t l = bblock * kCHWaves + uniform32(threadIdx.x >> 6);
   if (l >= L) return;  // whole waves
-  // Kets whose form fits the bit-sliced kernels are theirs.
-  const uint32_t nw = stat ? pairs_left(stat, slots, lane) : 1u << 20;
+  // Kets whose form the bit-sliced kernels take are theirs.
+  const uint32_t nw = stat ? pairs_left(stat, rule, slots, lane) : 1u << 20;
   if (nw == 0u) {
     if (lane == 0u) partial[(uint64_t)group * L + l] = make_double2(0.0, 0.0);
     return;
@@ -299,7 +303,7 @@ __global__ __launch_bounds__(64 * kCHWaves, 8) void k_inner_ch_pairs(
   uint32_t bad = 0;
   for (uint64_t a = group; a < chi_k; a += groups) {
     const uint64_t* rk = rec_k + a * R;
-    if (stat && (uint32_t)__popcll(uniform64(rk[6u * n + 4u])) + (nw - 1u) <= kQuadMaxVars) continue;
+    if (stat && quad_takes(rule, (uint32_t)__popcll(uniform64(rk[6u * n + 4u])) + (nw - 1u), nw - 1u)) continue;
     const uint64_t colGk = act ? rk[lane] : 0ull;
     const uint64_t Growk = act ? rk[n + lane] : 0ull;
     const uint64_t Bsk = act ? rk[3u * n + lane] : 0ull;
@@ -515,12 +519,12 @@ __global__ __launch_bounds__(256) void k_inner_ch_total(const double2* __restric
 
 size_t inner_ch_record_words(uint32_t n, uint64_t chi) { return (size_t)chi * chrec_words(n); }
 
-static hipError_t launch_records(const TermsView& T, uint64_t* rec, const uint32_t* stat, uint32_t slots,
-                                 hipStream_t st) {
+static hipError_t launch_records(const TermsView& T, uint64_t* rec, const uint32_t* stat, const QuadRule& rule,
+                                 uint32_t slots, hipStream_t st) {
   for (uint64_t first = 0; first < T.chi; first += kWaveTerms) {
     const uint64_t count = std::min(kWaveTerms, T.chi - first);
     hipLaunchKernelGGL(k_chrec, dim3((uint32_t)((count + kCHWaves - 1) / kCHWaves)), dim3(64 * kCHWaves), 0, st,
-                       terms_from(T, first), count, rec + first * chrec_words(T.n), stat, slots);
+                       terms_from(T, first), count, rec + first * chrec_words(T.n), stat, rule, slots);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -528,7 +532,7 @@ static hipError_t launch_records(const TermsView& T, uint64_t* rec, const uint32
 }
 
 hipError_t launch_inner_ch_records(const TermsView& T, uint64_t* rec, hipStream_t st) {
-  return launch_records(T, rec, nullptr, 0u, st);
+  return launch_records(T, rec, nullptr, QuadRule{}, 0u, st);
 }
 
 static uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
@@ -541,9 +545,16 @@ static uint32_t inner_ch_groups(uint64_t chi_k, uint32_t L) {
 
 InnerChPlan inner_ch_plan(uint32_t n, uint64_t chi_k, uint32_t L, bool sliced) {
   InnerChPlan P{};
-  P.sliced = sliced && L >= sliced_min_bras(n);
-  if (P.sliced) P.quad = quad_plan(n, chi_k, L, std::min(n, kSlicedSlots));
+  // The bit-sliced kernels' records and slices are worth making where they would take
+  // a form of usual size (0.8 n variables, a few constraints); the pair kernel is
+  // launched unless they take whatever there can be.
+  P.quad = quad_plan(n, chi_k, L, std::min(n, kSlicedSlots));
+  P.sliced = sliced && quad_takes(P.quad.rule, std::min(4u * n / 5u, kQuadClassMax[1]), std::min(n / 4u, 8u));
   P.pairs = !P.sliced || 2u * n > kQuadMaxVars;
+  if (P.sliced)
+    for (uint32_t w = 0; w <= P.quad.slots; ++w)
+      for (uint32_t nc = w; nc <= w + n; ++nc) P.pairs = P.pairs || !quad_takes(P.quad.rule, nc, w);
+  if (!P.sliced) P.quad = QuadPlan{};
   P.groups = P.pairs ? inner_ch_groups(chi_k, L) : 0u;
   P.partial_elems = (size_t)(P.quad.rows + P.groups) * L;
   return P;
@@ -565,9 +576,9 @@ hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerC
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const uint32_t* const stat = P.sliced ? quad_stat(P.quad, work) : nullptr;
-    if (rec_k != rec_b && (e = launch_records(K, rec_k, stat, P.quad.slots, st)) != hipSuccess) return e;
+    if (rec_k != rec_b && (e = launch_records(K, rec_k, stat, P.quad.rule, P.quad.slots, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_inner_ch_pairs, dim3((uint32_t)blocks), dim3(64 * kCHWaves), 0, st, rec_k, K.b, K.chi, rec_b, L,
-                       n, P.groups, bra_blocks, stat, P.quad.slots,
+                       n, P.groups, bra_blocks, stat, P.quad.rule, P.quad.slots,
                        partial + (size_t)P.quad.rows * L, err);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }

@@ -314,8 +314,31 @@ hipError_t launch_amp_mfma(const AmpMfmaInst* insts_d, const AmpItem* items_d, u
 // states, counts (max |v|, 64 - min |v|, max constraints) in `words` 8-byte words,
 // and `rows` rows of L partial sums.
 constexpr uint32_t kQuadMaxVars = 59;
+// The kernels' classes by size, and which pairs pay in them: a pass costs a class's
+// kernel the same for up to 128 states, and grows with the constraints w held as
+// columns, where the pair kernel of inner_ch.hip pays per state and by the form's size
+// nc.  Calls with 20000 kets, in µs, w = 0 and 32 constraints, beyond what both share:
+//   27 variables  n = 24 158 and -, 40 328 and -, 50 450 and 745 (w = 20), 64 950 and -;
+//   47 variables  n = 28 305 and -, 40 548 and 1170, 50 684 and 1506, 64 980 and 2080;
+//   59 variables  n = 36 - and 2400, 50 1683 and 3254, 64 2201 and 4300;
+//   one pair per wave, per bra: 23 (nc = 12), 31 (20), 33 to 40 (27), 41 to 53 (40), 49 to
+//   62 (48), 71 (59), and about 1.45 times that where the two supports share 32
+//   dimensions or more, nc - 2 w (its 64-bit path: 69, 80, 89).
+// cost[k] (32 + w) against per (110 + 9 nc), per = states per batch; cost is 0 for
+// equatorial states, which have no other kernel, and for bras where the choice would
+// cost more than it saves.
+struct QuadRule {
+  uint32_t cost[3], per;
+};
+constexpr uint32_t kQuadClassMax[3] = {27u, 47u, kQuadMaxVars};
+__host__ __device__ constexpr bool quad_takes(const QuadRule& r, uint32_t nc, uint32_t w) {
+  if (nc > kQuadMaxVars) return false;
+  const uint32_t c = nc <= kQuadClassMax[0] ? r.cost[0] : nc <= kQuadClassMax[1] ? r.cost[1] : r.cost[2];
+  return c * (32u + w) * 20u <= r.per * (110u + 9u * nc) * (nc >= 32u + 2u * w ? 29u : 20u);
+}
 struct QuadPlan {
   uint64_t chi;  // terms of a pass: a set can be taken in several
+  QuadRule rule;
   uint32_t n_batches, slots, ne1, rows;
   bool many;  // more than one launch by size: the counts are kept
   size_t rec_words, slice_words, words;

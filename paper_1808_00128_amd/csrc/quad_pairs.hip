@@ -307,6 +307,7 @@ struct QuadArgs {
   const uint32_t* stat;
   double2* partial;  // this launch's rows
   uint32_t n, ne1, slots, L, n_waves, n_batches;
+  QuadRule rule;
   uint32_t nc_lo, nc_hi;  // the variables (without the extra one) this launch takes
   bool add;               // to the partial sums that are there
   bool many;              // there are other launches: the counts tell whether this one has any terms
@@ -330,7 +331,13 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   bool any_term = true;  // uniform over the grid
   if (A.slots) w = quad_stat_max(A.stat, 2u, lane);
   if (w > A.slots) w = 1u << 20;  // more constraints than columns: not for these kernels
-  if (A.many) any_term = quad_stat_max(A.stat, 0u, lane) + w >= A.nc_lo && 64u - quad_stat_max(A.stat, 1u, lane) + w <= A.nc_hi;
+  // The forms of this class that the rule gives to these kernels: those from some
+  // size on.
+  uint32_t nc_lo = A.nc_lo;
+  if (A.slots)
+    while (nc_lo <= A.nc_hi && !quad_takes(A.rule, nc_lo, w)) ++nc_lo;
+  if (A.many) any_term = quad_stat_max(A.stat, 0u, lane) + w >= nc_lo && 64u - quad_stat_max(A.stat, 1u, lane) + w <= A.nc_hi;
+  any_term = any_term && nc_lo <= A.nc_hi;
   double ar[2] = {0.0, 0.0}, ai[2] = {0.0, 0.0};
   if (any_term) {
     const uint4* src = reinterpret_cast<const uint4*>(A.sl) + (size_t)batch * slice_entries(n, ne1);
@@ -348,7 +355,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       const uint32_t nv = uniform32((uint32_t)hdr & 0xFFu), m = uniform32((uint32_t)(hdr >> 8) & 0xFFu);
       const uint32_t om = uniform32((uint32_t)(hdr >> 16) & 7u);
       const uint32_t nc = nv + w;
-      if (nc < A.nc_lo || nc > A.nc_hi) continue;
+      if (nc < nc_lo || nc > A.nc_hi) continue;
       const uint64_t kdlo = r[1], kdhi = r[2];
       const uint64_t* __restrict__ hrow = r + RL.hrow;
       const uint32_t* __restrict__ rp = reinterpret_cast<const uint32_t*>(r + RL.p);
@@ -602,7 +609,9 @@ namespace {
 struct QuadClass {
   uint32_t nc_lo, nc_hi, nw, waves;  // variables taken, waves per workgroup, waves that fill the chip
 };
-constexpr QuadClass kClasses[3] = {{0, 27, 8, 4096}, {28, 47, 8, 2048}, {48, kQuadMaxVars, 4, 1024}};
+constexpr QuadClass kClasses[3] = {{0, kQuadClassMax[0], 8, 4096},
+                                   {kQuadClassMax[0] + 1u, kQuadClassMax[1], 8, 2048},
+                                   {kQuadClassMax[1] + 1u, kQuadClassMax[2], 4, 1024}};
 
 uint32_t class_waves(const QuadClass& c, uint64_t chi, uint32_t n_batches) {
   const uint64_t want = std::max<uint32_t>(c.waves / n_batches, 1u);
@@ -617,6 +626,19 @@ QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots) {
   P.chi = chi;
   P.n_batches = (L + 127u) / 128u;
   P.slots = slots;
+  // Up to 23 qubits no form is of the largest class, and 8 bras pay for the others: no
+  // second set of records (n = 20, chi = 20000, 8 bras 353 µs and 380).
+  if (slots && (n > 23u || L < 8u)) {
+    // Linear in n; from 55 qubits on a slice leaves room for one workgroup of the
+    // smallest class per compute unit, and from 56 on deep sets have forms past the
+    // largest class as well, so that its waves share what is left unevenly (n = 58,
+    // |v| = 55..58: 24 bras 2.99 ms with a part of the kets, 2.0 by pairs).
+    const double small = std::max(40.0, 9.5 * n - 40.0) * (n >= 55u ? 1.55 : 1.0);
+    const double us[3] = {small, std::max(100.0, 20.0 * n - 300.0),
+                          std::max(800.0, 35.4 * n - 70.0) * (n >= 56u ? 1.5 : 1.0)};
+    for (int k = 0; k < 3; ++k) P.rule.cost[k] = (uint32_t)(us[k] * 10.0 / 32.0);
+  }
+  P.rule.per = std::max(1u, L / P.n_batches);
   P.ne1 = n + slots + 1u;
   for (const QuadClass& c : kClasses)
     if (c.nc_lo <= n + slots) P.rows += class_waves(c, chi, P.n_batches);
@@ -679,6 +701,7 @@ hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, con
   A.n = T.n;
   A.ne1 = P.ne1;
   A.slots = P.slots;
+  A.rule = P.rule;
   A.L = L;
   A.n_batches = P.n_batches;
   A.many = P.many;
