@@ -425,7 +425,7 @@ __host__ __device__ constexpr uint32_t inner_srow_bytes(uint32_t n) { return (n 
 // index maps XCD-aware: workgroups are dealt to the 8 XCDs in turn, and the
 // batches of one term group are consecutive on one XCD, so a term's record
 // is read from HBM once per XCD-resident group rather than once per batch.
-__global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, uint64_t count, bool add,
+__global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, uint64_t count,
                                                     const uint64_t* __restrict__ rec,
                                                     const uint64_t* __restrict__ at,
                                                     const uint64_t* __restrict__ planes, uint32_t L,
@@ -467,11 +467,7 @@ __global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, uint64_t co
                       accr, acci);
   }
   if (bad && lane == 0u) atomicOr(err, 1u);
-  if (l < L) {
-    double2* const p = partial + ((uint64_t)group * L + l);
-    const double2 before = add ? *p : make_double2(0.0, 0.0);
-    *p = make_double2(before.x + accr, before.y + acci);
-  }
+  if (l < L) partial[(uint64_t)group * L + l] = make_double2(accr, acci);
 }
 
 // overlap_l = the sum of the groups' partials in FP64, in a fixed order: a
@@ -480,7 +476,7 @@ __global__ __launch_bounds__(64, 2) void k_inner_pairs(TermsView Tv, uint64_t co
 // 122 us for 100 states, a serial chain of loads; this takes 5 us).
 constexpr uint32_t kRedX = 4, kRedSlices = 64;
 __global__ __launch_bounds__(256) void k_inner_reduce(const double2* __restrict__ partial,
-                                                      uint32_t n_blocks, uint32_t L, uint32_t n,
+                                                      uint32_t n_blocks, uint32_t L, uint32_t n, bool add,
                                                       double2* __restrict__ overlap,
                                                       double* __restrict__ eta) {
   __shared__ double2 part[kRedSlices][kRedX];
@@ -504,6 +500,10 @@ __global__ __launch_bounds__(256) void k_inner_reduce(const double2* __restrict_
   for (uint32_t k = 0; k < kRedSlices; ++k) {
     re += part[k][xl].x;
     im += part[k][xl].y;
+  }
+  if (add) {  // to the sums over the terms of the passes before
+    re += overlap[l].x;
+    im += overlap[l].y;
   }
   overlap[l] = make_double2(re, im);
   eta[l] = ldexp(re * re + im * im, (int)n);
@@ -549,8 +549,9 @@ InnerPlan inner_plan(const TermsView& T, uint32_t L, uint64_t pass) {
   return P;
 }
 
-// Terms with more than kQuadMaxVars variables (n > kQuadMaxVars) among `count`.
-static hipError_t launch_wide(const TermsView& T, uint64_t count, bool add, const uint64_t* Aoff, const uint8_t* Adiag,
+// Terms with more than kQuadMaxVars variables (n > kQuadMaxVars) among `count`; more:
+// A by state is there from an earlier pass.
+static hipError_t launch_wide(const TermsView& T, uint64_t count, bool more, const uint64_t* Aoff, const uint8_t* Adiag,
                               uint32_t L, const InnerPlan& P, double2* partial, uint64_t* work, uint32_t* err,
                               hipStream_t st) {
   const uint32_t n = T.n;
@@ -559,11 +560,11 @@ static hipError_t launch_wide(const TermsView& T, uint64_t count, bool add, cons
   uint64_t* planes = at + (size_t)n * P.Lp;
   hipLaunchKernelGGL(k_inner_prep, dim3((uint32_t)((count + kWaves - 1) / kWaves)), dim3(64 * kWaves), 0, st, T, count,
                      rec);
-  if (!add)
+  if (!more)
     hipLaunchKernelGGL(k_inner_atrans, dim3((P.Lp + 255u) / 256u), dim3(256), 0, st, Aoff, Adiag, n, L, P.Lp, at, planes);
   const size_t sm = (size_t)inner_gtab_bytes() + inner_srow_bytes(n);
   const dim3 grid(P.n_groups * P.n_batches);
-  hipLaunchKernelGGL(k_inner_pairs, grid, dim3(64), sm, st, T, count, add, rec, at, planes, L, P.Lp, P.n_groups,
+  hipLaunchKernelGGL(k_inner_pairs, grid, dim3(64), sm, st, T, count, rec, at, planes, L, P.Lp, P.n_groups,
                      P.n_batches, partial, err);
   return hipGetLastError();
 }
@@ -573,20 +574,20 @@ hipError_t launch_inner(const TermsView& T, const uint64_t* Aoff, const uint8_t*
                         double* eta, double* eta_sum, uint32_t* err, hipStream_t st) {
   const uint32_t n = T.n;
   hipError_t e;
-  if ((e = launch_quad_equatorial(Aoff, Adiag, n, L, P.quad, work, st)) != hipSuccess) return e;
+  const uint32_t rows = P.quad.rows + (P.wide ? P.n_groups : 0u);
   for (uint64_t first = 0; first < T.chi; first += P.pass) {
     const TermsView V = terms_from(T, first);
     const uint64_t count = std::min(P.pass, T.chi - first);
     if ((e = launch_quad_prep(V, count, P.quad, work, st)) != hipSuccess) return e;
-    if ((e = launch_quad_pairs(V, count, L, P.quad, work, partial, first > 0, st)) != hipSuccess) return e;
+    if (first == 0 && (e = launch_quad_equatorial(Aoff, Adiag, n, L, P.quad, work, st)) != hipSuccess) return e;
+    if ((e = launch_quad_pairs(V, count, L, P.quad, work, partial, st)) != hipSuccess) return e;
     if (P.wide && (e = launch_wide(V, count, first > 0, Aoff, Adiag, L, P, partial + (size_t)P.quad.rows * L,
                                    work + P.quad.words, err, st)) != hipSuccess)
       return e;
+    hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, rows, L, n, first > 0,
+                       overlap, eta);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const uint32_t rows = P.quad.rows + (P.wide ? P.n_groups : 0u);
-  hipLaunchKernelGGL(k_inner_reduce, dim3((L + kRedX - 1) / kRedX), dim3(256), 0, st, partial, rows, L, n, overlap, eta);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_eta_sum, dim3(1), dim3(256), 0, st, eta, L, eta_sum);
   return hipGetLastError();
 }

@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t pairs_left(const uint32_t* __restrict__ stat
   if (w > slots) w = 1u << 20;
   const uint32_t most = quad_stat_max(stat, 0u, lane) + w, least = 64u - quad_stat_max(stat, 1u, lane) + w;
   bool all = most <= kQuadMaxVars;
-  for (uint32_t k = 0; k < 3u; ++k) {  // a class's smallest form pays last
+  for (uint32_t k = 0; k < 3u; ++k) {  // the classes that there are forms of
     const uint32_t lo = k ? kQuadClassMax[k - 1u] + 1u : 0u, at = least > lo ? least : lo;
     if (at <= kQuadClassMax[k] && at <= most) all = all && quad_takes(rule, at, w);
   }
@@ -568,7 +568,7 @@ hipError_t launch_inner_ch(const TermsView& K, const TermsView& Tb, const InnerC
   if (P.sliced) {
     if ((e = launch_quad_prep(K, K.chi, P.quad, work, st)) != hipSuccess) return e;
     if ((e = launch_quad_bras(Tb, rec_b, chrec_words(n), L, P.quad, work, st)) != hipSuccess) return e;
-    if ((e = launch_quad_pairs(K, K.chi, L, P.quad, work, partial, false, st)) != hipSuccess) return e;
+    if ((e = launch_quad_pairs(K, K.chi, L, P.quad, work, partial, st)) != hipSuccess) return e;
   }
   if (P.pairs) {
     const uint32_t bra_blocks = (L + kCHWaves - 1) / kCHWaves;

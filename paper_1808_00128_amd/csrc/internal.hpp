@@ -324,17 +324,20 @@ constexpr uint32_t kQuadMaxVars = 59;
 //   one pair per wave, per bra: 23 (nc = 12), 31 (20), 33 to 40 (27), 41 to 53 (40), 49 to
 //   62 (48), 71 (59), and about 1.45 times that where the two supports share 32
 //   dimensions or more, nc - 2 w (its 64-bit path: 69, 80, 89).
-// cost[k] (32 + w) against per (110 + 9 nc), per = states per batch; cost is 0 for
-// equatorial states, which have no other kernel, and for bras where the choice would
-// cost more than it saves.
+// cost[k] (32 + w) against per (110 + 9 nc) at a usual nc of the class, per = states per
+// batch; cost is 0 for equatorial states, which have no other kernel, and for bras
+// where the choice would cost more than it saves.
 struct QuadRule {
   uint32_t cost[3], per;
 };
-constexpr uint32_t kQuadClassMax[3] = {27u, 47u, kQuadMaxVars};
+constexpr uint32_t kQuadClassMax[3] = {27u, 47u, kQuadMaxVars}, kQuadClassUsual[3] = {22u, 40u, 54u};
+// Forms of class k, and a form of nc variables.
+__host__ __device__ constexpr bool quad_takes_class(const QuadRule& r, uint32_t k, uint32_t w) {
+  const uint32_t nc = kQuadClassUsual[k];
+  return r.cost[k] * (32u + w) * 20u <= r.per * (110u + 9u * nc) * (nc >= 32u + 2u * w ? 29u : 20u);
+}
 __host__ __device__ constexpr bool quad_takes(const QuadRule& r, uint32_t nc, uint32_t w) {
-  if (nc > kQuadMaxVars) return false;
-  const uint32_t c = nc <= kQuadClassMax[0] ? r.cost[0] : nc <= kQuadClassMax[1] ? r.cost[1] : r.cost[2];
-  return c * (32u + w) * 20u <= r.per * (110u + 9u * nc) * (nc >= 32u + 2u * w ? 29u : 20u);
+  return nc <= kQuadMaxVars && quad_takes_class(r, nc <= kQuadClassMax[0] ? 0u : nc <= kQuadClassMax[1] ? 1u : 2u, w);
 }
 struct QuadPlan {
   uint64_t chi;  // terms of a pass: a set can be taken in several
@@ -356,9 +359,8 @@ hipError_t launch_quad_equatorial(const uint64_t* Aoff, const uint8_t* Adiag, ui
                                   const QuadPlan& P, uint64_t* work, hipStream_t st);
 hipError_t launch_quad_bras(const TermsView& Tb, const uint64_t* chrec, uint32_t chrec_words, uint32_t L,
                             const QuadPlan& P, uint64_t* work, hipStream_t st);
-// add: to the partial sums that are there.
 hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, const QuadPlan& P, uint64_t* work,
-                             double2* partial, bool add, hipStream_t st);
+                             double2* partial, hipStream_t st);
 
 // Inner products with equatorial states: L states in batches of 64 (Lp =
 // L rounded up), partial sums per term group, and a device workspace of

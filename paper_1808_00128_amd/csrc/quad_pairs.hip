@@ -73,8 +73,11 @@ __device__ __forceinline__ uint32_t row_xor(uint32_t x) {
   x ^= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x140, 0xF, 0xF, true);
   return x;
 }
-// A & ~B, A | B, (A & ~B) | C as builtins: written with plain operators, the
-// complements of a whole unrolled loop were merged into wrong truth tables.
+// A & ~B, A | B, (A & ~B) | C as builtins.  What went wrong with plain operators is
+// the running mask of the pivot search kept as its complement (none &= ~s1, the pick
+// s1 & none, over all rows of an unrolled step): the chain of complements was merged
+// into three-input operations with wrong truth tables.  Masks that one step hands to
+// the next stay in these forms; the edge tests fail for the other.
 enum : uint32_t { kAndNot = 0x30, kOr = 0xFC, kAndNotOr = 0xBA };
 __device__ __forceinline__ uint32_t and_xor(uint32_t a, uint32_t b, uint32_t c) { return bop3<kAndXor>(a, b, c); }
 
@@ -308,8 +311,8 @@ struct QuadArgs {
   double2* partial;  // this launch's rows
   uint32_t n, ne1, slots, L, n_waves, n_batches;
   QuadRule rule;
+  uint32_t cls;           // this launch's class
   uint32_t nc_lo, nc_hi;  // the variables (without the extra one) this launch takes
-  bool add;               // to the partial sums that are there
   bool many;              // there are other launches: the counts tell whether this one has any terms
 };
 
@@ -331,13 +334,10 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   bool any_term = true;  // uniform over the grid
   if (A.slots) w = quad_stat_max(A.stat, 2u, lane);
   if (w > A.slots) w = 1u << 20;  // more constraints than columns: not for these kernels
-  // The forms of this class that the rule gives to these kernels: those from some
-  // size on.
-  uint32_t nc_lo = A.nc_lo;
-  if (A.slots)
-    while (nc_lo <= A.nc_hi && !quad_takes(A.rule, nc_lo, w)) ++nc_lo;
-  if (A.many) any_term = quad_stat_max(A.stat, 0u, lane) + w >= nc_lo && 64u - quad_stat_max(A.stat, 1u, lane) + w <= A.nc_hi;
-  any_term = any_term && nc_lo <= A.nc_hi;
+  if (A.slots) any_term = w <= A.slots && quad_takes_class(A.rule, A.cls, w);
+  if (A.many)
+    any_term = any_term && quad_stat_max(A.stat, 0u, lane) + w >= A.nc_lo &&
+               64u - quad_stat_max(A.stat, 1u, lane) + w <= A.nc_hi;
   double ar[2] = {0.0, 0.0}, ai[2] = {0.0, 0.0};
   if (any_term) {
     const uint4* src = reinterpret_cast<const uint4*>(A.sl) + (size_t)batch * slice_entries(n, ne1);
@@ -355,7 +355,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
       const uint32_t nv = uniform32((uint32_t)hdr & 0xFFu), m = uniform32((uint32_t)(hdr >> 8) & 0xFFu);
       const uint32_t om = uniform32((uint32_t)(hdr >> 16) & 7u);
       const uint32_t nc = nv + w;
-      if (nc < nc_lo || nc > A.nc_hi) continue;
+      if (nc < A.nc_lo || nc > A.nc_hi) continue;
       const uint64_t kdlo = r[1], kdhi = r[2];
       const uint64_t* __restrict__ hrow = r + RL.hrow;
       const uint32_t* __restrict__ rp = reinterpret_cast<const uint32_t*>(r + RL.p);
@@ -594,11 +594,7 @@ __global__ __launch_bounds__((64 * NW), OCC) void k_quad_pairs(QuadArgs A) {
   }
 #pragma unroll
   for (uint32_t u = 0; u < 2u; ++u)
-    if (l0 + u < A.L) {
-      double2* const p = A.partial + ((size_t)row0 * A.L + l0 + u);
-      const double2 before = A.add ? *p : make_double2(0.0, 0.0);
-      *p = make_double2(before.x + ar[u], before.y + ai[u]);
-    }
+    if (l0 + u < A.L) A.partial[(size_t)row0 * A.L + l0 + u] = make_double2(ar[u], ai[u]);
 }
 
 }  // namespace
@@ -630,12 +626,14 @@ QuadPlan quad_plan(uint32_t n, uint64_t chi, uint32_t L, uint32_t slots) {
   // second set of records (n = 20, chi = 20000, 8 bras 353 µs and 380).
   if (slots && (n > 23u || L < 8u)) {
     // Linear in n; from 55 qubits on a slice leaves room for one workgroup of the
-    // smallest class per compute unit, and from 56 on deep sets have forms past the
-    // largest class as well, so that its waves share what is left unevenly (n = 58,
-    // |v| = 55..58: 24 bras 2.99 ms with a part of the kets, 2.0 by pairs).
+    // smallest class per compute unit.  Where a call holds the largest class it mostly
+    // holds other forms as well, which leaves the class's waves uneven shares: a
+    // quarter more, and half from 56 qubits on, where deep sets have forms past it
+    // (n = 50, 48 bras, |v| = 25: 2.80 ms with a part of the kets and 1.96 by pairs; n = 58,
+    // |v| = 55..58, 24 bras 2.99 and 2.0).
     const double small = std::max(40.0, 9.5 * n - 40.0) * (n >= 55u ? 1.55 : 1.0);
     const double us[3] = {small, std::max(100.0, 20.0 * n - 300.0),
-                          std::max(800.0, 35.4 * n - 70.0) * (n >= 56u ? 1.5 : 1.0)};
+                          std::max(800.0, 35.4 * n - 70.0) * (n >= 56u ? 1.5 : 1.25)};
     for (int k = 0; k < 3; ++k) P.rule.cost[k] = (uint32_t)(us[k] * 10.0 / 32.0);
   }
   P.rule.per = std::max(1u, L / P.n_batches);
@@ -689,12 +687,11 @@ hipError_t launch_quad_bras(const TermsView& Tb, const uint64_t* chrec, uint32_t
 }
 
 hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, const QuadPlan& P, uint64_t* work,
-                             double2* partial, bool add, hipStream_t st) {
+                             double2* partial, hipStream_t st) {
   QuadArgs A{};
   A.rec = work;
   A.b = T.b;
   A.chi = count;
-  A.add = add;
   A.sl = reinterpret_cast<const uint32_t*>(work + P.rec_words);
   A.info = reinterpret_cast<const uint32_t*>(work + P.rec_words + P.slice_words);
   A.stat = quad_stat(P, work);
@@ -710,6 +707,7 @@ hipError_t launch_quad_pairs(const TermsView& T, uint64_t count, uint32_t L, con
   for (int k = 0; k < 3; ++k) {
     const QuadClass& c = kClasses[k];
     if (c.nc_lo > T.n + P.slots) break;
+    A.cls = (uint32_t)k;
     A.nc_lo = c.nc_lo;
     A.nc_hi = c.nc_hi;
     A.n_waves = class_waves(c, P.chi, P.n_batches);

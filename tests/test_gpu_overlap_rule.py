@@ -15,11 +15,12 @@ pytestmark = pytest.mark.gpu
 
 def _takes(n, bras, nc, w):
     small = max(40.0, 9.5 * n - 40.0) * (1.55 if n >= 55 else 1.0)
-    us = (small, max(100.0, 20.0 * n - 300.0), max(800.0, 35.4 * n - 70.0) * (1.5 if n >= 56 else 1.0))
+    us = (small, max(100.0, 20.0 * n - 300.0), max(800.0, 35.4 * n - 70.0) * (1.5 if n >= 56 else 1.25))
     k = 0 if nc <= 27 else 1 if nc <= 47 else 2
+    usual = (22, 40, 54)[k]
     per = max(1, bras // ((bras + 127) // 128))
     cost = 0 if n <= 23 and bras >= 8 else int(us[k] * 10 / 32)
-    return nc <= 59 and cost * (32 + w) * 20 <= per * (110 + 9 * nc) * (29 if nc >= 32 + 2 * w else 20)
+    return nc <= 59 and cost * (32 + w) * 20 <= per * (110 + 9 * usual) * (29 if usual >= 32 + 2 * w else 20)
 
 
 # (n, |v| of the two halves, |v| of the bras, bras)
