@@ -526,12 +526,13 @@ __global__ __launch_bounds__(256) void k_eta_sum(const double* __restrict__ eta,
 
 }  // namespace
 
-// Waves per batch of 64 states, each over chi / groups terms: 512, and with
-// few batches as many more as fill the chip: a wave's terms are a serial chain.  A
-// multiple of 8 (the XCD-aware block order).
-uint32_t term_groups(uint64_t chi, uint32_t n_batches) {
-  const uint32_t want = std::max<uint32_t>(512u, 3072u / n_batches);
-  const uint32_t g = (uint32_t)std::min<uint64_t>(want, chi);
+// Waves per batch of 64 states, each over chi / groups terms (a multiple of 8: the
+// XCD-aware block order).  A wave's terms are a serial chain, so the groups fill
+// the chip's 2048 places for them also with one batch (n = 63, |v| = 61, chi = 20000,
+// calls in ms with 512, 1024, 2048 and 3072 groups: 1 state 12.7, 7.0, 3.9 and 4.6, 130
+// states 14.2, 12.9, 10.6 and 10.9, 1000 states 54.9, 54.2, 53.6 and 53.3).
+uint32_t term_groups(uint64_t chi) {
+  const uint32_t g = (uint32_t)std::min<uint64_t>(2048u, chi);
   return g >= 8u ? g & ~7u : g;
 }
 
@@ -542,7 +543,7 @@ InnerPlan inner_plan(const TermsView& T, uint32_t L, uint64_t pass) {
   P.wide = T.n > kQuadMaxVars;
   P.Lp = (L + 63u) / 64u * 64u;
   P.n_batches = P.Lp / 64u;
-  P.n_groups = term_groups(pass, P.n_batches);
+  P.n_groups = term_groups(pass);
   P.partial_elems = (size_t)(P.quad.rows + (P.wide ? P.n_groups : 0u)) * L;
   P.work_words = P.quad.words;
   if (P.wide) P.work_words += (size_t)pass * inner_rec_words(T.n) + (size_t)T.n * P.Lp + 2u * (size_t)P.Lp;
