@@ -25,8 +25,8 @@
 // tiles of 32 terms; the four waves of a workgroup hold different strings and
 // share each tile's weights through LDS (double buffered, filled by loads
 // that go straight to LDS), so a 1 KB weight operand feeds 2 NB x 4
-// instructions.  With few strings the waves take different tiles instead and
-// read the weights from memory, each used once.  A lane holds one string
+// instructions.  With few strings and 128 tiles or more the waves take different
+// tiles instead and read the weights from memory, each used once.  A lane holds one string
 // (column) and 16 of a tile's 32 terms; the terms are assigned to rows so that
 // a lane's registers are two groups of 8 consecutive terms in order: the FP32
 // sum adds the 8 terms of a group plainly and joins the group sums with a
@@ -613,7 +613,7 @@ __global__ __launch_bounds__(256) void k_amp_mfma_reduce(const AmpMfmaInst* __re
   __shared__ double2 part[kRedSlices][kRedX];
   const uint32_t xl = threadIdx.x % kRedX, sl = threadIdx.x / kRedX;
   const uint64_t total = prefix[n_inst];
-  for (uint64_t g0 = (uint64_t)blockIdx.x * kRedX; g0 < total; g0 += (uint64_t)gridDim.x * kRedX) {
+  for (uint64_t g0 = (uint64_t)blockIdx.x * kRedX;;) {
     const uint64_t g = g0 + xl;
     const bool on = g < total;
     uint32_t lo = 0;
@@ -646,6 +646,8 @@ __global__ __launch_bounds__(256) void k_amp_mfma_reduce(const AmpMfmaInst* __re
       }
       insts[lo].out[i] = make_double2(sr, si);
     }
+    g0 += (uint64_t)gridDim.x * kRedX;
+    if (g0 >= total) break;  // uniform; a block's first strings are always there
     __syncthreads();  // the slices are read before the next strings' are written
   }
 }
