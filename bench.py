@@ -188,6 +188,17 @@ def shape_name(value):
     return f"{lanes} lanes/term, {what} in registers"
 
 
+def tuned_name(B, lanes, tune_ms):
+    """What the autotuner kept.  The default, which mixes mappings span by span, reads
+    as 4 lanes with columns; it was kept unless that value was the fastest."""
+    name = shape_name(lanes)
+    if lanes != (4 | B.CHSIM_EVOLVE_LDS):
+        return name
+    times = [t for t in tune_ms if t > 0]
+    fastest = times and min(times) == tune_ms[B.TUNE_SHAPES.index(lanes)]
+    return f"default, or {name}" if fastest else "default (mixed by span)"
+
+
 def mean_popcount(words):
     return float(np.mean([bin(int(w)).count("1") for w in np.asarray(words).ravel()]))
 
@@ -383,6 +394,13 @@ def pair_chain_step_bytes(chi, n_chain, win=METRO_WINDOW):
     return float(chi * (4 * n_chain + 8 * n_chain / win + 17 * (1 + (win + 2) / 4) + 33 / 2))
 
 
+def record_step_bytes(n, chi):
+    """Bytes of the amplitude records that an FP64 pass over the strings of a learned
+    step reads: per 32 terms S KB of weights, S = ceil((n (n + 1) / 2 + 1) / 64), the
+    head and 2 KB of doubles (not the KB of floats)."""
+    return float(-(-chi // 32) * 1024 * ((n * (n + 1) // 2 + 1 + 63) // 64 + 3))
+
+
 def table_chain_step_bytes(chi, n_chain):
     """The hot-path table's per-step bytes for single flips with one j per step
     shared by all chains: 16 B of state read + write per chain, 17 B for row j
@@ -452,14 +470,15 @@ def bench_learned(torch, B, W, stats, steps=1000, n_chain=64, chi=1 << 20, eps=0
     learned = chain_report(stats, ltr, lac, lms, burn, lcost, lfl)
     lbytes = chain_step_bytes(chi, n, n_chain)
     lach = lbytes * steps / (lms / 1e3) / 1e9
-    lown = float(chi * 32 * ((n * (n + 1) // 2 + 1 + 63) // 64 + 4))
+    lown = record_step_bytes(n, chi)
     learned["roofline"] = roof("hbm", lach, HBM_PEAK_BPS / 1e9, "GB/s", MEASURED.get("hbm"),
                                kernel="k_mlp_fused (masks and network) + k_amp_mfma<double> (proposals) + k_learned_accept",
                                traffic=None, bytes_per_step=lbytes,
                                count="chi (17 n + 16 chains + 33) B per step (every row staged for the masks)",
                                bytes_per_step_own=lown,
-                               own_count="the amplitude records: (n (n + 1) / 2 + 1) / 64 + 4 KB per 32 terms and "
-                                         "step (the caches are brought up to date once per call)",
+                               own_count="the amplitude records: (n (n + 1) / 2 + 1) / 64 + 3 KB per 32 terms and "
+                                         "step (weights, head, doubles; the caches are brought up to date once "
+                                         "per call; condition words past the third level not counted)",
                                frac_own_count=round(lown * steps / (lms / 1e3) / HBM_PEAK_BPS, 4))
     net.close()
     progress("metropolis: learned chains with the untrained network")
@@ -559,7 +578,6 @@ def bench_uneven(torch, B, W, steps=2, warmup=1):
     xs = [torch.from_numpy(sp["x"].view(np.int64)).to(dev) for sp in insts]
     for k in range(len(insts)):
         ctx.set_evolve_lanes(-1, inst=k)
-    ctx.set_amp_strings(-1)
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
     t_ev, t_batch, t_single = [], [], []
     outs = None
@@ -585,7 +603,6 @@ def bench_uneven(torch, B, W, steps=2, warmup=1):
     ms_s = float(np.mean(t_single))
     ms_e = float(np.mean(t_ev))
     ok = all(bool(torch.isfinite(o).all()) for o in outs)
-    amp_strings, _ = ctx.amp_strings()
     ctx.close()
     return {"workload": cfg["name"] + ": 64 circuits, n~U{20..60}, 40n Clifford gates + 10..60 phase "
                                       "slots, chi log-uniform 2^10..2^20 (sparsified), 1024 uniform x each",
@@ -593,7 +610,6 @@ def bench_uneven(torch, B, W, steps=2, warmup=1):
             "ms_evolve_all": ms_e, "ms_amplitudes_batched": ms_b, "ms_amplitudes_per_instance": ms_s,
             "evals_per_s_batched": evals / (ms_b / 1e3), "evals_per_s_per_instance": evals / (ms_s / 1e3),
             "evals_per_s_step": evals / ((ms_e + ms_b) / 1e3),
-            "amplitude_strings_per_item": amp_strings,
             "amplitude_roofline": roof("mfma", fp4 / (ms_b / 1e3) / 1e12, FP4_PEAK_OPS / 1e12, "TFLOP/s (FP4)"),
             "finite": ok}
 
@@ -611,7 +627,6 @@ def bench_hidden_shift(torch, B, W, steps=5, warmup=2):
     stream = torch.cuda.current_stream()
     ctx = B.Context([cfg, cfg])  # instance 1: scratch store for the marginal sampler
     ctx.set_evolve_lanes(-1)
-    ctx.set_amp_strings(-1)
     gates = B.gate_array(circ)
     ctx.apply_gates(gates)
     rng = np.random.default_rng(cfg["seed"] + 1)
@@ -749,7 +764,6 @@ def main():
         del src, dst
     ctx = B.Context([cfg])
     ctx.set_evolve_lanes(args.evolve_lanes)  # -1: autotune the mapping during warmup
-    ctx.set_amp_strings(-1)  # autotune bitstrings per work item at the first amplitude call
     gates = B.gate_array(circ)
     x_dev = torch.from_numpy(xs.view(np.int64)).to(dev)
     out32 = torch.empty((n_x, 2), dtype=torch.float64, device=dev)
@@ -779,7 +793,6 @@ def main():
     for i in range(max(1, args.warmup)):
         step(i, False)
     lanes, tune_ms = ctx.evolve_lanes()
-    amp_strings, amp_tune_ms = ctx.amp_strings()
     pf_mode, pf_levels, pf_frac = ctx.prefix_share()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -858,11 +871,9 @@ def main():
                                 "distinct_prefixes": ev_stats["distinct"],
                                 "gate_applications": {k: ev_stats[k] for k in ("H", "CX", "CZ", "S", "cond")},
                                 "per_term_gate_applications": chi * circ.n_gates},
-        "evolve_autotune": {"shape": shape_name(lanes), "terms_per_wave": 64 // (lanes & 0xff),
+        "evolve_autotune": {"shape": tuned_name(B, lanes, tune_ms),
                             "ms_by_shape": {shape_name(v): round(t, 4)
                                             for v, t in zip(B.TUNE_SHAPES, tune_ms)}},
-        "amplitude_autotune": {"strings_per_item": amp_strings,
-                               "ms_by_value": {"256": round(amp_tune_ms[0], 4), "512": round(amp_tune_ms[1], 4)}},
         "amplitude_kernel_evals_per_s": chi * n_x / (ms_amp / 1e3),
         "evolve_gates_per_s_per_term_count": chi * circ.n_gates / (ms_ev / 1e3),
         "evolve_gates_per_s_executed": executed_apps / (ms_ev / 1e3),
