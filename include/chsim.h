@@ -126,7 +126,11 @@ chsim_status chsim_apply_clifford(chsim_ctx* ctx, uint32_t inst, const chsim_gat
 /* out[2i], out[2i+1] = <x_i|psi>, psi = sum_alpha b_alpha |phi_alpha> (not
  * normalised), per Eqs. (amplitude), (amplitude1).  flags: CHSIM_FP64 or
  * CHSIM_FP32C, optionally | CHSIM_DEVICE_PTRS.  EINVAL: a bitstring has a bit
- * >= n set (checked for host pointers only), n_x == 0. */
+ * >= n set (checked for host pointers only), n_x == 0.  n <= 60: the instance keeps
+ * records of its terms beside them (n = 50: 1168 bytes per term) until they change
+ * or another call of the context needs the memory; past 1 GiB in a context they
+ * are laid out only where an eighth of the device memory stays free, and the table
+ * kernel (464 bytes per term) takes the call otherwise. */
 chsim_status chsim_amplitudes(chsim_ctx* ctx, uint32_t inst, const uint64_t* x, size_t n_x,
                               double* out, uint32_t flags, void* stream);
 
@@ -141,10 +145,12 @@ typedef struct chsim_amp_request {
   double* out;
 } chsim_amp_request;
 
-/* chsim_amplitudes for several requests in one launch (instances of
- * different n, chi and bitstring counts share one persistent grid that pulls
- * (request, term range, bitstring chunk) work items), same formula, flags and
- * results as one call per request.  Host bitstring arrays are checked as in
+/* chsim_amplitudes for several requests at once: the requests on instances of
+ * n <= 60 share one launch of the matrix-core kernel over (request, term range,
+ * bitstring chunk) work items dealt longest first, the others (n > 60, or no room
+ * for records) one persistent grid of the table kernel that pulls its items from
+ * a queue.  Same formula and flags as one call per request, results to rounding
+ * (the terms may be cut into other ranges).  Host bitstring arrays are checked as in
  * chsim_amplitudes.  EINVAL: n_req == 0, a request with a bad instance, a null
  * array or n_x == 0.  The plan is cached in the context: a context must not be
  * used from two streams at once. */
@@ -153,8 +159,9 @@ chsim_status chsim_amplitudes_batch(chsim_ctx* ctx, const chsim_amp_request* req
 
 /* chsim_amplitudes for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same formula, kernels and results as chsim_amplitudes with the same
- * flags, but every intermediate (the prologue rows and term constants, the
+ * the same formula and flags, by the table kernel at every n (chsim_amplitudes
+ * takes the matrix cores for n <= 60, so that the two agree to rounding there, and
+ * bit for bit above), but every intermediate (the prologue rows and term constants, the
  * per-range partial sums, the work items and the queue counter) lives in a
  * fixed device array of 64 MiB that the library's code object holds on each
  * GPU until the process ends; no hipMalloc, hipFree or other allocating call
@@ -334,6 +341,12 @@ typedef struct chsim_learned_args {
 
 /* Advance the chains started by chsim_metropolis_init with the learned
  * proposal (requires n <= 62 and the network's n equal to the instance's).
+ * The proposals' amplitudes come from the matrix cores (n <= 60) or from the
+ * chains' caches, by the number of chains, the call's number of steps and, in
+ * calls of fewer than 8 steps, whether the instance's amplitude records are there:
+ * the two agree to rounding, so that the same steps cut into other calls can differ
+ * in the last bits of amp, and in a decision only where U is that close to the
+ * ratio.
  * Outputs as chsim_metropolis_step, plus n_flips[c*n_steps + t] = |m| (may be
  * NULL; a step with |m| = 0 leaves the chain in place and counts as
  * accepted). */

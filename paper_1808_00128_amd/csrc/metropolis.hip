@@ -330,10 +330,13 @@ __global__ __launch_bounds__(kPThreads) void k_propose(TermsView T, MetroView Mv
 // against about 240 for twelve trees.
 //
 // VALU issue bounds it: 102 instructions per 64 terms, chain and pair of steps at
-// n = 50 (about 190 of the 283 µs per launch at chi = 2^20 and 64 chains with one
+// n = 50 (about 190 of the 279 µs per launch at chi = 2^20 and 64 chains with one
 // flip bit; 537 MB read, and as much written by every second launch).  Before, one
-// step per launch with the values computed per proposal: 196 µs per step, now 141;
-// n = 12, chi = 2^16, 64 chains with their own bits (kPacked): 29 and 10.7.
+// step per launch with the values computed per proposal: 196 µs per step, now 140;
+// n = 12, chi = 2^16, 64 chains with their own bits (kPacked): 29 and 10.7.  Few chains
+// (whole calls, 40 steps with own bits, n = 50, chi = 200000, in µs, one step per launch
+// and now): 1 chain 469 and 440, 2 chains 533 and 528, 5 chains 711 and 644, 12 chains
+// 1025 and 974.
 constexpr uint32_t kGWaves = 4;
 constexpr uint32_t kGSub = kMetroTile / 64;  // terms per lane
 constexpr uint32_t kModeWrite = 1u;
