@@ -591,10 +591,25 @@ __global__ __launch_bounds__(64 * kGWaves) void k_propose_pair(TermsView T, Metr
   }
 }
 
-// The rows' form: packed while n bits of F and M and two of gamma fit a word
-// (chi = 2^16, 64 chains with their own bits, n = 12: 10.7 µs per step; the term
-// store's rows read per chain took 29), 32-bit halves up to n = 30 (M and F in one
-// register each), 64-bit words above.  Workgroups along the chains: with few tiles the chains are split over more
+// The rows' form: 32-bit halves up to n = 30 (M and F in one register each),
+// 64-bit words above; packed where n bits of F and M and two of gamma fit a word
+// and reading every row of a tile costs less than the bits' rows.  It does while
+// there are no more rows than slots; while the rows (17 bytes each) stay in the
+// L2s, 4 MB per XCD; and past them from a number of chains with bits of their own
+// that grows with n.  Whole calls of 40 steps, own bits, in µs, packed and not:
+// n = 12, chi = 2^16: 2 chains 289 and 317, 12 chains 347 and 413 (one bit for all
+// chains: 287 and 310, 341 and 359); chi = 2^20: n = 8, 1 chain 1230 and 1069, 2
+// chains 1089 and 1222; n = 12, 3 chains 1510 and 1376, 4 chains 1566 and 1627, 12
+// chains 2243 and 3604; n = 15, 5 chains 1957 and 1674, 6 chains 2062 and 2037, 8
+// chains 2223 and 2425.  (One bit for all of them is not known here: n = 15, 6
+// chains 2055 and 1281, 12 chains 2542 and 1666.)
+constexpr uint64_t kPackedBytes = 28ull << 20;
+bool packs_rows(uint32_t n, uint64_t chi, uint32_t n_chain) {
+  if (n > kPackedMaxN) return false;
+  return n <= kSlots || chi <= kPackedBytes / (17u * n) || n_chain >= std::max(2u, n * n / 32u);
+}
+
+// Workgroups along the chains: with few tiles the chains are split over more
 // workgroups (the tile's rows staged by each), up to about four per compute
 // unit; a wave keeps at least two chains, the pair of one pass.
 uint32_t chain_splits(uint32_t n_tiles, uint32_t n_chain) {
@@ -606,7 +621,7 @@ hipError_t launch_pair(const TermsView& T, MetroView& Mv, uint32_t step, uint32_
                        uint32_t npend, uint32_t mode, hipStream_t st) {
   const dim3 grid(Mv.n_tiles, chain_splits(Mv.n_tiles, Mv.n_chain));
   const size_t vals = 5u * kMetroTile * sizeof(double2);
-  if (T.n <= kPackedMaxN)
+  if (packs_rows(T.n, T.chi, Mv.n_chain))
     hipLaunchKernelGGL(k_propose_pair<kPacked>, grid, dim3(64 * kGWaves), vals + (size_t)T.n * kMetroTile * 4u, st, T,
                        Mv, step, nprop, pbase, npend, mode);
   else if (T.n <= kSlots32MaxN)
