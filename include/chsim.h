@@ -198,8 +198,9 @@ chsim_status chsim_inner_products(chsim_ctx* ctx, uint32_t inst, const uint64_t*
  * intersection of the two supports, an exponential sum of Lemma (Exponential
  * Sum); the paper gives its O(n^3) cost (Sec. "Fast norm estimation") and
  * defers the method to earlier work.  overlap has 2 chi_bra doubles; with
- * CHSIM_DEVICE_PTRS overlap and total are device pointers and the call only
- * enqueues, else it returns after copying.  EINVAL: instances of different n,
+ * CHSIM_DEVICE_PTRS overlap and total are device pointers; the call returns once
+ * its work on the stream is done (it reads an error flag back), so it cannot be
+ * captured into a graph.  EINVAL: instances of different n,
  * null overlap.  EUNSUPPORTED: n = 64 with a ket term whose |v| = 64. */
 chsim_status chsim_inner_products_ch(chsim_ctx* ctx, uint32_t inst, uint32_t bra_inst, double* overlap,
                                      double* total, uint32_t flags, void* stream);
